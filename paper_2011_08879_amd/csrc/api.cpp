@@ -2676,7 +2676,7 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
         const values v = own_values(A);
         const int64_t ldv = gmres_ld(n);
         dbuf V(c, (size_t)(m + 1) * ldv * 8);
-        if (c->opts.single_workgroup && n <= gmres_small_max_rows() && m <= kGmresSmallKrylov &&
+        if (c->opts.single_workgroup && gmres_small_fits(n, m) &&
             (A->fmt == GKO_FMT_CSR || A->fmt == GKO_FMT_CSR_MERGE)) {
             // the whole solve on one workgroup, one launch
             dbuf state(c, sizeof(gmres_state));
@@ -2694,16 +2694,17 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
             return h.done;
         }
         // work arrays carved from one buffer
+        const bool compact = gmres_compact(n);
         const int64_t np = gmres_partial_elems(n, m);
-        const int64_t sizes[] = {np, m + 2, m + 2, 1, 1, m + 1, (int64_t)(m + 1) * m, m, m,
+        const int64_t sizes[] = {np, compact ? np : 0, m + 2, m + 2, 1, 1, (int64_t)(m + 1) * m, m, m,
                                  m + 1, m};
         int64_t total = 0;
         for (int64_t z : sizes) total += z;
-        dbuf work(c, total * 8), state(c, sizeof(gmres_state));
+        dbuf work(c, total * 8), state(c, 2 * sizeof(gmres_state));
         double *q = work.as<double>();
         gmres_work wk;
-        double **slots[] = {&wk.partials, &wk.dot1, &wk.dot2, &wk.upd1, &wk.upd2, &wk.hcol,
-                            &wk.H,        &wk.cs,   &wk.sn,   &wk.g,    &wk.y};
+        double **slots[] = {&wk.partials, &wk.partials2, &wk.dot1, &wk.dot2, &wk.upd1, &wk.upd2,
+                            &wk.H,        &wk.cs,        &wk.sn,   &wk.g,    &wk.y};
         static_assert(std::size(sizes) == std::size(slots), "one size per work array");
         for (size_t i = 0; i < std::size(slots); ++i) {
             *slots[i] = q;
@@ -2715,20 +2716,22 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
         h.maxit = maxit;
         h.done = kRunning;
         h.cycle_done = 1;
-        auto *S = state.as<gmres_state>();
+        auto *S = state.as<gmres_state>(), *S2 = S + 1;
         HIPC(hipMemcpyAsync(S, &h, sizeof(h), hipMemcpyHostToDevice, s));
         c->sync();   // h is reused as the read-back buffer below
         double *V0 = V.as<double>();
         for (;;) {
             HIPC(hipMemcpyAsync(V0, b, n * 8, hipMemcpyDeviceToDevice, s));
             spmv_dispatch(A, v, -1.0, x, 1.0, V0);
-            HIPC(gmres_cycle_start(s, n, V0, S, wk));
+            HIPC(gmres_cycle_start(s, n, V0, S, S2, wk));
+            if (compact) std::swap(S, S2);
             HIPC(hipMemcpyAsync(&h, S, sizeof(h), hipMemcpyDeviceToHost, s));
             c->sync();
             if (h.done != kRunning) break;
             for (int j = 0; j < m; ++j) {
                 spmv_dispatch(A, v, 1.0, V0 + (int64_t)j * ldv, 0.0, V0 + (int64_t)(j + 1) * ldv);
-                HIPC(gmres_arnoldi_step(s, n, m, j, V0, ldv, S, wk));
+                HIPC(gmres_arnoldi_step(s, n, m, j, V0, ldv, S, S2, wk));
+                if (compact) std::swap(S, S2);
                 if ((j + 1) % check_every == 0 && j + 1 < m) {
                     HIPC(hipMemcpyAsync(&h, S, sizeof(h), hipMemcpyDeviceToHost, s));
                     c->sync();

@@ -125,9 +125,12 @@ hipError_t cgs_direction(hipStream_t s, int64_t n, const void *r, const void *q,
 // v0 = b - A x into basis slot 0, calls gmres_cycle_start, then for each step
 // j writes w = A v_j into slot j+1 and calls gmres_arnoldi_step, and closes
 // the cycle with gmres_cycle_end (x += V_k y).  Flags and scalars live in
-// gmres_state; every kernel of a closed cycle returns at once.
+// gmres_state; every kernel of a closed cycle returns at once.  Where
+// gmres_compact(n) holds, cycle_start and arnoldi_step read the state st and
+// leave the new one in next (the caller swaps the two); otherwise they update
+// st in place.
 constexpr int kGmresMaxKrylov = 128;   // largest restart length
-constexpr int kGmresSmallKrylov = 64;  // largest restart length of the one-workgroup solve
+constexpr int kGmresSmallKrylov = 40;  // largest restart length of the one-workgroup solve
 constexpr int kGmresMaxBlocks = 2048;  // grid of the multi-vector passes (1024: 12% slower)
 struct gmres_state {
     double stop;        // tol * ||b||
@@ -145,10 +148,9 @@ struct gmres_state {
     int32_t reorths;    // steps that took a second round
 };
 struct gmres_work {
-    double *partials;      // gmres_partial_elems(n, m)
+    double *partials, *partials2;  // gmres_partial_elems(n, m) each (partials2: compact only)
     double *dot1, *dot2;   // m + 2 each
     double *upd1, *upd2;   // 1 each
-    double *hcol;          // m + 1
     double *H;             // (m + 1) * m, row-major
     double *cs, *sn;       // m each
     double *g;             // m + 1
@@ -156,17 +158,17 @@ struct gmres_work {
 };
 int64_t gmres_ld(int64_t n);   // leading dimension of the basis
 int64_t gmres_partial_elems(int64_t n, int m);
+bool gmres_compact(int64_t n);
 hipError_t gmres_cycle_start(hipStream_t s, int64_t n, double *V, gmres_state *st,
-                             const gmres_work &wk);
+                             gmres_state *next, const gmres_work &wk);
 hipError_t gmres_arnoldi_step(hipStream_t s, int64_t n, int m, int j, double *V, int64_t ldv,
-                              gmres_state *st, const gmres_work &wk);
+                              gmres_state *st, gmres_state *next, const gmres_work &wk);
 hipError_t gmres_cycle_end(hipStream_t s, int64_t n, int m, const double *V, int64_t ldv, double *x,
                            gmres_state *st, const gmres_work &wk);
-// The whole solve of a small CSR system (n <= gmres_small_max_rows(), m <=
-// kGmresSmallKrylov) in one launch of one workgroup, from x (in/out), with
+// The whole solve of a small CSR system (gmres_small_fits(n, m)) in one launch of one workgroup, from x (in/out), with
 // the basis in V ((m + 1) ldv doubles).  out: iter, cycles, reorths, done,
 // est, beta, k as the multi-kernel path leaves them in gmres_state.
-int64_t gmres_small_max_rows();
+bool gmres_small_fits(int64_t n, int m);
 hipError_t gmres_small(hipStream_t s, int64_t n, int m, const int32_t *rp, const int32_t *col,
                        const double *val, const double *b, double *x, double *V, int64_t ldv,
                        double stop, int maxit, gmres_state *out);

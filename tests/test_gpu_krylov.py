@@ -225,6 +225,25 @@ def test_gmres_one_workgroup_matches_multikernel(g, orc, gen_mod, ctx, m, maxit)
         assert abs(i1["rel_residual"] - i0["rel_residual"]) <= 1e-10
 
 
+@pytest.mark.parametrize("n", [2, 255, 257, 32768, 32769, 65536, 65537, 131073, 524288, 524289])
+def test_gmres_multikernel_sizes(g, orc, gen_mod, ctx, n):
+    """The multi-kernel passes at the edges of their workgroup sizes (256, 512
+    and 1024 rows per workgroup up to 524,288 rows, then the large-grid
+    passes), with a restart length past the 32 basis vectors kept in
+    registers and a second cycle: 38 steps are the oracle's, to the bound of
+    the k-step comparison above (classical against modified Gram-Schmidt)."""
+    A = gen_mod.laplace1d(n)
+    b = orc.spmv(A, gen_mod.uniform(17, n))
+    ctx.set_solver_opts(krylov_dim=34, single_workgroup=0)
+    rc, xo, info_o = orc.gmres(A, b, tol=1e-13, maxit=38, m=34)
+    x = dev(np.zeros(n))
+    info = g.gmres(g.Matrix.from_csr(*A), dev(b), x, tol=1e-13, maxit=38)
+    if n > 2:
+        assert info["iterations"] == info_o["iters"] == 38
+        assert info["outer_iterations"] == info_o["cycles"] == 2
+    assert np.linalg.norm(host(x) - xo) <= 1e-10 * np.linalg.norm(xo)
+
+
 def test_gmres_statuses(g, gen_mod, ctx):
     d = np.array([1.0, 2.0, 3.0] * 17)[:50]
     Dm = g.Matrix.from_csr(np.arange(51, dtype=np.int32), np.arange(50, dtype=np.int32), d)
