@@ -836,6 +836,48 @@ bool fused_view(gko_matrix A, const values &v, fused_matrix &f) {
     return false;
 }
 
+// The same for the kernels of mid-size systems (midsize.hip): also CSR stored
+// for merge-path, whose arrays are CSR's, unless its rows are irregular.
+bool mid_view(gko_matrix A, const values &v, fused_matrix &f) {
+    if (A->n < 1 || A->nnz < 1) return false;
+    if (A->fmt == GKO_FMT_CSR_MERGE && A->merge_rows) {
+        f = fused_matrix{};
+        f.t = v.t;
+        f.n = A->n;
+        f.rp = A->rp;
+        f.col = A->col;
+        f.val = v.val;
+    } else if (!fused_view(A, v, f)) {
+        return false;
+    }
+    if (f.format == fused_matrix::csr)
+        f.lanes = A->nnz > 96 * A->n ? 32 : csr_row_lanes(A->n, A->nnz);
+    return mid_fits(f, A->nnz);
+}
+
+// The states and partials that the kernels of a mid-size iteration pass on:
+// three states and a region of partials for each kernel.
+constexpr int kStates = 3;
+
+struct mid_flow {
+    krylov_scalars *states;
+    double *partials;
+    int parts[3] = {0, 0, 0};  // of each region's sums
+
+    double *region(int r) const { return partials + r * 3 * kMidParts; }
+    mid_sums leave(int r) { return {region(r), &parts[r]}; }
+    // state i after the scalar step on region r's sums, stored as state j
+    scalar_link take(int i, int j, int r) const {
+        return {states + i, states + j, region(r), parts[r]};
+    }
+    scalar_link as_is(int i) const { return {states + i, nullptr, nullptr, 0}; }
+};
+static_assert(3 * 3 * kMidParts * sizeof(double) <= kPartialBytes, "three regions of partials fit");
+
+// Iterations of one replayed interval: vectors that alternate between two
+// buffers must be back where they began.
+int mid_interval(int check_every) { return check_every + check_every % 2; }
+
 // One polling interval of a solver loop (check_every iterations of kernel
 // launches) as a HIP graph: the first run() captures the body's launches on a
 // stream of its own, which the body sees as the context stream, and every
@@ -902,10 +944,11 @@ class interval_graph {
 // preconditioner) of n values, the grid reductions' partials and ticket, the
 // iteration scalars and a norm slot.  The solvers allocate them per call
 // (cg_buffers); gko_cg_solve_noalloc carves them from the library's static
-// scratch array instead.  graphs = false keeps the iteration kernel by
+// scratch array instead (S: kStates states).  graphs = false keeps the iteration kernel by
 // kernel (no graph is instantiated).
 struct cg_workspace {
     void *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;
+    void *p2 = nullptr;  // mid-size systems: p's second buffer
     double *partials = nullptr, *nrm = nullptr;
     unsigned *ticket = nullptr;
     krylov_scalars *S = nullptr;
@@ -913,16 +956,18 @@ struct cg_workspace {
 };
 
 struct cg_buffers {
-    dbuf r, p, q, z, partials, ticket, sc, nrm;
+    dbuf r, p, q, z, p2, partials, ticket, sc, nrm;
     cg_buffers(gko_context c, int64_t n, size_t vb, int bs)
         : r(c, n * vb), p(c, n * vb), q(c, n * vb), z(c, bs > 0 ? n * vb : 8),
-          partials(c, kPartialBytes), ticket(c, 8), sc(c, sizeof(krylov_scalars)), nrm(c, 8) {}
+          p2(c, n <= kMidRows ? n * vb : 8), partials(c, kPartialBytes), ticket(c, 8),
+          sc(c, kStates * sizeof(krylov_scalars)), nrm(c, 8) {}
     cg_workspace view() {
         cg_workspace w;
         w.r = r.p;
         w.p = p.p;
         w.q = q.p;
         w.z = z.p;
+        w.p2 = p2.p;
         w.partials = partials.as<double>();
         w.nrm = nrm.as<double>();
         w.ticket = ticket.as<unsigned>();
@@ -944,7 +989,9 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
     HIPC(scalars_reset(s, S, maxit));
     void *zz = bs > 0 ? w.z : w.r;
     fused_matrix fm;
-    const bool fused = fused_view(A, v, fm);
+    const bool mid = mid_view(A, v, fm);
+    const bool fused = !mid && fused_view(A, v, fm);
+    mid_flow fl{S, w.partials};
     interval_graph graph(c, w.graphs ? n : kGraphMaxRows + 1);
     solve_result res;
     krylov_scalars h{};
@@ -956,6 +1003,17 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
         while (h.done == kRunning) {
             graph.run([&] {
                 const hipStream_t st = c->stream;
+                if (mid) {
+                    void *p[2] = {w.p, w.p2};
+                    for (int j = 0; j < mid_interval(check_every); ++j) {
+                        HIPC(mid_cg_product(st, fm, zz, p[j % 2], p[1 - j % 2], w.q, flexible,
+                                            j == 0 ? fl.as_is(0) : fl.take(1, 0, 1), fl.leave(0)));
+                        HIPC(mid_cg_update(st, v.t, n, x, w.r, zz, p[1 - j % 2], w.q, inv, bs,
+                                           flexible, fl.take(0, 1, 0), fl.leave(1)));
+                    }
+                    HIPC(mid_cg_close(st, flexible, fl.take(1, 0, 1)));
+                    return;
+                }
                 for (int j = 0; j < check_every; ++j) {
                     if (fused) {
                         HIPC(cg_spmv(st, fm, w.p, w.q, S, w.partials, w.ticket));
@@ -1002,7 +1060,7 @@ solve_result pipecg_core(gko_matrix A, const values &v, const void *b, void *x, 
     const size_t pre = bs > 0 ? n * vb : 8;
     dbuf r(c, n * vb), w(c, n * vb), nn(c, n * vb), z(c, n * vb), sv(c, n * vb), p(c, n * vb);
     dbuf u(c, pre), m(c, pre), q(c, pre);
-    dbuf partials(c, kPartialBytes), ticket(c, 8), sc(c, sizeof(krylov_scalars)), nrm(c, 8);
+    dbuf partials(c, kPartialBytes), ticket(c, 8), sc(c, kStates * sizeof(krylov_scalars)), nrm(c, 8);
     HIPC(hipMemsetAsync(ticket.p, 0, 8, s));
     auto *S = sc.as<krylov_scalars>();
     HIPC(scalars_reset(s, S, maxit));
@@ -1017,6 +1075,9 @@ solve_result pipecg_core(gko_matrix A, const values &v, const void *b, void *x, 
     pv.u = bs > 0 ? u.p : r.p;
     pv.m = bs > 0 ? m.p : w.p;
     pv.q = bs > 0 ? q.p : sv.p;
+    fused_matrix fm;
+    const bool mid = bs == 0 && mid_view(A, v, fm);
+    mid_flow fl{S, partials.as<double>()};
     interval_graph graph(c, n);
     solve_result res;
     krylov_scalars h{};
@@ -1032,6 +1093,17 @@ solve_result pipecg_core(gko_matrix A, const values &v, const void *b, void *x, 
         h = read_back(c, S);
         while (h.done == kRunning) {
             graph.run([&] {
+                if (mid) {  // w alternates between its buffer and that of n = A m
+                    void *wb[2] = {w.p, nn.p};
+                    int cur = 0;
+                    for (int j = 0; j < mid_interval(check_every); ++j) {
+                        const scalar_link k = j == 0 ? fl.as_is(0) : fl.take(cur, 1 - cur, 1 - j % 2);
+                        if (j > 0) cur = 1 - cur;
+                        HIPC(mid_pipe(c->stream, fm, wb[j % 2], wb[1 - j % 2], pv, k, fl.leave(j % 2)));
+                    }
+                    HIPC(mid_pipe_close(c->stream, fl.take(cur, 0, 1)));
+                    return;
+                }
                 for (int j = 0; j < check_every; ++j) {
                     spmv_dispatch(A, v, 1.0, pv.m, 0.0, nn.p);
                     HIPC(pipe_update(c->stream, v.t, n, pv, inv, bs, S, partials.as<double>(),
@@ -2443,7 +2515,8 @@ gko_status gko_cg_solve(gko_matrix A, const void *b, void *x, double tol, int32_
 namespace {
 constexpr size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 constexpr size_t kNaSmall = 0, kNaMaxLen = 128, kNaTicket = 256, kNaScalars = 512;
-constexpr size_t kNaNorm = kNaScalars + round256(sizeof(krylov_scalars));
+constexpr size_t kNaNorm = kNaScalars + 256;
+static_assert(2 * sizeof(krylov_scalars) <= 256, "CG passes on two states");
 constexpr size_t kNaPartials = kNaNorm + 256;
 constexpr size_t kNaVectors = kNaPartials + round256(kPartialBytes);
 static_assert(sizeof(small_cg_result) <= kNaMaxLen, "small-CG result overlaps the max-length slot");
@@ -2451,6 +2524,7 @@ static_assert(sizeof(small_cg_result) <= kNaMaxLen, "small-CG result overlaps th
 constexpr int64_t kNaMaxRows = int64_t((kScratchBytes - kNaVectors) / 3 / 256 * 256 / 8);
 static_assert(kNaMaxRows == GKO_CG_NOALLOC_MAX_ROWS, "header limit out of date");
 static_assert(kScratchBytes == GKO_NOALLOC_SCRATCH_BYTES, "header scratch size out of date");
+static_assert(kNaVectors + 4 * round256(size_t(kMidRows) * 8) <= kScratchBytes, "p2 fits");
 }  // namespace
 
 gko_status gko_cg_solve_noalloc(gko_matrix A, const void *b, void *x, double tol, int32_t maxit) {
@@ -2493,6 +2567,7 @@ gko_status gko_cg_solve_noalloc(gko_matrix A, const void *b, void *x, double tol
         w.r = base + kNaVectors;
         w.p = base + kNaVectors + vb;
         w.q = base + kNaVectors + 2 * vb;
+        w.p2 = base + kNaVectors + 3 * vb;  // inside the array for n <= kMidRows
         w.graphs = false;
         HIPC(fill_zero(s, vt::f64, 1, w.ticket));
         const double bnorm = device_norm(c, vt::f64, n, b, w.nrm, w.partials, w.ticket);
@@ -2585,19 +2660,35 @@ gko_status gko_bicgstab_solve(gko_matrix A, const void *b, void *x, double tol, 
         const int64_t n = A->n;
         const values v = own_values(A);
         dbuf r(c, n * 8), rh(c, n * 8), p(c, n * 8), vv(c, n * 8), sv(c, n * 8), t(c, n * 8);
-        dbuf sc(c, sizeof(krylov_scalars));
+        dbuf sc(c, kStates * sizeof(krylov_scalars));
         auto *S = sc.as<krylov_scalars>();
+        fused_matrix fm;
+        const bool mid = mid_view(A, v, fm);
+        const bool fused = !mid && fused_view(A, v, fm);
+        dbuf v2(c, mid ? n * 8 : 8);
+        mid_flow fl{S, P};
         HIPC(scalars_reset(s, S, maxit));
         HIPC(hipMemcpyAsync(r.p, b, n * 8, hipMemcpyDeviceToDevice, s));
         spmv_dispatch(A, v, -1.0, x, 1.0, r.p);
         HIPC(bicg_init(s, n, b, r.p, rh.p, p.p, vv.p, tol, S, P, T));
-        fused_matrix fm;
-        const bool fused = fused_view(A, v, fm);
         krylov_scalars h = read_back(c, S);
         interval_graph graph(c, n);
         while (h.done == kRunning) {
             graph.run([&] {
                 const hipStream_t st = c->stream;
+                if (mid) {  // p alternates with s's buffer, v with v2
+                    void *pb[2] = {p.p, sv.p}, *vb[2] = {vv.p, v2.p};
+                    for (int j = 0; j < mid_interval(c->opts.check_every); ++j) {
+                        const int o = j % 2, k = 1 - o;
+                        HIPC(mid_bicg_v(st, fm, r.p, pb[o], vb[o], rh.p, pb[k], vb[k],
+                                        j == 0 ? fl.as_is(0) : fl.take(2, 0, 2), fl.leave(0)));
+                        HIPC(mid_bicg_t(st, fm, r.p, vb[k], t.p, fl.take(0, 1, 0), fl.leave(1)));
+                        HIPC(mid_bicg_update(st, n, x, r.p, rh.p, pb[k], vb[k], t.p, fl.take(1, 2, 1),
+                                             fl.leave(2)));
+                    }
+                    HIPC(mid_bicg_close(st, fl.take(2, 0, 2)));
+                    return;
+                }
                 for (int j = 0; j < c->opts.check_every; ++j) {
                     HIPC(bicg_p(st, n, r.p, vv.p, p.p, S));
                     if (fused) {
@@ -2632,19 +2723,33 @@ gko_status gko_cgs_solve(gko_matrix A, const void *b, void *x, double tol, int32
         const values v = own_values(A);
         dbuf r(c, n * 8), rh(c, n * 8), p(c, n * 8), u(c, n * 8), q(c, n * 8), w(c, n * 8),
             t(c, n * 8);
-        dbuf sc(c, sizeof(krylov_scalars));
+        dbuf sc(c, kStates * sizeof(krylov_scalars));
         auto *S = sc.as<krylov_scalars>();
+        fused_matrix fm;
+        const bool mid = mid_view(A, v, fm);
+        const bool fused = !mid && fused_view(A, v, fm);
+        mid_flow fl{S, P};
         HIPC(scalars_reset(s, S, maxit));
         HIPC(hipMemcpyAsync(r.p, b, n * 8, hipMemcpyDeviceToDevice, s));
         spmv_dispatch(A, v, -1.0, x, 1.0, r.p);
         HIPC(cgs_init(s, n, b, r.p, rh.p, p.p, u.p, tol, S, P, T));
-        fused_matrix fm;
-        const bool fused = fused_view(A, v, fm);
+        if (mid) HIPC(fill_zero(s, vt::f64, n, q.p));  // the first u = r + 0 q
         krylov_scalars h = read_back(c, S);
         interval_graph graph(c, n);
         while (h.done == kRunning) {
             graph.run([&] {
                 const hipStream_t st = c->stream;
+                if (mid) {  // p alternates with w's buffer
+                    void *pb[2] = {p.p, w.p};
+                    for (int j = 0; j < mid_interval(c->opts.check_every); ++j) {
+                        HIPC(mid_cgs_t(st, fm, r.p, q.p, pb[j % 2], rh.p, u.p, pb[1 - j % 2], t.p,
+                                       j == 0 ? fl.as_is(0) : fl.take(1, 0, 1), fl.leave(0)));
+                        HIPC(mid_cgs_w(st, fm, u.p, t.p, rh.p, q.p, x, r.p, fl.take(0, 1, 0),
+                                       fl.leave(1)));
+                    }
+                    HIPC(mid_cgs_close(st, fl.take(1, 0, 1)));
+                    return;
+                }
                 for (int j = 0; j < c->opts.check_every; ++j) {
                     if (fused) {
                         HIPC(cgs_spmv_alpha(st, fm, p.p, t.p, rh.p, S, P, T));

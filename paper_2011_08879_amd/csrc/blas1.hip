@@ -10,6 +10,7 @@
 #include <climits>
 #include <cmath>
 
+#include "bj_tile.hpp"
 #include "csr_rows.hpp"
 #include "device.hpp"
 #include "ell_rows.hpp"
@@ -41,7 +42,8 @@ int reduction_blocks(int64_t n) {
 // ------------------------------------------------------------------ finishing operations
 // What the totals of each reduction update, applied once per launch (by the
 // last block or by the finalize kernel).  skip() repeats the early-exit test
-// of the kernel whose partials are being summed.
+// of the kernel whose partials are being summed.  The scalar steps of the
+// iterations are in krylov_ops.hpp; these are the starts'.
 struct dot_op {
     double *result;
     bool sq;
@@ -58,49 +60,12 @@ struct cg_init_op {
         sc->rho = o[0];
         sc->rr = o[1];
         sc->bb = o[2];
+        sc->beta = 0.0;  // the first direction is z
         sc->stop2 = tol * tol * o[2];
         if (!std::isfinite(o[1]) || !std::isfinite(o[0])) sc->done = kBreakdown;
         else if (o[1] <= sc->stop2) sc->done = kConverged;
         else if (sc->iter >= sc->maxit) sc->done = kMaxIter;
         else sc->done = kRunning;
-    }
-};
-
-// alpha = rho / p.q; p.q <= 0 means A is not SPD.
-struct cg_alpha_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        const double pq = o[0];
-        sc->aux = pq;
-        if (!(pq > 0.0)) {
-            sc->done = std::isnan(pq) ? kBreakdown : kNotSpd;
-            sc->iter += 1;
-        } else {
-            sc->alpha = sc->rho / pq;
-        }
-    }
-};
-
-// After the update: totals r.z, r.r (and, for flexible CG, z.(r - r_old));
-// convergence test, then beta: r.z / rho (Fletcher-Reeves, CG) or
-// z.(r - r_old) / rho (Polak-Ribiere, flexible CG).
-struct cg_update_op {
-    krylov_scalars *sc;
-    bool flex;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->iter += 1;
-        sc->rr = o[1];
-        if (!std::isfinite(o[1]) || !std::isfinite(o[0])) {
-            sc->done = kBreakdown;
-        } else if (o[1] <= sc->stop2) {
-            sc->done = kConverged;
-        } else {
-            sc->beta = (flex ? o[2] : o[0]) / sc->rho;
-            sc->rho = o[0];
-            if (sc->iter >= sc->maxit) sc->done = kMaxIter;
-        }
     }
 };
 
@@ -123,67 +88,6 @@ struct bicg_init_op {
         else {
             sc->beta = (sc->rho / sc->rho_old) * (sc->alpha / sc->omega);
             sc->done = kRunning;
-        }
-    }
-};
-
-// alpha = rho / (rhat.v)
-struct bicg_alpha_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->aux = o[0];
-        if (!(fabs(o[0]) >= 1e-300)) sc->done = kBreakdown;
-        else sc->alpha = sc->rho / o[0];
-    }
-};
-
-// s.s: converging here finishes at the half step.
-struct bicg_s_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->iter += 1;
-        if (!std::isfinite(o[0])) sc->done = kBreakdown;
-        else if (o[0] <= sc->stop2) {
-            sc->half = 1;
-            sc->rr = o[0];
-        }
-    }
-};
-
-// omega = (t.s) / (t.t)
-struct bicg_omega_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0 || sc->half != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->aux = o[1];
-        if (!(o[1] >= 1e-300)) sc->done = kBreakdown;
-        else sc->omega = o[0] / o[1];
-    }
-};
-
-// After the update: totals r.r and the next rho = rhat.r.
-struct bicg_update_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        if (sc->half) {
-            sc->done = kConverged;
-            return;
-        }
-        sc->rr = o[0];
-        if (!std::isfinite(o[0])) sc->done = kBreakdown;
-        else if (o[0] <= sc->stop2) sc->done = kConverged;
-        else if (sc->omega == 0.0) sc->done = kBreakdown;
-        else {
-            sc->rho_old = sc->rho;
-            sc->rho = o[1];
-            if (!(fabs(o[1]) >= 1e-300)) sc->done = kBreakdown;
-            else {
-                sc->beta = (sc->rho / sc->rho_old) * (sc->alpha / sc->omega);
-                if (sc->iter >= sc->maxit) sc->done = kMaxIter;
-            }
         }
     }
 };
@@ -228,40 +132,6 @@ hipError_t scalars_reset(hipStream_t s, krylov_scalars *sc, int32_t maxit) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ block-Jacobi apply
-// z_i = sum_j D_b^{-1}[i mod bs][j] r_{b*bs + j}, j ascending, for the tile
-// of 256 rows starting at `base`, with entry (i, j) of a symmetric inverse
-// block read from its packed upper triangle (the (min, max) entry).  The
-// tile's packed blocks (contiguous because BS divides 256) and residuals are
-// staged in LDS with coalesced loads.  Slots of a short last block beyond n
-// are zero in `inv`.
-template <int BS>
-constexpr int bj_packed() { return BS * (BS + 1) / 2; }
-
-template <typename V, int BS>
-__device__ inline V bj_tile_apply(int64_t n, int64_t base, V ri, const V *__restrict__ inv,
-                                  V *r_lds, V *inv_lds) {
-    constexpr int P = bj_packed<BS>();
-    const int tid = threadIdx.x;
-    r_lds[tid] = ri;
-    const int64_t nb = (n + BS - 1) / BS;
-    const int64_t off = (base / BS) * P;
-    for (int t = tid; t < (kB / BS) * P; t += kB)
-        inv_lds[t] = (off + t < nb * P) ? inv[off + t] : V(0);
-    __syncthreads();
-    V z = V(0);
-    const int i = tid % BS, b0 = tid - i;
-    const V *D = inv_lds + (tid / BS) * P;
-    const int row_i = i * BS - i * (i - 1) / 2 - i;  // packed (i, j) = row_i + j, j >= i
-#pragma unroll
-    for (int j = 0; j < BS; ++j) {
-        const int idx = j >= i ? row_i + j : j * BS - j * (j - 1) / 2 - j + i;
-        z += D[idx] * r_lds[b0 + j];
-    }
-    __syncthreads();
-    return z;
-}
-
 // ------------------------------------------------------------------ CG
 // Start (or restart) from r = b - A x: z = M^-1 r, p = z, rho = r.z, rr = r.r,
 // bb = b.b; flags convergence at zero iterations.
@@ -271,14 +141,16 @@ __global__ __launch_bounds__(kB) void cg_init_kernel(int64_t n, const V *__restr
                                                      V *__restrict__ p, const V *__restrict__ inv,
                                                      double tol, krylov_scalars *sc,
                                                      red_args ra) {
-    __shared__ V r_lds[BS > 0 ? kB : 1];
-    __shared__ V inv_lds[BS > 0 ? kB / (BS > 0 ? BS : 1) * bj_packed<BS>() : 1];
+    __shared__ bj_lds<V, BS, kB> L;
     double a_rz = 0.0, a_rr = 0.0, a_bb = 0.0;
     for (int64_t base = (int64_t)blockIdx.x * kB; base < n; base += (int64_t)gridDim.x * kB) {
         const int64_t i = base + threadIdx.x;
         const V ri = i < n ? r[i] : V(0);
         V zi = ri;
-        if constexpr (BS > 0) zi = bj_tile_apply<V, BS>(n, base, ri, inv, r_lds, inv_lds);
+        if constexpr (BS > 0) {
+            bj_tile_stage<V, BS, kB>(n, base, inv, L);
+            zi = bj_tile_apply<V, BS, kB>(ri, L);
+        }
         if (i < n) {
             if constexpr (BS > 0) z[i] = zi;
             p[i] = zi;
@@ -322,7 +194,7 @@ template <typename V, typename Op>
 struct omega_dot {
     static constexpr int NV = 2;
     Op op;
-    __device__ bool skip() const { return op.skip(); }
+    __device__ bool skip() const { return op.skip() || op.sc->half != 0; }
     __device__ void add(double (&a)[NV], int64_t, V in, V out) const {
         a[0] += (double)out * (double)in;
         a[1] += (double)out * (double)out;
@@ -458,8 +330,7 @@ __global__ __launch_bounds__(kB) void cg_update_kernel(int64_t n, V *__restrict_
                                                        const V *__restrict__ q,
                                                        const V *__restrict__ inv,
                                                        krylov_scalars *sc, red_args ra) {
-    __shared__ V r_lds[BS > 0 ? kB : 1];
-    __shared__ V inv_lds[BS > 0 ? kB / (BS > 0 ? BS : 1) * bj_packed<BS>() : 1];
+    __shared__ bj_lds<V, BS, kB> L;
     if (sc->done) return;
     const double alpha = sc->alpha;
     double a_rz = 0.0, a_rr = 0.0, a_zt = 0.0;
@@ -473,7 +344,10 @@ __global__ __launch_bounds__(kB) void cg_update_kernel(int64_t n, V *__restrict_
             r[i] = ri;
         }
         V zi = ri;
-        if constexpr (BS > 0) zi = bj_tile_apply<V, BS>(n, base, ri, inv, r_lds, inv_lds);
+        if constexpr (BS > 0) {
+            bj_tile_stage<V, BS, kB>(n, base, inv, L);
+            zi = bj_tile_apply<V, BS, kB>(ri, L);
+        }
         if (i < n) {
             if constexpr (BS > 0) z[i] = zi;
             a_rz += (double)ri * (double)zi;
@@ -690,24 +564,6 @@ hipError_t cg_direction(hipStream_t s, vt t, int64_t n, const void *z, void *p,
 // yields the next alpha and beta.  Without a preconditioner u = r, m = w and
 // q = s, and the kernel carries the four vectors z, s, p, w besides x, r.
 
-// alpha and beta of the step that follows the sums gamma, delta:
-// first step beta = 0, alpha = gamma / delta; then beta = gamma / gamma_old,
-// alpha = gamma / (delta - beta gamma / alpha_old).  The denominator is
-// p.Ap in exact arithmetic, <= 0 means A is not SPD.
-__device__ inline void pipe_next(krylov_scalars *sc, double gamma, double delta, bool first) {
-    const double beta = first ? 0.0 : gamma / sc->rho;
-    const double den = first ? delta : delta - beta * gamma / sc->alpha;
-    sc->aux = den;
-    if (!(den > 0.0)) {
-        sc->done = std::isnan(den) ? kBreakdown : kNotSpd;
-        sc->iter += 1;
-        return;
-    }
-    sc->beta = beta;
-    sc->alpha = gamma / den;
-    sc->rho = gamma;
-}
-
 // Start: totals gamma, delta, r.r, b.b.
 struct pipe_init_op {
     krylov_scalars *sc;
@@ -722,22 +578,8 @@ struct pipe_init_op {
         else if (sc->iter >= sc->maxit) sc->done = kMaxIter;
         else {
             sc->done = kRunning;
-            pipe_next(sc, o[0], o[1], true);
+            pipe_next(*sc, o[0], o[1], true);
         }
-    }
-};
-
-// After an update: totals gamma, delta, r.r.
-struct pipe_update_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->iter += 1;
-        sc->rr = o[2];
-        if (!std::isfinite(o[2]) || !std::isfinite(o[0]) || !std::isfinite(o[1])) sc->done = kBreakdown;
-        else if (o[2] <= sc->stop2) sc->done = kConverged;
-        else if (sc->iter >= sc->maxit) sc->done = kMaxIter;
-        else pipe_next(sc, o[0], o[1], false);
     }
 };
 
@@ -746,12 +588,12 @@ template <typename V, int BS>
 __global__ __launch_bounds__(kB) void pipe_precond_kernel(int64_t n, const V *__restrict__ r,
                                                           V *__restrict__ u,
                                                           const V *__restrict__ inv) {
-    __shared__ V r_lds[kB];
-    __shared__ V inv_lds[kB / BS * bj_packed<BS>()];
+    __shared__ bj_lds<V, BS, kB> L;
     for (int64_t base = (int64_t)blockIdx.x * kB; base < n; base += (int64_t)gridDim.x * kB) {
         const int64_t i = base + threadIdx.x;
         const V ri = i < n ? r[i] : V(0);
-        const V ui = bj_tile_apply<V, BS>(n, base, ri, inv, r_lds, inv_lds);
+        bj_tile_stage<V, BS, kB>(n, base, inv, L);
+        const V ui = bj_tile_apply<V, BS, kB>(ri, L);
         if (i < n) u[i] = ui;
     }
 }
@@ -764,14 +606,16 @@ __global__ __launch_bounds__(kB) void pipe_init_kernel(int64_t n, const V *__res
                                                        const V *__restrict__ w, V *__restrict__ m,
                                                        const V *__restrict__ inv, double tol,
                                                        krylov_scalars *sc, red_args ra) {
-    __shared__ V r_lds[BS > 0 ? kB : 1];
-    __shared__ V inv_lds[BS > 0 ? kB / (BS > 0 ? BS : 1) * bj_packed<BS>() : 1];
+    __shared__ bj_lds<V, BS, kB> L;
     double a_g = 0.0, a_d = 0.0, a_rr = 0.0, a_bb = 0.0;
     for (int64_t base = (int64_t)blockIdx.x * kB; base < n; base += (int64_t)gridDim.x * kB) {
         const int64_t i = base + threadIdx.x;
         const V wi = i < n ? w[i] : V(0);
         V mi = wi;
-        if constexpr (BS > 0) mi = bj_tile_apply<V, BS>(n, base, wi, inv, r_lds, inv_lds);
+        if constexpr (BS > 0) {
+            bj_tile_stage<V, BS, kB>(n, base, inv, L);
+            mi = bj_tile_apply<V, BS, kB>(wi, L);
+        }
         if (i < n) {
             if constexpr (BS > 0) m[i] = mi;
             const double ri = (double)r[i], ui = (double)u[i], bi = (double)b[i];
@@ -794,8 +638,7 @@ __global__ __launch_bounds__(kB) void pipe_update_kernel(
     int64_t n, const V *__restrict__ nv, V *__restrict__ z, V *__restrict__ q, V *__restrict__ s,
     V *__restrict__ p, V *__restrict__ x, V *__restrict__ r, V *__restrict__ u, V *__restrict__ w,
     V *__restrict__ m, const V *__restrict__ inv, krylov_scalars *sc, red_args ra) {
-    __shared__ V r_lds[BS > 0 ? kB : 1];
-    __shared__ V inv_lds[BS > 0 ? kB / (BS > 0 ? BS : 1) * bj_packed<BS>() : 1];
+    __shared__ bj_lds<V, BS, kB> L;
     if (sc->done) return;
     const double alpha = sc->alpha, beta = sc->beta;
     double a_g = 0.0, a_d = 0.0, a_rr = 0.0;
@@ -828,7 +671,8 @@ __global__ __launch_bounds__(kB) void pipe_update_kernel(
             w[i] = wi;
         }
         if constexpr (BS > 0) {
-            const V mi = bj_tile_apply<V, BS>(n, base, wi, inv, r_lds, inv_lds);
+            bj_tile_stage<V, BS, kB>(n, base, inv, L);
+            const V mi = bj_tile_apply<V, BS, kB>(wi, L);
             if (i < n) m[i] = mi;
         }
         if (i < n) {

@@ -30,30 +30,12 @@ struct cgs_init_op {
         sc->rho = o[0];
         sc->rr = o[0];
         sc->bb = o[1];
+        sc->beta = 0.0;  // the first direction is r
         sc->stop2 = tol * tol * o[1];
         if (!std::isfinite(o[0])) sc->done = kBreakdown;
         else if (o[0] <= sc->stop2) sc->done = kConverged;
         else if (sc->iter >= sc->maxit) sc->done = kMaxIter;
         else sc->done = kRunning;
-    }
-};
-
-
-// After r -= alpha A (u + q): totals r.r, r.rhat; convergence, then beta.
-struct cgs_update_op {
-    krylov_scalars *sc;
-    __device__ bool skip() const { return sc->done != 0; }
-    __device__ void operator()(const double *o) const {
-        sc->iter += 1;
-        sc->rr = o[0];
-        if (!std::isfinite(o[0])) sc->done = kBreakdown;
-        else if (o[0] <= sc->stop2) sc->done = kConverged;
-        else if (sc->iter >= sc->maxit) sc->done = kMaxIter;
-        else if (!(fabs(o[1]) >= 1e-300)) sc->done = kBreakdown;
-        else {
-            sc->beta = o[1] / sc->rho;
-            sc->rho = o[1];
-        }
     }
 };
 

@@ -21,6 +21,13 @@ __device__ inline int64_t xcd_block(int64_t b, int64_t G) {
     return x * q + (x < r ? x : r) + b / kXcds;
 }
 
+// The hardware index of the workgroup that xcd_block maps to c.
+__device__ inline int64_t xcd_block_inverse(int64_t c, int64_t G) {
+    const int64_t q = G / kXcds, r = G % kXcds, longer = r * (q + 1);
+    if (c < longer) return c % (q + 1) * kXcds + c / (q + 1);
+    return (c - longer) % q * kXcds + r + (c - longer) / q;
+}
+
 // Workgroup order of the row-blocked kernels (row-per-thread CSR, ELL,
 // SELL-P, plain and fused with the CG product): XCD-contiguous up to
 // kXcdRowsMax rows, hardware order above.  Measured on the 27-point stencil

@@ -121,6 +121,53 @@ hipError_t cgs_update(hipStream_t s, int64_t n, void *r, const void *t, const vo
 hipError_t cgs_direction(hipStream_t s, int64_t n, const void *r, const void *q, void *u, void *p,
                          const krylov_scalars *sc);
 
+// Iterations of systems that mid_fits accepts, at most kMidRows rows (midsize.hip).  Each kernel
+// takes its scalars by a scalar_link and leaves its sums as *parts partials
+// each (up to 3 * kMidParts doubles).  lanes of a CSR matrix: 1, 4, 8 or 32.  p / p_old (and v / v_old, w / w_old) are different buffers.
+constexpr int64_t kMidRows = 2000000;
+constexpr int kMidBlocks = 512;          // workgroups of a grid
+constexpr int kMidParts = 4 * kMidBlocks;  // partials of a sum
+// nnz: entries of A; A.lanes set.
+bool mid_fits(const fused_matrix &A, int64_t nnz);
+struct mid_sums {
+    double *partials;
+    int *parts;
+};
+// p = z + beta p_old, q = A p (step: the update's sums); x += alpha p, r -=
+// alpha q, z = M^-1 r (step: p.q); close: the update's sums.
+hipError_t mid_cg_product(hipStream_t s, const fused_matrix &A, const void *z, const void *p_old,
+                          void *p, void *q, bool flexible, const scalar_link &k,
+                          const mid_sums &out);
+hipError_t mid_cg_update(hipStream_t s, vt t, int64_t n, void *x, void *r, void *z, const void *p,
+                         const void *q, const void *inv, int bs, bool flexible,
+                         const scalar_link &k, const mid_sums &out);
+hipError_t mid_cg_close(hipStream_t s, bool flexible, const scalar_link &k);
+// Pipelined CG without a preconditioner: an iteration (step: the sums of the
+// one before); v.z, v.s, v.p, v.x, v.r are used.
+hipError_t mid_pipe(hipStream_t s, const fused_matrix &A, const void *w_old, void *w,
+                    const pipe_vectors &v, const scalar_link &k, const mid_sums &out);
+hipError_t mid_pipe_close(hipStream_t s, const scalar_link &k);
+// BiCGSTAB: p = r + beta (p_old - omega v_old), v = A p (step: the update's
+// sums); t = A (r - alpha v) (step: rhat.v); the update of x and r (step: s.s,
+// t.s, t.t); close: the update's sums.
+hipError_t mid_bicg_v(hipStream_t s, const fused_matrix &A, const void *r, const void *p_old,
+                      const void *v_old, const void *rh, void *p, void *v, const scalar_link &k,
+                      const mid_sums &out);
+hipError_t mid_bicg_t(hipStream_t s, const fused_matrix &A, const void *r, const void *v, void *t,
+                      const scalar_link &k, const mid_sums &out);
+hipError_t mid_bicg_update(hipStream_t s, int64_t n, void *x, void *r, const void *rh, const void *p,
+                           const void *v, const void *t, const scalar_link &k, const mid_sums &out);
+hipError_t mid_bicg_close(hipStream_t s, const scalar_link &k);
+// CGS: u, p and t = A p (step: the sums of mid_cgs_w); q, x and r -= alpha A w
+// (step: t.rhat); close: the sums of mid_cgs_w.
+hipError_t mid_cgs_t(hipStream_t s, const fused_matrix &A, const void *r, const void *q,
+                     const void *p_old, const void *rh, void *u, void *p, void *t,
+                     const scalar_link &k, const mid_sums &out);
+hipError_t mid_cgs_w(hipStream_t s, const fused_matrix &A, const void *u, const void *t,
+                     const void *rh, void *q, void *x, void *r, const scalar_link &k,
+                     const mid_sums &out);
+hipError_t mid_cgs_close(hipStream_t s, const scalar_link &k);
+
 // Restarted GMRES (FP64, unpreconditioned; gmres.hip).  The host computes
 // v0 = b - A x into basis slot 0, calls gmres_cycle_start, then for each step
 // j writes w = A v_j into slot j+1 and calls gmres_arnoldi_step, and closes

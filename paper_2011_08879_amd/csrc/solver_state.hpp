@@ -31,4 +31,14 @@ struct krylov_scalars {
     int32_t half;     // BiCGSTAB: converged at the half step, x += alpha p pending
 };
 
+// How a kernel of a mid-size iteration gets its scalars (midsize.hip): state
+// *in, after the kernel's scalar step on the totals of g partials per sum at
+// `sums`, stored in *out.  out null: *in as it is.
+struct scalar_link {
+    const krylov_scalars *in;
+    krylov_scalars *out;
+    const double *sums;
+    int g;
+};
+
 }  // namespace gko

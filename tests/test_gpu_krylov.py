@@ -340,6 +340,50 @@ def test_pipecg_block_jacobi_mixed_and_statuses(g, orc, gen_mod, ctx):
     assert info["status"] == g.ERR_NOT_SPD and info["iterations"] == info_d["iters"]
 
 
+# --------------------------------------------------------------------------- mid-size iterations
+def band_spd(n, h):
+    """2h + 1 diagonals of -1 around 2h + 1.5: symmetric, row sums >= 1.5."""
+    off = np.arange(-h, h + 1)
+    c = np.arange(n)[:, None] + off
+    ok = (c >= 0) & (c < n)
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(ok.sum(1))
+    v = np.where(off == 0, 2 * h + 1.5, -1.0) * np.ones((n, 1))
+    return rp, c[ok].astype(np.int32), v[ok]
+
+
+@pytest.mark.parametrize("n,h,fmt", [
+    (1, 0, "csr"), (40, 1, "ell"), (1023, 1, "sellp"), (1025, 1, "csr"), (1024, 1, "csr_merge"),
+    (2049, 10, "csr"), (2049, 10, "ell"), (2047, 10, "sellp"), (1025, 30, "csr"), (1500, 60, "csr"),
+    (262144, 1, "ell"), (262145, 1, "csr"), (300001, 1, "sellp"), (70000, 10, "csr"), (40000, 30, "csr")])
+def test_midsize_iterations_match_oracle(g, orc, gen_mod, ctx, n, h, fmt):
+    """The few-kernel iterations of mid-size systems: rows around the 1024 of a
+    workgroup and the 256 workgroups of a grid, 1, 4, 8 and 32 lanes per CSR
+    row, rows longer than the 8 entries loaded ahead, odd check_every.  The
+    k-step iterates are the oracle's.  The matrix has condition at most 4h + 2
+    (Gershgorin) and k is small, so rounding differences stay near k kappa u
+    for CG (1e-11) and are squared by CGS's polynomial (1e-9)."""
+    A = band_spd(n, h)
+    b = orc.spmv(A, gen_mod.uniform(19, n))
+    M = g.Matrix.from_csr(*A).convert(fmt)
+    for solver, k, bound in (("cg", 13, 1e-11), ("fcg", 13, 1e-11), ("pipecg", 9, 1e-11),
+                             ("bicgstab", 7, 1e-9), ("cgs", 5, 1e-9)):
+        k = min(k, max(1, n // 3))
+        ctx.set_solver_opts(check_every=5, single_workgroup=0)
+        rc, xo, info_o = getattr(orc, solver)(A, b, tol=1e-14, maxit=k)
+        x = dev(np.zeros(n))
+        info = getattr(g, solver)(M, dev(b), x, tol=1e-14, maxit=k)
+        assert info["iterations"] == info_o["iters"], (solver, info, info_o)
+        assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo), solver
+    for bs in (1, 2, 4, 8, 16):
+        rc, inv = orc.bj_invert(A, bs)
+        rc, xo, info_o = orc.cg(A, b, tol=1e-14, maxit=min(6, n), bj_inv=inv, bs=bs)
+        ctx.set_solver_opts(check_every=5, precond=g.PRECOND_BLOCK_JACOBI, block_size=bs)
+        x = dev(np.zeros(n))
+        info = g.cg(M, dev(b), x, tol=1e-14, maxit=min(6, n))
+        assert np.linalg.norm(host(x) - xo) <= 1e-11 * np.linalg.norm(xo), bs
+
+
 # --------------------------------------------------------------------------- shared edge cases
 def test_nonzero_initial_guess_and_long_restart(g, orc, gen_mod, ctx):
     A = gen_mod.convdiff2d(30, 0.5)
