@@ -354,6 +354,10 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
 }
 
 // ---------------------------------------------------------------- conversions
+slot_layout slots_of(gko_matrix A) {
+    return A->fmt == GKO_FMT_SELLP ? slot_layout{A->sset, 0, 0} : slot_layout{nullptr, A->K, A->ld};
+}
+
 // Writes the logical matrix as CSR (n+1 offsets, nnz columns, nnz values of
 // the given value arrays) into device buffers, whatever the stored format.
 void export_csr_into(gko_matrix A, const values &v, int32_t *rp, int32_t *col, void *val) {
@@ -363,37 +367,31 @@ void export_csr_into(gko_matrix A, const values &v, int32_t *rp, int32_t *col, v
     switch (A->fmt) {
         case GKO_FMT_CSR:
         case GKO_FMT_CSR_MERGE:
-            HIPC(hipMemcpyAsync(rp, A->rp, (A->n + 1) * 4, hipMemcpyDeviceToDevice, s));
-            HIPC(hipMemcpyAsync(col, A->col, A->nnz * 4, hipMemcpyDeviceToDevice, s));
-            HIPC(hipMemcpyAsync(val, v.val, A->nnz * vb, hipMemcpyDeviceToDevice, s));
+            HIPC(copy_arrays(s, {rp, A->rp, (A->n + 1) * 4}, {col, A->col, A->nnz * 4},
+                             {val, v.val, A->nnz * (int64_t)vb}));
             break;
         case GKO_FMT_COO:
             HIPC(rows_to_ptr(s, A->n, A->nnz, A->row, rp));
-            HIPC(hipMemcpyAsync(col, A->col, A->nnz * 4, hipMemcpyDeviceToDevice, s));
-            HIPC(hipMemcpyAsync(val, v.val, A->nnz * vb, hipMemcpyDeviceToDevice, s));
+            HIPC(copy_arrays(s, {col, A->col, A->nnz * 4}, {val, v.val, A->nnz * (int64_t)vb}));
             break;
         case GKO_FMT_ELL:
-        case GKO_FMT_HYBRID: {
+        case GKO_FMT_HYBRID:
+        case GKO_FMT_SELLP: {
+            const slot_layout S = slots_of(A);
+            const bool tail = A->fmt == GKO_FMT_HYBRID && A->tnnz > 0;
             dbuf tptr;
-            if (A->fmt == GKO_FMT_HYBRID) {
+            if (tail) {
                 tptr = dbuf(c, (A->n + 1) * 4);
                 HIPC(rows_to_ptr(s, A->n, A->tnnz, A->trow, tptr.as<int32_t>()));
             }
             dbuf len(c, std::max<int64_t>(A->n, 1) * 4);
             dbuf tmp(c, scan_tmp_elems(A->n) * 4);
-            HIPC(hyb_lengths(s, A->n, A->K, A->ld, A->ecol, tptr.as<int32_t>(), len.as<int32_t>()));
+            HIPC(slot_lengths(s, A->n, S, A->ecol, tptr.as<int32_t>(), len.as<int32_t>()));
             HIPC(exclusive_scan(s, A->n, len.as<int32_t>(), rp, tmp.as<int32_t>()));
-            HIPC(hyb_to_csr(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, tptr.as<int32_t>(), A->tcol,
-                            v.tval, rp, col, val));
-            c->sync();
-            break;
-        }
-        case GKO_FMT_SELLP: {
-            dbuf len(c, std::max<int64_t>(A->n, 1) * 4);
-            dbuf tmp(c, scan_tmp_elems(A->n) * 4);
-            HIPC(sellp_lengths(s, A->n, A->sset, A->ecol, len.as<int32_t>()));
-            HIPC(exclusive_scan(s, A->n, len.as<int32_t>(), rp, tmp.as<int32_t>()));
-            HIPC(sellp_to_csr(s, v.t, A->n, A->sset, A->ecol, v.eval, rp, col, val));
+            HIPC(slots_to_csr(s, v.t, A->n, S, A->ecol, v.eval, tail, rp, col, val));
+            if (tail)
+                HIPC(tail_to_csr(s, v.t, A->tnnz, tptr.as<int32_t>(), A->trow, A->tcol, v.tval, rp,
+                                 col, val));
             c->sync();
             break;
         }
@@ -525,7 +523,8 @@ sellp_layout sellp_layout_of(gko_matrix A, const int32_t *rp) {
     return L;
 }
 
-void csr_to_format(gko_matrix A, gko_format fmt) {
+// known: the SELL-P layout where the caller has it, else null.
+void csr_to_format(gko_matrix A, gko_format fmt, const sellp_layout *known) {
     gko_context c = A->ctx;
     hipStream_t s = c->stream;
     switch (fmt) {
@@ -548,7 +547,7 @@ void csr_to_format(gko_matrix A, gko_format fmt) {
         }
         case GKO_FMT_COO: {
             dbuf row(c, A->nnz * 4);
-            HIPC(csr_rows(s, A->n, A->rp, row.as<int32_t>()));
+            HIPC(csr_rows(s, A->n, A->nnz, A->rp, row.as<int32_t>()));
             ensure_carries(A, coo_chunks(A->nnz));
             c->sync();
             A->drop(A->rp);
@@ -560,7 +559,8 @@ void csr_to_format(gko_matrix A, gko_format fmt) {
         }
         case GKO_FMT_ELL:
         case GKO_FMT_HYBRID: {
-            const int64_t maxlen = max_len_of_csr(A);
+            if (A->max_len < 0) A->max_len = A->n > 0 ? max_len_of_csr(A) : 0;
+            const int64_t maxlen = A->max_len;
             const int64_t K = fmt == GKO_FMT_ELL ? maxlen : hyb_width_of_csr(A, maxlen);
             const int64_t ld = round_up64(A->n);
             const int64_t vsz = (int64_t)A->vs();
@@ -575,11 +575,12 @@ void csr_to_format(gko_matrix A, gko_format fmt) {
                 trow = dbuf(c, tnnz * 4);
                 tcol = dbuf(c, tnnz * 4);
                 tval = dbuf(c, tnnz * vsz);
-                HIPC(csr_to_tail(s, A->type(), A->n, A->rp, A->col, A->val, K, tptr.as<int32_t>(),
+                HIPC(csr_to_tail(s, A->type(), A->n, tnnz, A->rp, A->col, A->val, tptr.as<int32_t>(),
                                  trow.as<int32_t>(), tcol.as<int32_t>(), tval.p));
             }
             dbuf ecol(c, K * ld * 4), eval(c, K * ld * vsz);
-            HIPC(csr_to_ell(s, A->type(), A->n, A->rp, A->col, A->val, K, ld, ecol.as<int32_t>(), eval.p));
+            HIPC(csr_to_slots(s, A->type(), A->n, A->rp, A->col, A->val, {nullptr, K, ld},
+                              ecol.as<int32_t>(), eval.p));
             if (tnnz > 0) ensure_carries(A, coo_chunks(tnnz));
             c->sync();
             void *ca = A->carry_a, *cb = A->carry_b;
@@ -601,13 +602,13 @@ void csr_to_format(gko_matrix A, gko_format fmt) {
             return;
         }
         case GKO_FMT_SELLP: {
-            const sellp_layout L = sellp_layout_of(A, A->rp);
+            const sellp_layout L = known ? *known : sellp_layout_of(A, A->rp);
             const int64_t ns = A->slices();
             dbuf sets(c, (ns + 1) * 8), widths(c, std::max<int64_t>(ns, 1) * 4);
             dbuf scol(c, L.sets[ns] * 4), sval(c, L.sets[ns] * A->vs());
             HIPC(hipMemcpyAsync(sets.p, L.sets.data(), (ns + 1) * 8, hipMemcpyHostToDevice, s));
             HIPC(hipMemcpyAsync(widths.p, L.widths.data(), ns * 4, hipMemcpyHostToDevice, s));
-            HIPC(csr_to_sellp(s, A->type(), A->n, A->rp, A->col, A->val, sets.as<int64_t>(),
+            HIPC(csr_to_slots(s, A->type(), A->n, A->rp, A->col, A->val, {sets.as<int64_t>(), 0, 0},
                               scol.as<int32_t>(), sval.p));
             // wide slices: (slice, first column) work items of kSellpWideChunk columns
             std::vector<int32_t> wsl, wfirst, witems;
@@ -660,8 +661,10 @@ bool ell_feasible(gko_matrix A, int64_t maxlen) {
     return ell <= 4.0 * csr;
 }
 
-// Maximum row length of the logical matrix, whatever the format.
+// Maximum row length of the logical matrix, whatever the format: found when
+// the matrix was created, and kept by the conversions.
 int64_t max_len_any(gko_matrix A) {
+    if (A->max_len >= 0) return A->max_len;
     if (A->fmt == GKO_FMT_CSR || A->fmt == GKO_FMT_CSR_MERGE) return max_len_of_csr(A);
     gko_context c = A->ctx;
     dbuf rp(c, (A->n + 1) * 4), col(c, A->nnz * 4), val(c, A->nnz * A->vs());
@@ -681,20 +684,23 @@ bool sellp_feasible(gko_matrix A, int64_t slots) {
     return sellp <= 4.0 * csr;
 }
 
-void check_sellp_feasible(gko_matrix A) {
-    int64_t slots = 0;
+// The SELL-P layout of the logical matrix, refused where it is infeasible.
+sellp_layout feasible_sellp_layout(gko_matrix A) {
+    sellp_layout L;
     if (A->fmt == GKO_FMT_CSR || A->fmt == GKO_FMT_CSR_MERGE) {
-        slots = sellp_layout_of(A, A->rp).sets.back();
+        L = sellp_layout_of(A, A->rp);
     } else {
         gko_context c = A->ctx;
         dbuf rp(c, (A->n + 1) * 4), col(c, A->nnz * 4), val(c, A->nnz * A->vs());
         export_csr_into(A, own_values(A), rp.as<int32_t>(), col.as<int32_t>(), val.p);
-        slots = sellp_layout_of(A, rp.as<int32_t>()).sets.back();
+        L = sellp_layout_of(A, rp.as<int32_t>());
     }
+    const int64_t slots = L.sets.back();
     if (!sellp_feasible(A, slots))
         fail(GKO_ERR_UNSUPPORTED, "SELL-P storage would exceed 4x the CSR storage (" +
                                       std::to_string(slots) + " slots for " +
                                       std::to_string(A->nnz) + " nonzeros)");
+    return L;
 }
 
 void convert_to(gko_matrix A, gko_format fmt) {
@@ -705,10 +711,11 @@ void convert_to(gko_matrix A, gko_format fmt) {
             fail(GKO_ERR_UNSUPPORTED, "ELL storage would exceed 4x the CSR storage (max row length " +
                                           std::to_string(maxlen) + ")");
     }
-    if (fmt == GKO_FMT_SELLP) check_sellp_feasible(A);
+    sellp_layout layout;
+    if (fmt == GKO_FMT_SELLP) layout = feasible_sellp_layout(A);
     A->drop_caches();
     to_csr(A);
-    csr_to_format(A, fmt);
+    csr_to_format(A, fmt, fmt == GKO_FMT_SELLP ? &layout : nullptr);
 }
 
 // ---------------------------------------------------------------- FP32 copies
@@ -2117,13 +2124,12 @@ gko_status gko_matrix_export_storage(gko_matrix A, int32_t *ell_col, void *ell_v
         require(has_coo || (!coo_row && !coo_col && !coo_val), GKO_ERR_INVALID_ARG,
                 "format stores no COO arrays");
         const int64_t slots = A->K * A->ld;
-        if (ell_col) HIPC(hipMemcpyAsync(ell_col, A->ecol, slots * 4, hipMemcpyDeviceToDevice, s));
-        if (ell_val) HIPC(hipMemcpyAsync(ell_val, A->eval, slots * vb, hipMemcpyDeviceToDevice, s));
+        HIPC(copy_arrays(s, {ell_col, A->ecol, slots * 4}, {ell_val, A->eval, slots * (int64_t)vb}));
         const bool hyb = A->fmt == GKO_FMT_HYBRID;
         const int64_t cn = hyb ? A->tnnz : A->nnz;
-        if (coo_row) HIPC(hipMemcpyAsync(coo_row, hyb ? A->trow : A->row, cn * 4, hipMemcpyDeviceToDevice, s));
-        if (coo_col) HIPC(hipMemcpyAsync(coo_col, hyb ? A->tcol : A->col, cn * 4, hipMemcpyDeviceToDevice, s));
-        if (coo_val) HIPC(hipMemcpyAsync(coo_val, hyb ? A->tval : A->val, cn * vb, hipMemcpyDeviceToDevice, s));
+        HIPC(copy_arrays(s, {coo_row, hyb ? A->trow : A->row, cn * 4},
+                         {coo_col, hyb ? A->tcol : A->col, cn * 4},
+                         {coo_val, hyb ? A->tval : A->val, cn * (int64_t)vb}));
         c->sync();
     });
 }
@@ -2136,12 +2142,9 @@ gko_status gko_matrix_export_sellp(gko_matrix A, int64_t *slice_sets, int32_t *s
         gko_context c = A->ctx;
         hipStream_t s = c->stream;
         const int64_t ns = A->slices();
-        if (slice_sets)
-            HIPC(hipMemcpyAsync(slice_sets, A->sset, (ns + 1) * 8, hipMemcpyDeviceToDevice, s));
-        if (slice_widths)
-            HIPC(hipMemcpyAsync(slice_widths, A->swidth, ns * 4, hipMemcpyDeviceToDevice, s));
-        if (col) HIPC(hipMemcpyAsync(col, A->ecol, A->slots * 4, hipMemcpyDeviceToDevice, s));
-        if (val) HIPC(hipMemcpyAsync(val, A->eval, A->slots * A->vs(), hipMemcpyDeviceToDevice, s));
+        HIPC(copy_arrays(s, {slice_sets, A->sset, (ns + 1) * 8}, {slice_widths, A->swidth, ns * 4}));
+        HIPC(copy_arrays(s, {col, A->ecol, A->slots * 4},
+                         {val, A->eval, A->slots * (int64_t)A->vs()}));
         c->sync();
     });
 }

@@ -5,7 +5,8 @@
 //   CSR -> ELL : slot (j, i) at j*ld + i = j-th entry of row i, else padding
 //                col = -1, val = +0.0.
 //   CSR -> HYB : ELL of width K plus a COO tail with entries K.. of each row.
-//   ELL/HYB -> CSR : per-row counts, exclusive scan, copy.
+//   CSR -> SELL-P : as ELL, each slice of 64 rows with its own width.
+//   ELL/HYB/SELL-P -> CSR : per-row counts, exclusive scan, copy.
 #include <climits>
 #include <cstdint>
 
@@ -61,17 +62,41 @@ hipError_t narrow_row_ptr(hipStream_t s, int64_t n, const int64_t *rp64, int32_t
 }
 
 // ------------------------------------------------------------------ CSR <-> COO
-// One wave per row: lanes write consecutive row indices.
-__global__ void csr_rows_kernel(int64_t n, const int32_t *__restrict__ rp, int32_t *__restrict__ row) {
-    const int64_t i = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (i >= n) return;
-    const int lane = threadIdx.x % kWave;
-    for (int32_t k = rp[i] + lane; k < rp[i + 1]; k += kWave) row[k] = (int32_t)i;
+// G lanes per row write consecutive row indices, G about half the mean length:
+// a wavefront per row leaves most lanes idle on short rows, a thread per entry
+// with a search for its row in LDS was slower on longer ones (200,000 rows of
+// 32: 189 -> 210 us for CSR -> COO -> CSR).  Rows of more than 16 G entries are
+// left to the whole workgroup: 250,000 lognormal rows took 26 us without.
+template <int G>
+__global__ __launch_bounds__(256) void csr_rows_kernel(int64_t n, const int32_t *__restrict__ rp,
+                                                       int32_t *__restrict__ row) {
+    constexpr int R = 256 / G;
+    __shared__ int any_long;
+    const int64_t r0 = (int64_t)blockIdx.x * R;
+    if (threadIdx.x == 0) any_long = 0;
+    __syncthreads();
+    const int64_t i = r0 + threadIdx.x / G;
+    if (i < n) {
+        const int32_t b = rp[i], e = rp[i + 1];
+        if (e - b > 16 * G) any_long = 1;
+        else
+            for (int32_t k = b + threadIdx.x % G; k < e; k += G) row[k] = (int32_t)i;
+    }
+    __syncthreads();
+    if (!any_long) return;
+    for (int64_t r = r0; r < r0 + R && r < n; ++r) {
+        const int32_t b = rp[r], e = rp[r + 1];
+        if (e - b > 16 * G)
+            for (int32_t k = b + threadIdx.x; k < e; k += 256) row[k] = (int32_t)r;
+    }
 }
 
-hipError_t csr_rows(hipStream_t s, int64_t n, const int32_t *rp, int32_t *row) {
-    if (n == 0) return hipSuccess;
-    csr_rows_kernel<<<grid_for(n, 4), 256, 0, s>>>(n, rp, row);
+hipError_t csr_rows(hipStream_t s, int64_t n, int64_t nnz, const int32_t *rp, int32_t *row) {
+    if (n == 0 || nnz == 0) return hipSuccess;
+    const int64_t mean = nnz / n;
+    if (mean < 12) csr_rows_kernel<4><<<grid_for(n, 64), 256, 0, s>>>(n, rp, row);
+    else if (mean < 48) csr_rows_kernel<16><<<grid_for(n, 16), 256, 0, s>>>(n, rp, row);
+    else csr_rows_kernel<kWave><<<grid_for(n, 4), 256, 0, s>>>(n, rp, row);
     return hipGetLastError();
 }
 
@@ -94,10 +119,16 @@ hipError_t rows_to_ptr(hipStream_t s, int64_t n, int64_t nnz, const int32_t *row
 }
 
 // ------------------------------------------------------------------ row lengths
+// At most kMaxLenBlocks workgroups, each with one atomic: 65,536 workgroups
+// (2^24 rows) queued on the one address for 748 us.
+constexpr unsigned kMaxLenBlocks = 512;
+
 __global__ void max_len_kernel(int64_t n, const int32_t *__restrict__ rp, int *maxlen) {
     __shared__ int lds[256 / kWave];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int v = i < n ? rp[i + 1] - rp[i] : 0;
+    int v = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        v = max(v, rp[i + 1] - rp[i]);
 #pragma unroll
     for (int b = 1; b < kWave; b <<= 1) v = max(v, __shfl_xor(v, b));
     if ((threadIdx.x % kWave) == 0) lds[threadIdx.x / kWave] = v;
@@ -110,41 +141,38 @@ __global__ void max_len_kernel(int64_t n, const int32_t *__restrict__ rp, int *m
 
 hipError_t max_row_len(hipStream_t s, int64_t n, const int32_t *rp, int *maxlen) {
     if (n == 0) return hipSuccess;
-    max_len_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, rp, maxlen);
+    const unsigned g = grid_for(n, 256);
+    max_len_kernel<<<g < kMaxLenBlocks ? g : kMaxLenBlocks, 256, 0, s>>>(n, rp, maxlen);
     return hipGetLastError();
 }
 
-// Row-length histogram.  Row lengths of structured matrices take few
-// distinct values, so counting straight into global memory serialises on a
-// handful of addresses; each block counts into LDS first (when the bins fit)
-// and adds its nonzero bins once.
+// Row-length histogram.  Row lengths take few distinct values, so counting
+// straight into global memory serialises on a handful of addresses (818 us for
+// 250,000 lognormal rows with one of 10,000 entries); each block counts into
+// LDS first and adds its nonzero bins once.  Rows too long for the LDS bins,
+// few in any matrix, count into global memory.
 constexpr int kHistLdsBins = 8192;
+constexpr unsigned kHistBlocks = 256;
 
-__global__ void hist_lds_kernel(int64_t n, const int32_t *__restrict__ rp, int *hist, int nbins) {
+__global__ void hist_kernel(int64_t n, const int32_t *__restrict__ rp, int *hist, int nbins) {
     __shared__ int lh[kHistLdsBins];
     for (int t = threadIdx.x; t < nbins; t += blockDim.x) lh[t] = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&lh[rp[i + 1] - rp[i]], 1);
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int l = rp[i + 1] - rp[i];
+        atomicAdd(l < nbins ? &lh[l] : hist + l, 1);
+    }
     __syncthreads();
     for (int t = threadIdx.x; t < nbins; t += blockDim.x)
         if (lh[t]) atomicAdd(hist + t, lh[t]);
 }
 
-__global__ void hist_kernel(int64_t n, const int32_t *__restrict__ rp, int *hist) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(hist + (rp[i + 1] - rp[i]), 1);
-}
-
 hipError_t row_len_hist(hipStream_t s, int64_t n, const int32_t *rp, int *hist, int64_t maxlen) {
     if (n == 0) return hipSuccess;
-    if (maxlen + 1 <= kHistLdsBins) {
-        const unsigned g = grid_for(n, 256) < 1024 ? grid_for(n, 256) : 1024;
-        hist_lds_kernel<<<g, 256, 0, s>>>(n, rp, hist, (int)(maxlen + 1));
-    } else {
-        hist_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, rp, hist);
-    }
+    const unsigned g = grid_for(n, 256);
+    const int bins = (int)(maxlen + 1 < kHistLdsBins ? maxlen + 1 : kHistLdsBins);
+    hist_kernel<<<g < kHistBlocks ? g : kHistBlocks, 256, 0, s>>>(n, rp, hist, bins);
     return hipGetLastError();
 }
 
@@ -260,38 +288,214 @@ hipError_t gather_probe(hipStream_t s, int64_t n, const double *x, int64_t m, co
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ CSR -> ELL / HYB
+// ------------------------------------------------------------------ CSR <-> slots
+// ELL, the ELL part of HYB and SELL-P keep the rows' entries in column-major
+// slots.  A workgroup converts a tile of 64 rows (SELL-P: one slice), whose CSR
+// entries are one contiguous range, through LDS in chunks: the CSR side is read
+// or written in its own order, the slot side by wavefronts with a lane per
+// row, so both sides are coalesced (a thread per row walking its CSR entries:
+// 500,000 rows of 16 entries CSR -> ELL 132 us, ELL -> CSR 255 us).
+constexpr int kSlotRows = kWave;
+constexpr int kSlotThreads = 256;
+constexpr int kSlotChunk = 2048;
+
+static_assert(kSlotRows == kSellpSlice, "a SELL-P slice is a tile");
+
+// Slot j of the tile's row r is at start + j stride + r, j < width.
+struct slot_tile {
+    int64_t start, stride, width;
+};
+
+__device__ inline slot_tile slot_tile_of(const slot_layout &S, int64_t tile) {
+    if (!S.sets) return {tile * kSlotRows, S.ld, S.K};
+    return {S.sets[tile], kSlotRows, (S.sets[tile + 1] - S.sets[tile]) / kSlotRows};
+}
+
+// A chunk's entries in LDS, spread so that lanes reading rows of equal length
+// do not meet in one bank.
 template <typename V>
-__global__ void csr_to_ell_kernel(int64_t n, int64_t ld, const int32_t *__restrict__ rp,
-                                  const int32_t *__restrict__ col, const V *__restrict__ val,
-                                  int64_t K, int32_t *__restrict__ ecol, V *__restrict__ eval) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ld) return;
-    const int64_t b = i < n ? rp[i] : 0;
-    const int64_t len = i < n ? rp[i + 1] - b : 0;
-    for (int64_t j = 0; j < K; ++j) {
-        if (j < len) {
-            ecol[j * ld + i] = col[b + j];
-            eval[j * ld + i] = val[b + j];
-        } else {
-            ecol[j * ld + i] = -1;
-            eval[j * ld + i] = V(0);
+struct slot_lds {
+    int32_t col[kSlotChunk + kSlotChunk / 32];
+    V val[kSlotChunk + kSlotChunk / 32];
+    __device__ static int at(int t) { return t + (t >> 5); }
+};
+
+// The slots of one row (entries b..e) that fall into the chunk of cn entries
+// at c0: [lo, hi); and the wavefront's smallest lo and largest hi.
+struct slot_span {
+    int32_t lo, hi, first, last;
+};
+
+__device__ inline slot_span span_of(int32_t b, int32_t e, int64_t width, int32_t c0, int32_t cn) {
+    slot_span p;
+    const int32_t end = e - b < width ? e : b + (int32_t)width;
+    p.lo = (b > c0 ? b : c0) - b;
+    p.hi = (end < c0 + cn ? end : c0 + cn) - b;
+    p.first = p.lo < p.hi ? p.lo : INT_MAX;
+    p.last = p.lo < p.hi ? p.hi : 0;
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) {
+        p.first = min(p.first, __shfl_xor(p.first, s));
+        p.last = max(p.last, __shfl_xor(p.last, s));
+    }
+    p.first = min(p.first, p.last);  // no row in the chunk: an empty range
+    return p;
+}
+
+template <typename V>
+__global__ __launch_bounds__(kSlotThreads) void csr_to_slots_kernel(
+    int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ val, slot_layout S, int32_t *__restrict__ scol, V *__restrict__ sval) {
+    __shared__ slot_lds<V> L;
+    const int64_t r0 = (int64_t)blockIdx.x * kSlotRows;
+    const slot_tile T = slot_tile_of(S, blockIdx.x);
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    constexpr int NW = kSlotThreads / kWave, E = kSlotChunk / kSlotThreads;
+    const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
+    const int32_t b = rp[i < n ? i : n], e = rp[i + 1 < n ? i + 1 : n];
+    const int32_t kb = rp[r0 < n ? r0 : n], ke = rp[last];
+    for (int32_t c0 = kb; c0 < ke; c0 += kSlotChunk) {
+        const int32_t cn = ke - c0 < kSlotChunk ? ke - c0 : kSlotChunk;
+        const slot_span p = span_of(b, e, T.width, c0, cn);
+        if (p.first >= p.last) continue;  // all past their rows' slots (the same in every wavefront)
+        int32_t cc[E];
+        V vv[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int t = threadIdx.x + u * kSlotThreads;
+            cc[u] = t < cn ? load_stream(col + c0 + t) : 0;
+            vv[u] = t < cn ? load_stream(val + c0 + t) : V(0);
         }
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int t = threadIdx.x + u * kSlotThreads;
+            L.col[L.at(t)] = cc[u];
+            L.val[L.at(t)] = vv[u];
+        }
+        __syncthreads();
+        for (int32_t j = p.first + wv; j < p.last; j += NW)
+            if (j >= p.lo && j < p.hi) {
+                const int64_t slot = T.start + j * T.stride + lane;
+                const int t = L.at(b + j - c0);
+                scol[slot] = L.col[t];
+                sval[slot] = L.val[t];
+            }
+        __syncthreads();
+    }
+    // padding from the rows' ends on (rows past the last one: all slots)
+    const int64_t len = e - b;
+    int32_t shortest = e - b;
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) shortest = min(shortest, __shfl_xor(shortest, s));
+    for (int64_t j = shortest + wv; j < T.width; j += NW)
+        if (j >= len) {
+            const int64_t slot = T.start + j * T.stride + lane;
+            scol[slot] = -1;
+            sval[slot] = V(0);
+        }
+}
+
+// rp: the rows' offsets (with a tail: of the whole rows; TAIL leaves the
+// places of the tail's entries alone).
+template <typename V, bool TAIL>
+__global__ __launch_bounds__(kSlotThreads) void slots_to_csr_kernel(
+    int64_t n, slot_layout S, const int32_t *__restrict__ scol, const V *__restrict__ sval,
+    const int32_t *__restrict__ rp, int32_t *__restrict__ col, V *__restrict__ val) {
+    __shared__ slot_lds<V> L;
+    const int64_t r0 = (int64_t)blockIdx.x * kSlotRows;
+    const slot_tile T = slot_tile_of(S, blockIdx.x);
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    constexpr int NW = kSlotThreads / kWave, E = kSlotChunk / kSlotThreads;
+    const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
+    const int32_t b = rp[i < n ? i : n], e = rp[i + 1 < n ? i + 1 : n];
+    const int32_t kb = rp[r0], ke = rp[last];
+    for (int32_t c0 = kb; c0 < ke; c0 += kSlotChunk) {
+        const int32_t cn = ke - c0 < kSlotChunk ? ke - c0 : kSlotChunk;
+        const slot_span p = span_of(b, e, T.width, c0, cn);
+        if (p.first >= p.last) continue;  // the tail's (the same in every wavefront)
+        if constexpr (TAIL) {
+            for (int u = 0; u < E; ++u) L.col[L.at(threadIdx.x + u * kSlotThreads)] = -1;
+            __syncthreads();
+        }
+        for (int32_t j = p.first + wv; j < p.last; j += NW)
+            if (j >= p.lo && j < p.hi) {
+                const int64_t slot = T.start + j * T.stride + lane;
+                const int t = L.at(b + j - c0);
+                L.col[t] = load_stream(scol + slot);
+                L.val[t] = load_stream(sval + slot);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int t = threadIdx.x + u * kSlotThreads;
+            if (t < cn && (!TAIL || L.col[L.at(t)] >= 0)) {
+                col[c0 + t] = L.col[L.at(t)];
+                val[c0 + t] = L.val[L.at(t)];
+            }
+        }
+        __syncthreads();
     }
 }
 
-hipError_t csr_to_ell(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
-                      const void *val, int64_t K, int64_t ld, int32_t *ecol, void *eval) {
-    if (ld == 0 || K == 0) return hipSuccess;
+// A row's entries are its slots up to the first padding slot, found by
+// bisection (reading every slot of 500,000 rows of 34: 24 us).
+__global__ void slot_len_kernel(int64_t n, slot_layout S, const int32_t *__restrict__ scol,
+                                const int32_t *__restrict__ tail_ptr, int32_t *__restrict__ len) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const slot_tile T = slot_tile_of(S, i / kSlotRows);
+    const int32_t *c = scol + T.start + i % kSlotRows;
+    int64_t lo = 0, hi = T.width;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (c[mid * T.stride] >= 0) lo = mid + 1;
+        else hi = mid;
+    }
+    len[i] = (int32_t)lo + (tail_ptr ? tail_ptr[i + 1] - tail_ptr[i] : 0);
+}
+
+hipError_t csr_to_slots(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
+                        const void *val, const slot_layout &S, int32_t *scol, void *sval) {
+    const unsigned tiles = grid_for(n, kSlotRows);
+    if (tiles == 0 || (!S.sets && S.K == 0)) return hipSuccess;
     if (t == vt::f64)
-        csr_to_ell_kernel<double><<<grid_for(ld, 256), 256, 0, s>>>(
-            n, ld, rp, col, static_cast<const double *>(val), K, ecol, static_cast<double *>(eval));
+        csr_to_slots_kernel<double><<<tiles, kSlotThreads, 0, s>>>(
+            n, rp, col, static_cast<const double *>(val), S, scol, static_cast<double *>(sval));
     else
-        csr_to_ell_kernel<float><<<grid_for(ld, 256), 256, 0, s>>>(
-            n, ld, rp, col, static_cast<const float *>(val), K, ecol, static_cast<float *>(eval));
+        csr_to_slots_kernel<float><<<tiles, kSlotThreads, 0, s>>>(
+            n, rp, col, static_cast<const float *>(val), S, scol, static_cast<float *>(sval));
     return hipGetLastError();
 }
 
+hipError_t slot_lengths(hipStream_t s, int64_t n, const slot_layout &S, const int32_t *scol,
+                        const int32_t *tail_ptr, int32_t *len) {
+    if (n == 0) return hipSuccess;
+    slot_len_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, S, scol, tail_ptr, len);
+    return hipGetLastError();
+}
+
+template <typename V>
+static hipError_t launch_slots_to_csr(hipStream_t s, int64_t n, const slot_layout &S,
+                                      const int32_t *scol, const void *sval, bool tail,
+                                      const int32_t *rp, int32_t *col, void *val) {
+    const unsigned tiles = grid_for(n, kSlotRows);
+    if (tail)
+        slots_to_csr_kernel<V, true><<<tiles, kSlotThreads, 0, s>>>(
+            n, S, scol, static_cast<const V *>(sval), rp, col, static_cast<V *>(val));
+    else
+        slots_to_csr_kernel<V, false><<<tiles, kSlotThreads, 0, s>>>(
+            n, S, scol, static_cast<const V *>(sval), rp, col, static_cast<V *>(val));
+    return hipGetLastError();
+}
+
+hipError_t slots_to_csr(hipStream_t s, vt t, int64_t n, const slot_layout &S, const int32_t *scol,
+                        const void *sval, bool tail, const int32_t *rp, int32_t *col, void *val) {
+    if (n == 0) return hipSuccess;
+    return t == vt::f64 ? launch_slots_to_csr<double>(s, n, S, scol, sval, tail, rp, col, val)
+                        : launch_slots_to_csr<float>(s, n, S, scol, sval, tail, rp, col, val);
+}
+
+// ------------------------------------------------------------------ HYB's tail
 __global__ void tail_len_kernel(int64_t n, const int32_t *__restrict__ rp, int64_t K,
                                 int32_t *__restrict__ len) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -306,93 +510,67 @@ hipError_t tail_lengths(hipStream_t s, int64_t n, const int32_t *rp, int64_t K, 
     return hipGetLastError();
 }
 
+// The tail's rows (trow, by csr_rows on tail_ptr) say where its entries are in
+// CSR: entry q of row r is the (tail_ptr[r + 1] - q)-th from the row's end.  A
+// thread per tail entry, so the few long rows that hold most of a tail are as
+// parallel as the rest (a wavefront per row: 71 us for 250,000 lognormal rows
+// with 3.5M tail entries).
 template <typename V>
-__global__ void csr_to_tail_kernel(int64_t n, const int32_t *__restrict__ rp,
+__global__ void csr_to_tail_kernel(int64_t tnnz, const int32_t *__restrict__ rp,
                                    const int32_t *__restrict__ col, const V *__restrict__ val,
-                                   int64_t K, const int32_t *__restrict__ tail_ptr,
-                                   int32_t *__restrict__ trow, int32_t *__restrict__ tcol,
+                                   const int32_t *__restrict__ tail_ptr,
+                                   const int32_t *__restrict__ trow, int32_t *__restrict__ tcol,
                                    V *__restrict__ tval) {
-    const int64_t i = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (i >= n) return;
-    const int lane = threadIdx.x % kWave;
-    const int64_t b = (int64_t)rp[i] + K, e = rp[i + 1];
-    const int64_t o = tail_ptr[i];
-    for (int64_t k = b + lane; k < e; k += kWave) {
-        trow[o + (k - b)] = (int32_t)i;
-        tcol[o + (k - b)] = col[k];
-        tval[o + (k - b)] = val[k];
-    }
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= tnnz) return;
+    const int32_t r = trow[q];
+    const int64_t k = rp[r + 1] - (tail_ptr[r + 1] - q);
+    tcol[q] = col[k];
+    tval[q] = val[k];
 }
 
-hipError_t csr_to_tail(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
-                       const void *val, int64_t K, const int32_t *tail_ptr, int32_t *trow,
+hipError_t csr_to_tail(hipStream_t s, vt t, int64_t n, int64_t tnnz, const int32_t *rp,
+                       const int32_t *col, const void *val, const int32_t *tail_ptr, int32_t *trow,
                        int32_t *tcol, void *tval) {
-    if (n == 0) return hipSuccess;
+    if (tnnz == 0) return hipSuccess;
+    const hipError_t e = csr_rows(s, n, tnnz, tail_ptr, trow);
+    if (e != hipSuccess) return e;
     if (t == vt::f64)
-        csr_to_tail_kernel<double><<<grid_for(n, 4), 256, 0, s>>>(
-            n, rp, col, static_cast<const double *>(val), K, tail_ptr, trow, tcol,
+        csr_to_tail_kernel<double><<<grid_for(tnnz, 256), 256, 0, s>>>(
+            tnnz, rp, col, static_cast<const double *>(val), tail_ptr, trow, tcol,
             static_cast<double *>(tval));
     else
-        csr_to_tail_kernel<float><<<grid_for(n, 4), 256, 0, s>>>(
-            n, rp, col, static_cast<const float *>(val), K, tail_ptr, trow, tcol,
+        csr_to_tail_kernel<float><<<grid_for(tnnz, 256), 256, 0, s>>>(
+            tnnz, rp, col, static_cast<const float *>(val), tail_ptr, trow, tcol,
             static_cast<float *>(tval));
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ ELL / HYB -> CSR
-__global__ void hyb_len_kernel(int64_t n, int64_t K, int64_t ld, const int32_t *__restrict__ ecol,
-                               const int32_t *__restrict__ tail_ptr, int32_t *__restrict__ len) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int32_t l = 0;
-    for (int64_t j = 0; j < K; ++j) l += ecol[j * ld + i] >= 0;
-    if (tail_ptr) l += tail_ptr[i + 1] - tail_ptr[i];
-    len[i] = l;
-}
-
-hipError_t hyb_lengths(hipStream_t s, int64_t n, int64_t K, int64_t ld, const int32_t *ecol,
-                       const int32_t *tail_ptr, int32_t *len) {
-    if (n == 0) return hipSuccess;
-    hyb_len_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, K, ld, ecol, tail_ptr, len);
-    return hipGetLastError();
-}
-
 template <typename V>
-__global__ void hyb_to_csr_kernel(int64_t n, int64_t K, int64_t ld, const int32_t *__restrict__ ecol,
-                                  const V *__restrict__ eval, const int32_t *__restrict__ tail_ptr,
-                                  const int32_t *__restrict__ tcol, const V *__restrict__ tval,
-                                  const int32_t *__restrict__ rp, int32_t *__restrict__ col,
-                                  V *__restrict__ val) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int64_t o = rp[i];
-    for (int64_t j = 0; j < K; ++j) {
-        const int32_t c = ecol[j * ld + i];
-        if (c < 0) break;
-        col[o] = c;
-        val[o] = eval[j * ld + i];
-        ++o;
-    }
-    if (tail_ptr)
-        for (int64_t k = tail_ptr[i]; k < tail_ptr[i + 1]; ++k) {
-            col[o] = tcol[k];
-            val[o] = tval[k];
-            ++o;
-        }
+__global__ void tail_to_csr_kernel(int64_t tnnz, const int32_t *__restrict__ tail_ptr,
+                                   const int32_t *__restrict__ trow, const int32_t *__restrict__ tcol,
+                                   const V *__restrict__ tval, const int32_t *__restrict__ rp,
+                                   int32_t *__restrict__ col, V *__restrict__ val) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= tnnz) return;
+    const int32_t r = trow[q];
+    const int64_t k = rp[r + 1] - (tail_ptr[r + 1] - q);
+    col[k] = tcol[q];
+    val[k] = tval[q];
 }
 
-hipError_t hyb_to_csr(hipStream_t s, vt t, int64_t n, int64_t K, int64_t ld, const int32_t *ecol,
-                      const void *eval, const int32_t *tail_ptr, const int32_t *tcol,
-                      const void *tval, const int32_t *rp, int32_t *col, void *val) {
-    if (n == 0) return hipSuccess;
+hipError_t tail_to_csr(hipStream_t s, vt t, int64_t tnnz, const int32_t *tail_ptr,
+                       const int32_t *trow, const int32_t *tcol, const void *tval,
+                       const int32_t *rp, int32_t *col, void *val) {
+    if (tnnz == 0) return hipSuccess;
     if (t == vt::f64)
-        hyb_to_csr_kernel<double><<<grid_for(n, 256), 256, 0, s>>>(
-            n, K, ld, ecol, static_cast<const double *>(eval), tail_ptr, tcol,
-            static_cast<const double *>(tval), rp, col, static_cast<double *>(val));
+        tail_to_csr_kernel<double><<<grid_for(tnnz, 256), 256, 0, s>>>(
+            tnnz, tail_ptr, trow, tcol, static_cast<const double *>(tval), rp, col,
+            static_cast<double *>(val));
     else
-        hyb_to_csr_kernel<float><<<grid_for(n, 256), 256, 0, s>>>(
-            n, K, ld, ecol, static_cast<const float *>(eval), tail_ptr, tcol,
-            static_cast<const float *>(tval), rp, col, static_cast<float *>(val));
+        tail_to_csr_kernel<float><<<grid_for(tnnz, 256), 256, 0, s>>>(
+            tnnz, tail_ptr, trow, tcol, static_cast<const float *>(tval), rp, col,
+            static_cast<float *>(val));
     return hipGetLastError();
 }
 
@@ -481,6 +659,69 @@ hipError_t exclusive_scan(hipStream_t s, int64_t n, const int32_t *len, int32_t 
     scan_tile_sums<<<(unsigned)tiles, kScanBlock, 0, s>>>(n, len, tmp);
     scan_sums_kernel<<<1, kScanBlock, 0, s>>>(tiles, tmp);
     scan_tiles_kernel<<<(unsigned)tiles, kScanBlock, 0, s>>>(n, len, tmp, out);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ array copies
+// Up to three device arrays copied by one launch with 16-byte non-temporal
+// loads and stores: bound by memory.  The columns and values of an ELL matrix
+// with 18M slots (216 MB, read and written) take 59 us, two of the runtime's
+// copies 87 us.  A thread takes 16 bytes; an array's last bytes past a multiple
+// of 16 go byte by byte.
+typedef uint32_t copy_quad __attribute__((ext_vector_type(4)));
+
+struct copy_args {
+    array_copy a[3];
+    int64_t units[3];  // 16-byte units of each array, the last one partial
+};
+
+__global__ __launch_bounds__(256) void copy_arrays_kernel(copy_args c) {
+    int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (u < c.units[k]) {
+            const char *src = static_cast<const char *>(c.a[k].src) + u * 16;
+            char *dst = static_cast<char *>(c.a[k].dst) + u * 16;
+            const int64_t left = c.a[k].bytes - u * 16;
+            if (left >= 16)
+                __builtin_nontemporal_store(
+                    __builtin_nontemporal_load(reinterpret_cast<const copy_quad *>(src)),
+                    reinterpret_cast<copy_quad *>(dst));
+            else
+                for (int64_t q = 0; q < left; ++q) dst[q] = src[q];
+            return;
+        }
+        u -= c.units[k];
+    }
+}
+
+// What the kernel may write: memory of the current device.  A caller's buffer
+// that is on the host or on another device is left to the runtime.
+static bool kernel_writable(const void *p) {
+    hipPointerAttribute_t at;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
+hipError_t copy_arrays(hipStream_t s, const array_copy &a, const array_copy &b, const array_copy &c) {
+    copy_args args{{a, b, c}, {}};
+    int64_t units = 0;
+    for (int k = 0; k < 3; ++k) {
+        array_copy &x = args.a[k];
+        if (!x.dst || x.bytes <= 0) x.bytes = 0;
+        else if ((((uintptr_t)x.dst | (uintptr_t)x.src) & 15) || !kernel_writable(x.dst)) {
+            const hipError_t e = hipMemcpyAsync(x.dst, x.src, x.bytes, hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return e;
+            x.bytes = 0;
+        }
+        units += args.units[k] = (x.bytes + 15) / 16;
+    }
+    if (units == 0) return hipSuccess;
+    copy_arrays_kernel<<<grid_for(units, 256), 256, 0, s>>>(args);
     return hipGetLastError();
 }
 

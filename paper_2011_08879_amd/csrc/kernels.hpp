@@ -94,7 +94,7 @@ hipError_t scale(hipStream_t s, vt t, int64_t n, double beta, void *y);
 hipError_t validate_csr(hipStream_t s, int64_t n, int64_t m, int64_t nnz, const int32_t *rp,
                         const int32_t *col, int *err);
 hipError_t narrow_row_ptr(hipStream_t s, int64_t n, const int64_t *rp64, int32_t *rp32, int *err);
-hipError_t csr_rows(hipStream_t s, int64_t n, const int32_t *rp, int32_t *row);
+hipError_t csr_rows(hipStream_t s, int64_t n, int64_t nnz, const int32_t *rp, int32_t *row);
 hipError_t rows_to_ptr(hipStream_t s, int64_t n, int64_t nnz, const int32_t *row, int32_t *rp);
 // maxlen: one device int, must be zero on entry.
 hipError_t max_row_len(hipStream_t s, int64_t n, const int32_t *rp, int *maxlen);
@@ -107,28 +107,39 @@ hipError_t gather_probe(hipStream_t s, int64_t n, const double *x, int64_t m, co
                         double *y);
 hipError_t stream_op(hipStream_t s, int op, int64_t n, const double *a, const double *b, double sc,
                      double *c);
-hipError_t csr_to_ell(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
-                      const void *val, int64_t K, int64_t ld, int32_t *ecol, void *eval);
+// Column-major slots: ELL (K slots of leading dimension ld, sets null) or
+// SELL-P (slice k at sets[k], its width from the next offset).
+struct slot_layout {
+    const int64_t *sets;
+    int64_t K, ld;
+};
+// The slot arrays from CSR (a row's entries past its slots are left out), the
+// rows' lengths back from the slots (plus their tails'), and their CSR arrays
+// given the rows' offsets (tail: the rows also have entries in a COO tail).
+hipError_t csr_to_slots(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
+                        const void *val, const slot_layout &S, int32_t *scol, void *sval);
+hipError_t slot_lengths(hipStream_t s, int64_t n, const slot_layout &S, const int32_t *scol,
+                        const int32_t *tail_ptr, int32_t *len);
+hipError_t slots_to_csr(hipStream_t s, vt t, int64_t n, const slot_layout &S, const int32_t *scol,
+                        const void *sval, bool tail, const int32_t *rp, int32_t *col, void *val);
 // tail_ptr: n+1 offsets of the tail entries of each row (exclusive scan of max(0, len-K)).
 hipError_t tail_lengths(hipStream_t s, int64_t n, const int32_t *rp, int64_t K, int32_t *len);
-hipError_t csr_to_tail(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
-                       const void *val, int64_t K, const int32_t *tail_ptr, int32_t *trow,
+hipError_t csr_to_tail(hipStream_t s, vt t, int64_t n, int64_t tnnz, const int32_t *rp,
+                       const int32_t *col, const void *val, const int32_t *tail_ptr, int32_t *trow,
                        int32_t *tcol, void *tval);
-// lengths of rows stored as ELL (+ optional COO tail given by its row offsets).
-hipError_t hyb_lengths(hipStream_t s, int64_t n, int64_t K, int64_t ld, const int32_t *ecol,
-                       const int32_t *tail_ptr, int32_t *len);
-hipError_t hyb_to_csr(hipStream_t s, vt t, int64_t n, int64_t K, int64_t ld, const int32_t *ecol,
-                      const void *eval, const int32_t *tail_ptr, const int32_t *tcol,
-                      const void *tval, const int32_t *rp, int32_t *col, void *val);
-// SELL-P conversions: widths[s] = longest row of slice s; the slot arrays
-// from CSR given sets; row lengths and CSR arrays back from the slots.
+hipError_t tail_to_csr(hipStream_t s, vt t, int64_t tnnz, const int32_t *tail_ptr,
+                       const int32_t *trow, const int32_t *tcol, const void *tval,
+                       const int32_t *rp, int32_t *col, void *val);
+// widths[s] = longest row of SELL-P slice s.
 hipError_t sellp_widths(hipStream_t s, int64_t n, const int32_t *rp, int32_t *widths);
-hipError_t csr_to_sellp(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
-                        const void *val, const int64_t *sets, int32_t *scol, void *sval);
-hipError_t sellp_lengths(hipStream_t s, int64_t n, const int64_t *sets, const int32_t *scol,
-                         int32_t *len);
-hipError_t sellp_to_csr(hipStream_t s, vt t, int64_t n, const int64_t *sets, const int32_t *scol,
-                        const void *sval, const int32_t *rp, int32_t *col, void *val);
+// Device-to-device copies, up to three by one launch (dst null or bytes 0: none).
+struct array_copy {
+    void *dst;
+    const void *src;
+    int64_t bytes;
+};
+hipError_t copy_arrays(hipStream_t s, const array_copy &a, const array_copy &b = {},
+                       const array_copy &c = {});
 // Exclusive scan of n int32 lengths into n+1 offsets; tmp: scan_tmp_elems(n) ints.
 int64_t scan_tmp_elems(int64_t n);
 hipError_t exclusive_scan(hipStream_t s, int64_t n, const int32_t *len, int32_t *out, int32_t *tmp);

@@ -213,6 +213,65 @@ def test_conversions_bit_exact(g, orc, cases, f32):
         B.close()
 
 
+def _edge_lens(name):
+    rng = np.random.default_rng(7)
+    if name.startswith("even"):             # n rows of l entries: tiles of 64 rows, chunks of 2048 entries
+        n, l = (int(v) for v in name[4:].split("x"))
+        return np.full(n, l)
+    lens = rng.integers(0, 12, 700)
+    lens[int(rng.integers(0, 700))] = int(name[4:])   # one row of that length
+    return lens
+
+
+@pytest.mark.parametrize("name", ["even1x1", "even63x3", "even64x32", "even65x32", "even64x33", "even255x5",
+                                  "even257x16", "long2047", "long2048", "long2049", "long5000", "long8191",
+                                  "long8192", "long9000"])
+@pytest.mark.parametrize("f32", [False, True])
+def test_conversions_at_tile_and_chunk_edges(g, orc, name, f32):
+    """Row tiles (64 and 256 rows) and LDS chunks (2048 entries; 8192 histogram
+    bins) at their edges: stored arrays against the oracle's, and back."""
+    lens = _edge_lens(name)
+    n, m = len(lens), 10000
+    rng = np.random.default_rng(11)
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    col = np.concatenate([np.sort(rng.choice(m, size=l, replace=False)) for l in lens]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(col)).astype(np.float32 if f32 else np.float64)
+    case = (n, m, rp, col, vals)
+    A = make(g, (n, m, rp, col, vals.astype(np.float64)), f32)
+    Ah = (rp, col, vals.astype(np.float64))
+
+    def back(fmt):
+        erp, ecol, evl = (host(t) for t in A.convert("csr").export_csr())
+        assert np.array_equal(erp, rp) and np.array_equal(ecol, col), fmt
+        assert np.array_equal(bits(evl), bits(vals)), fmt
+
+    s = A.convert("coo").export_storage()
+    assert np.array_equal(host(s["coo_row"]), np.repeat(np.arange(n), lens))
+    back("coo")
+    s = A.convert("hybrid").export_storage()
+    K, ld, ec, ev, tr, tc, tv = orc.csr_to_hyb(Ah, value_bytes=4 if f32 else 8)
+    assert (s["K"], s["ld"]) == (K, ld)
+    for key, want in (("ell_col", ec), ("coo_row", tr), ("coo_col", tc)):
+        assert np.array_equal(host(s[key]), want), key
+    assert np.array_equal(bits(host(s["ell_val"])), bits(ev.astype(vals.dtype)))
+    assert np.array_equal(bits(host(s["coo_val"])), bits(tv.astype(vals.dtype)))
+    back("hybrid")
+    if not ell_infeasible(case, 4 if f32 else 8):
+        s = A.convert("ell").export_storage()
+        K, ld, ec, ev = orc.csr_to_ell(Ah)
+        assert np.array_equal(host(s["ell_col"]), ec)
+        assert np.array_equal(bits(host(s["ell_val"])), bits(ev.astype(vals.dtype)))
+        back("ell")
+    if not sellp_infeasible(case, 4 if f32 else 8):
+        s = A.convert("sellp").export_sellp()
+        w, sets, sc, sv = orc.csr_to_sellp(Ah)
+        assert np.array_equal(host(s["widths"]), w) and np.array_equal(host(s["sets"]), sets)
+        assert np.array_equal(host(s["col"]), sc)
+        assert np.array_equal(bits(host(s["val"])), bits(sv.astype(vals.dtype)))
+        back("sellp")
+
+
 def test_auto_picks_a_format(g, cases):
     A = make(g, cases["stencil27_14"])
     A.convert("auto")
