@@ -112,7 +112,10 @@ gko_status gko_context_set_allocator(gko_context ctx, gko_alloc_fn alloc,
  *   col_idx : nnz int32 columns in [0, n_cols), strictly increasing per row.
  *   values  : nnz values of type dt.
  * The structure is validated on the device; a violation returns
- * GKO_ERR_INVALID_ARG and creates nothing. */
+ * GKO_ERR_INVALID_ARG and creates nothing.  Of a matrix with at least a
+ * million entries whose rows repeat a few lists of column offsets (a stencil
+ * on a grid) the handle also keeps these lists, a byte per row and 4 KB, for
+ * products that need not read the columns; memory permitting. */
 gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols, int64_t nnz,
                                  gko_dtype dt, const void *row_ptr, gko_itype row_ptr_type,
                                  const int32_t *col_idx, const void *values, gko_matrix *out);

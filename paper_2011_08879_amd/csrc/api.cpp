@@ -185,6 +185,10 @@ struct gko_matrix_s {
     int row_lanes = 1;              // CSR row-per-thread kernel: lanes per row
     bool merge_rows = false;        // CSR_MERGE: tiles sum their rows in parallel
     int64_t max_len = -1;           // longest row (a property of the matrix), -1 until needed
+    // row patterns (of the matrix, whatever its format), null where it has none
+    uint8_t *pat_id = nullptr;
+    int32_t *pat_tab = nullptr;
+    int pat_stride = 0, pat_ints = 0;
     int64_t n_long = 0;             // CSR rows handled by a workgroup each
     int32_t *long_rows = nullptr;
     void *carry_a = nullptr, *carry_b = nullptr;  // merge / COO carries
@@ -201,6 +205,7 @@ struct gko_matrix_s {
     int64_t slices() const { return (n + kSellpSlice - 1) / kSellpSlice; }
     // elements of ecol / eval
     int64_t ell_elems() const { return fmt == GKO_FMT_SELLP ? slots : K * ld; }
+    row_patterns patterns() const { return {pat_id, pat_tab, pat_stride, pat_ints}; }
     sellp_wide wide() const {
         sellp_wide w;
         w.n_wide = n_wide;
@@ -236,6 +241,11 @@ struct gko_matrix_s {
         drop(wide_partial);
         tiles = K = ld = tnnz = carry_elems = n_long = slots = n_wide = n_wide_items = 0;
         drop_caches();
+    }
+    void drop_all() {
+        drop_storage();
+        drop(pat_id);
+        drop(pat_tab);
     }
     int64_t stored_bytes() const {
         const int64_t s = (int64_t)vs();
@@ -326,7 +336,7 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
     switch (A->fmt) {
         case GKO_FMT_CSR:
             HIPC(spmv_csr(s, v.t, A->n, A->rp, A->col, v.val, x, alpha, beta, y, A->subwarp,
-                          A->row_lanes, A->n_long, A->long_rows));
+                          A->row_lanes, A->n_long, A->long_rows, A->patterns()));
             break;
         case GKO_FMT_CSR_MERGE:
             HIPC(spmv_merge(s, v.t, A->n, A->nnz, A->rp, A->col, v.val, A->part, x, alpha, beta, y,
@@ -337,16 +347,19 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
                           A->carry_a, A->carry_b));
             break;
         case GKO_FMT_ELL:
-            HIPC(spmv_ell(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, x, alpha, beta, y));
+            HIPC(spmv_ell(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, A->patterns(), x, alpha,
+                          beta, y));
             break;
         case GKO_FMT_HYBRID:
-            HIPC(spmv_ell(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, x, alpha, beta, y));
+            HIPC(spmv_ell(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, A->patterns(), x, alpha,
+                          beta, y));
             if (A->tnnz > 0)
                 HIPC(spmv_coo(s, v.t, A->n, A->tnnz, A->trow, A->tcol, v.tval, x, alpha, 1.0, y,
                               true, A->carry_a, A->carry_b));
             break;
         case GKO_FMT_SELLP:
-            HIPC(spmv_sellp(s, v.t, A->n, A->sset, A->ecol, v.eval, x, alpha, beta, y, A->wide()));
+            HIPC(spmv_sellp(s, v.t, A->n, A->sset, A->ecol, v.eval, A->patterns(), x, alpha, beta, y,
+                            A->wide()));
             break;
         default:
             fail(GKO_ERR_INVALID_ARG, "matrix has no storage format");
@@ -434,6 +447,60 @@ void analyse_csr(gko_matrix A) {
     A->subwarp = csr_kernel_width(A->n, A->nnz, A->max_len);
     A->row_lanes = csr_row_lanes(A->n, A->nnz);
     refresh_long_rows(A);
+}
+
+// What a matrix can do without: left out where there is no memory for it.
+template <typename F>
+void if_memory_allows(F f) {
+    try {
+        f();
+    } catch (const api_error &e) {
+        if (e.status != GKO_ERR_ALLOC) throw;
+        (void)hipGetLastError();
+    }
+}
+
+// The row patterns of a CSR matrix, found when it is created, from
+// kPatternNnz entries on: smaller products stay in the caches and gained
+// nothing (7-point stencil with 0.76M entries 5.3 us with and without, with
+// 1.8M in FP64 5.2 -> 5.0, 64^3 rows of 27 19.5 -> 14.5).  The search costs two
+// readings of the columns: 27-point stencil 128^3, creation 1.40 -> 1.51 ms.
+constexpr int64_t kPatternNnz = 1000000;
+
+void find_patterns(gko_matrix A) {
+    const int stride = (int)((A->max_len + 3) / 4 * 4);
+    if (A->n < 1 || A->nnz < kPatternNnz || A->max_len > kPatternInts / 2) return;
+    gko_context c = A->ctx;
+    hipStream_t s = c->stream;
+    dbuf found(c, sizeof(pattern_keys));
+    HIPC(pattern_collect(s, A->n, A->rp, A->col, found.as<pattern_keys>()));
+    pattern_keys h;
+    HIPC(hipMemcpyAsync(&h, found.p, sizeof(h), hipMemcpyDeviceToHost, s));
+    c->sync();
+    if (h.too_many) return;
+    std::vector<std::pair<unsigned long long, unsigned>> lists;
+    for (int t = 0; t < kPatternKeys; ++t)
+        if (h.key[t] != 0) lists.emplace_back(h.key[t], h.first[t]);
+    const int count = (int)lists.size(), ints = (count + 1) * stride;
+    if (count > kPatternMost || ints > kPatternInts) return;
+    std::sort(lists.begin(), lists.end());
+    std::vector<unsigned long long> key(count);
+    std::vector<unsigned> first(count);
+    for (int p = 0; p < count; ++p) {
+        key[p] = lists[p].first;
+        first[p] = lists[p].second;
+    }
+    dbuf dkey(c, count * 8), dfirst(c, count * 4), wrong(c, 4), tab(c, ints * 4), id(c, pattern_ids(A->n));
+    HIPC(hipMemcpyAsync(dkey.p, key.data(), count * 8, hipMemcpyHostToDevice, s));
+    HIPC(hipMemcpyAsync(dfirst.p, first.data(), count * 4, hipMemcpyHostToDevice, s));
+    HIPC(hipMemsetAsync(wrong.p, 0, 4, s));
+    HIPC(pattern_assign(s, A->n, A->rp, A->col, count, stride, dkey.as<unsigned long long>(),
+                        dfirst.as<unsigned>(), tab.as<int32_t>(), id.as<uint8_t>(), wrong.as<int>()));
+    if (read_int(c, wrong.as<int>()) != 0) return;
+    A->pat_id = static_cast<uint8_t *>(id.release());
+    A->pat_tab = static_cast<int32_t *>(tab.release());
+    A->pat_stride = stride;
+    A->pat_ints = ints;
 }
 
 void to_csr(gko_matrix A) {
@@ -816,6 +883,7 @@ bool fused_view(gko_matrix A, const values &v, fused_matrix &f) {
     f = fused_matrix{};
     f.t = v.t;
     f.n = A->n;
+    f.pat = A->patterns();
     if (A->fmt == GKO_FMT_CSR && A->n_long == 0) {
         f.format = fused_matrix::csr;
         f.rp = A->rp;
@@ -2009,8 +2077,9 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
         A->val = val.release();
         try {
             analyse_csr(A);
+            if_memory_allows([&] { find_patterns(A); });
         } catch (...) {
-            A->drop_storage();
+            A->drop_all();
             delete A;
             throw;
         }
@@ -2021,7 +2090,7 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
 gko_status gko_matrix_destroy(gko_matrix A) {
     return guarded([&] {
         if (!A) return;
-        A->drop_storage();
+        A->drop_all();
         delete A;
     });
 }
@@ -2067,10 +2136,16 @@ gko_status gko_matrix_clone(gko_matrix A, gko_matrix *out) {
             B->tval = copy(A->tval, A->tnnz * vb);
             B->n_long = A->n_long;
             B->long_rows = (int32_t *)copy(A->long_rows, A->n_long * 4);
+            if_memory_allows([&] {
+                B->pat_tab = (int32_t *)copy(A->pat_tab, A->pat_ints * 4);
+                B->pat_id = (uint8_t *)copy(A->pat_id, pattern_ids(A->n));
+                B->pat_stride = A->pat_stride;
+                B->pat_ints = A->pat_ints;
+            });
             if (A->carry_a) ensure_carries(B, A->carry_elems);
             c->sync();
         } catch (...) {
-            B->drop_storage();
+            B->drop_all();
             delete B;
             throw;
         }

@@ -234,42 +234,49 @@ __global__ __launch_bounds__(kB) void fused_csr_kernel(int64_t n, const int32_t 
 // CSR with G lanes per row and the entries staged through LDS (short regular
 // rows, as in the plain SpMV); the workgroup strides over tiles of kB / G
 // rows, and the first lane of each row stores it and adds its terms.
-template <typename V, typename P, int G>
+template <typename V, typename P, int G, int M>
 __global__ __launch_bounds__(kRowThreadBlock) void fused_csr_rowthread_kernel(
     int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ val, const V *__restrict__ in, V *__restrict__ out, P pol, red_args ra) {
+    const V *__restrict__ val, row_patterns pat, const V *__restrict__ in, V *__restrict__ out, P pol,
+    red_args ra) {
     static_assert(kRowThreadBlock == kB, "one reduction block shape");
     constexpr int64_t RT = kB / G;
-    __shared__ rowthread_lds<V> L;
+    __shared__ rowthread_lds<V, G, M> L;
     if (pol.skip()) return;
     double acc[P::NV] = {};
     // up to kXcdRowsMax rows, each round of the grid stride gives each XCD
     // one contiguous range of rows
     for (int64_t r0 = row_block_order(n) * RT; r0 < n; r0 += (int64_t)gridDim.x * RT) {
-        const V s = csr_rowthread_sum<V, G>(n, r0, rp, col, val, in, L);
+        const V s = csr_rowthread_sum<V, G, M>(n, r0, rp, col, val, in, pat, L);
         const int64_t i = r0 + threadIdx.x / G;
         if (i < n && threadIdx.x % G == 0) {
             out[i] = s;
             pol.add(acc, i, in[i], s);
         }
+        if constexpr (M > 0) __syncthreads();  // L is free again
     }
     grid_sum_apply<kB, P::NV>(acc, ra, pol.op);
 }
 
 // ELL, two adjacent rows per thread (as in the plain SpMV).
-template <typename V, typename P>
+template <typename V, typename P, bool PAT>
 __global__ __launch_bounds__(kB) void fused_ell_kernel(int64_t n, int64_t K, int64_t ld,
                                                        const int32_t *__restrict__ ecol,
-                                                       const V *__restrict__ eval,
+                                                       const V *__restrict__ eval, row_patterns pat,
                                                        const V *__restrict__ in, V *__restrict__ out,
                                                        P pol, red_args ra) {
+    __shared__ pattern_lds L;
     if (pol.skip()) return;
+    if constexpr (PAT) {
+        pattern_stage<kB>(pat, L);
+        __syncthreads();
+    }
     double acc[P::NV] = {};
     // workgroup order as in the plain SpMV (row_block_order)
     for (int64_t i = 2 * (row_block_order(n) * kB + threadIdx.x); i < n;
          i += 2 * (int64_t)gridDim.x * kB) {
         V s0, s1;
-        ell_pair_rows(K, ld, i, ecol, eval, in, s0, s1);
+        ell_pair_rows<PAT>(K, ld, i, ecol, eval, in, pat, L, s0, s1);
         out[i] = s0;
         pol.add(acc, i, in[i], s0);
         if (i + 1 < n) {
@@ -285,24 +292,30 @@ __global__ __launch_bounds__(kB) void fused_ell_kernel(int64_t n, int64_t K, int
 // STRIDE: the grid is smaller than the row count.  Without the grid-stride
 // loop the FP64 kernel needs 40 VGPRs instead of 92 (8 waves per SIMD
 // instead of 5).
-template <typename V, typename P, bool STRIDE>
+template <typename V, typename P, bool STRIDE, bool PAT>
 __global__ __launch_bounds__(kB) void fused_sellp_kernel(int64_t n, const int64_t *__restrict__ sets,
                                                          const int32_t *__restrict__ scol,
                                                          const V *__restrict__ sval,
+                                                         row_patterns pat,
                                                          const V *__restrict__ in,
                                                          V *__restrict__ out, P pol, red_args ra) {
     static_assert(kB % kSellpSlice == 0, "whole slices per workgroup");
+    __shared__ pattern_lds L;
     if (pol.skip()) return;
+    if constexpr (PAT) {
+        pattern_stage<kB>(pat, L);
+        __syncthreads();
+    }
     double acc[P::NV] = {};
     int64_t i = row_block_order(n) * kB + threadIdx.x;
     if constexpr (STRIDE) {
         for (; i < n; i += (int64_t)gridDim.x * kB) {
-            const V s0 = sellp_row(i, sets, scol, sval, in);
+            const V s0 = sellp_row<PAT>(i, sets, scol, sval, in, pat, L);
             out[i] = s0;
             pol.add(acc, i, in[i], s0);
         }
     } else if (i < n) {
-        const V s0 = sellp_row(i, sets, scol, sval, in);
+        const V s0 = sellp_row<PAT>(i, sets, scol, sval, in, pat, L);
         out[i] = s0;
         pol.add(acc, i, in[i], s0);
     }
@@ -425,19 +438,26 @@ static hipError_t launch_fused(hipStream_t s, const fused_matrix &A, const void 
     if (A.format == fused_matrix::ell) {
         const int g = fused_blocks((A.n + 1) / 2);
         const red_args ra = red_for(g, partials, ticket);
-        fused_ell_kernel<V, P><<<g, kB, 0, s>>>(A.n, A.K, A.ld, A.ecol,
-                                                static_cast<const V *>(A.eval), in, out, pol, ra);
+        (void)with_patterns(A.pat, [&](auto p) {
+            fused_ell_kernel<V, P, decltype(p)::value><<<g, kB, 0, s>>>(
+                A.n, A.K, A.ld, A.ecol, static_cast<const V *>(A.eval), A.pat, in, out, pol, ra);
+            return hipSuccess;
+        });
         return red_finish<P::NV>(s, g, ra, pol.op);
     }
     if (A.format == fused_matrix::sellp) {
         const int g = fused_blocks(A.n);
         const red_args ra = red_for(g, partials, ticket);
-        if ((int64_t)g * kB >= A.n)
-            fused_sellp_kernel<V, P, false><<<g, kB, 0, s>>>(
-                A.n, A.sets, A.scol, static_cast<const V *>(A.sval), in, out, pol, ra);
-        else
-            fused_sellp_kernel<V, P, true><<<g, kB, 0, s>>>(
-                A.n, A.sets, A.scol, static_cast<const V *>(A.sval), in, out, pol, ra);
+        (void)with_patterns(A.pat, [&](auto p) {
+            constexpr bool PAT = decltype(p)::value;
+            if ((int64_t)g * kB >= A.n)
+                fused_sellp_kernel<V, P, false, PAT><<<g, kB, 0, s>>>(
+                    A.n, A.sets, A.scol, static_cast<const V *>(A.sval), A.pat, in, out, pol, ra);
+            else
+                fused_sellp_kernel<V, P, true, PAT><<<g, kB, 0, s>>>(
+                    A.n, A.sets, A.scol, static_cast<const V *>(A.sval), A.pat, in, out, pol, ra);
+            return hipSuccess;
+        });
         return red_finish<P::NV>(s, g, ra, pol.op);
     }
     if (A.w == kCsrRowThread) {
@@ -445,15 +465,17 @@ static hipError_t launch_fused(hipStream_t s, const fused_matrix &A, const void 
         // one block per tile of kB / lanes rows, at most kFusedMaxBlocks
         const int g = fused_blocks(A.n * A.lanes);
         const red_args ra = red_for(g, partials, ticket);
-        if (A.lanes == 8)
-            fused_csr_rowthread_kernel<V, P, 8><<<g, kB, 0, s>>>(
-                A.n, A.rp, A.col, static_cast<const V *>(A.val), in, out, pol, ra);
-        else if (A.lanes == 4)
-            fused_csr_rowthread_kernel<V, P, 4><<<g, kB, 0, s>>>(
-                A.n, A.rp, A.col, static_cast<const V *>(A.val), in, out, pol, ra);
-        else
-            fused_csr_rowthread_kernel<V, P, 1><<<g, kB, 0, s>>>(
-                A.n, A.rp, A.col, static_cast<const V *>(A.val), in, out, pol, ra);
+        const auto launch = [&](auto lanes) {
+            constexpr int G = decltype(lanes)::value;
+            (void)with_csr_mode<G>(A.pat, [&](auto m) {
+                fused_csr_rowthread_kernel<V, P, G, decltype(m)::value><<<g, kB, 0, s>>>(
+                    A.n, A.rp, A.col, static_cast<const V *>(A.val), A.pat, in, out, pol, ra);
+                return hipSuccess;
+            });
+        };
+        if (A.lanes == 8) launch(std::integral_constant<int, 8>{});
+        else if (A.lanes == 4) launch(std::integral_constant<int, 4>{});
+        else launch(std::integral_constant<int, 1>{});
         return red_finish<P::NV>(s, g, ra, pol.op);
     }
     switch (A.w) {

@@ -4,6 +4,7 @@
 
 #include "device.hpp"
 #include "kernels.hpp"
+#include "patterns.hpp"
 
 namespace gko {
 
@@ -17,25 +18,40 @@ template <> struct ell_pair<float> { typedef float type __attribute__((ext_vecto
 typedef int32_t ell_cpair __attribute__((ext_vector_type(2)));
 
 // s0, s1 = rows i and i+1 of A x (i even, i < ld); each row stops at its
-// first padding slot, the pair when both have reached theirs.
-template <typename V>
+// first padding slot, the pair when both have reached theirs.  PAT: the
+// columns come from the matrix's row patterns, whose table is in L.
+typedef uint8_t pattern_pair __attribute__((ext_vector_type(2)));
+template <bool PAT, typename V>
 __device__ inline void ell_pair_rows(int64_t K, int64_t ld, int64_t i,
                                      const int32_t *__restrict__ ecol, const V *__restrict__ eval,
-                                     const V *__restrict__ x, V &s0, V &s1) {
+                                     const V *__restrict__ x, const row_patterns &pat,
+                                     const pattern_lds &L, V &s0, V &s1) {
     using V2 = typename ell_pair<V>::type;
     const ell_cpair *c = reinterpret_cast<const ell_cpair *>(ecol + i);
     const V2 *v = reinterpret_cast<const V2 *>(eval + i);
     const int64_t ld2 = ld / 2;
     s0 = V(0);
     s1 = V(0);
+    int tab0 = 0, tab1 = 0;
+    if constexpr (PAT) {
+        const pattern_pair p = *reinterpret_cast<const pattern_pair *>(pat.id + i);
+        tab0 = p.x * pat.stride;
+        tab1 = p.y * pat.stride;
+    }
     for (int64_t j = 0; j < K; j += 4) {
         ell_cpair cc[4];
         V2 vv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const bool ok = j + u < K;
-            cc[u] = ok ? load_stream(c + (j + u) * ld2) : ell_cpair{-1, -1};
+            if constexpr (!PAT) cc[u] = ok ? load_stream(c + (j + u) * ld2) : ell_cpair{-1, -1};
             vv[u] = ok ? load_stream(v + (j + u) * ld2) : V2{V(0), V(0)};
+        }
+        if constexpr (PAT) {
+            const pattern_quad c0 = pattern_cols(L, tab0, j, (int32_t)i);
+            const pattern_quad c1 = pattern_cols(L, tab1, j, (int32_t)i + 1);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) cc[u] = j + u < K ? ell_cpair{c0[u], c1[u]} : ell_cpair{-1, -1};
         }
         // Padding slots gather x[0] (the matrix has an entry, so x has one)
         // and keep the sum: no branch per gather, so all eight are in flight
@@ -82,11 +98,14 @@ __device__ inline sellp_slice_of sellp_slice(int64_t i, const int64_t *__restric
 }
 
 // Sum over the slots j0 <= j < j1 of row r of the slice starting at base,
-// eight loads in flight; a row stops at its first padding slot.
-template <typename V>
+// eight loads in flight; a row stops at its first padding slot.  PAT: the
+// row is row i of the matrix, its columns come from the pattern offsets at
+// L's entry tab.
+template <bool PAT, typename V>
 __device__ inline V sellp_slots_sum(int64_t base, int64_t r, int64_t j0, int64_t j1,
                                     const int32_t *__restrict__ scol,
-                                    const V *__restrict__ sval, const V *__restrict__ x) {
+                                    const V *__restrict__ sval, const V *__restrict__ x,
+                                    const pattern_lds &L, int tab, int32_t i) {
     const int32_t *c = scol + base + r;
     const V *v = sval + base + r;
     V s = V(0);
@@ -96,8 +115,16 @@ __device__ inline V sellp_slots_sum(int64_t base, int64_t r, int64_t j0, int64_t
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const bool ok = j + u < j1;
-            cc[u] = ok ? load_stream(c + (j + u) * kSellpSlice) : -1;
+            if constexpr (!PAT) cc[u] = ok ? load_stream(c + (j + u) * kSellpSlice) : -1;
             vv[u] = ok ? load_stream(v + (j + u) * kSellpSlice) : V(0);
+        }
+        if constexpr (PAT) {
+#pragma unroll
+            for (int u = 0; u < 8; u += 4) {
+                const pattern_quad q = j + u < j1 ? pattern_cols(L, tab, j + u, i) : pattern_quad(-1);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) cc[u + w] = j + u + w < j1 ? q[w] : -1;
+            }
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -108,12 +135,14 @@ __device__ inline V sellp_slots_sum(int64_t base, int64_t r, int64_t j0, int64_t
 }
 
 // Row i of A x over its whole slice.
-template <typename V>
+template <bool PAT, typename V>
 __device__ inline V sellp_row(int64_t i, const int64_t *__restrict__ sets,
                               const int32_t *__restrict__ scol, const V *__restrict__ sval,
-                              const V *__restrict__ x) {
+                              const V *__restrict__ x, const row_patterns &pat,
+                              const pattern_lds &L) {
     const sellp_slice_of sl = sellp_slice(i, sets);
-    return sellp_slots_sum(sl.base, sl.r, 0, sl.w, scol, sval, x);
+    const int tab = PAT ? pat.id[i] * pat.stride : 0;
+    return sellp_slots_sum<PAT>(sl.base, sl.r, 0, sl.w, scol, sval, x, L, tab, (int32_t)i);
 }
 
 }  // namespace gko

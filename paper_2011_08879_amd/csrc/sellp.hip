@@ -22,19 +22,26 @@ constexpr int kSellpBlock = 256;
 
 inline unsigned blocks_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
-template <typename V>
+template <typename V, bool PAT>
 __global__ __launch_bounds__(kSellpBlock) void spmv_sellp_kernel(int64_t n,
                                                                  const int64_t *__restrict__ sets,
                                                                  const int32_t *__restrict__ scol,
                                                                  const V *__restrict__ sval,
+                                                                 row_patterns pat,
                                                                  const V *__restrict__ x, V alpha,
                                                                  V beta, V *__restrict__ y) {
+    __shared__ pattern_lds L;
+    if constexpr (PAT) {
+        pattern_stage<kSellpBlock>(pat, L);
+        __syncthreads();
+    }
     // up to kXcdRowsMax rows each XCD takes one contiguous range of slices
     const int64_t i = row_block_order(n) * kSellpBlock + threadIdx.x;
     if (i >= n) return;
     const sellp_slice_of sl = sellp_slice(i, sets);
     if (sl.w > kSellpWide) return;  // the whole wavefront: the wide-slice kernels
-    const V s0 = sellp_slots_sum(sl.base, sl.r, 0, sl.w, scol, sval, x);
+    const int tab = PAT ? pat.id[i] * pat.stride : 0;
+    const V s0 = sellp_slots_sum<PAT>(sl.base, sl.r, 0, sl.w, scol, sval, x, L, tab, (int32_t)i);
     y[i] = (beta == V(0)) ? alpha * s0 : alpha * s0 + beta * y[i];
 }
 
@@ -54,7 +61,8 @@ __global__ __launch_bounds__(kSellpBlock) void sellp_wide_kernel(int64_t n_items
     const int64_t sl = items[2 * q], j0 = items[2 * q + 1];
     const int64_t base = sets[sl], w = (sets[sl + 1] - base) / kSellpSlice;
     const int64_t j1 = j0 + kSellpWideChunk < w ? j0 + kSellpWideChunk : w;
-    partial[q * kSellpSlice + r] = sellp_slots_sum(base, r, j0, j1, scol, sval, x);
+    __shared__ pattern_lds L;  // not used
+    partial[q * kSellpSlice + r] = sellp_slots_sum<false>(base, r, j0, j1, scol, sval, x, L, 0, 0);
 }
 
 // Wide slice q (a wavefront): row r's partials in item order, then y.
@@ -74,13 +82,16 @@ __global__ __launch_bounds__(kSellpBlock) void sellp_wide_sum_kernel(
 
 template <typename V>
 hipError_t launch_sellp(hipStream_t s, int64_t n, const int64_t *sets, const int32_t *scol,
-                        const void *sval, const void *x, double alpha, double beta, void *y,
-                        const sellp_wide &wide) {
+                        const void *sval, const row_patterns &pat, const void *x, double alpha,
+                        double beta, void *y, const sellp_wide &wide) {
     const V *SV = static_cast<const V *>(sval), *X = static_cast<const V *>(x);
     V *Y = static_cast<V *>(y);
-    spmv_sellp_kernel<V><<<blocks_for(n, kSellpBlock), kSellpBlock, 0, s>>>(
-        n, sets, scol, SV, X, (V)alpha, (V)beta, Y);
-    if (wide.n_wide == 0) return hipGetLastError();
+    const hipError_t e = with_patterns(pat, [&](auto p) {
+        spmv_sellp_kernel<V, decltype(p)::value><<<blocks_for(n, kSellpBlock), kSellpBlock, 0, s>>>(
+            n, sets, scol, SV, pat, X, (V)alpha, (V)beta, Y);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess || wide.n_wide == 0) return e;
     constexpr int WPB = kSellpBlock / kWave;
     V *P = static_cast<V *>(wide.partial);
     sellp_wide_kernel<V><<<blocks_for(wide.n_items, WPB), kSellpBlock, 0, s>>>(
@@ -106,11 +117,11 @@ __global__ __launch_bounds__(kSellpBlock) void sellp_widths_kernel(int64_t n, in
 }  // namespace
 
 hipError_t spmv_sellp(hipStream_t s, vt t, int64_t n, const int64_t *sets, const int32_t *scol,
-                      const void *sval, const void *x, double alpha, double beta, void *y,
-                      const sellp_wide &wide) {
+                      const void *sval, const row_patterns &pat, const void *x, double alpha,
+                      double beta, void *y, const sellp_wide &wide) {
     if (n == 0) return hipSuccess;
-    return t == vt::f64 ? launch_sellp<double>(s, n, sets, scol, sval, x, alpha, beta, y, wide)
-                        : launch_sellp<float>(s, n, sets, scol, sval, x, alpha, beta, y, wide);
+    return t == vt::f64 ? launch_sellp<double>(s, n, sets, scol, sval, pat, x, alpha, beta, y, wide)
+                        : launch_sellp<float>(s, n, sets, scol, sval, pat, x, alpha, beta, y, wide);
 }
 
 hipError_t sellp_widths(hipStream_t s, int64_t n, const int32_t *rp, int32_t *widths) {

@@ -53,6 +53,7 @@ struct fused_matrix {
     const int64_t *sets = nullptr;                // SELL-P
     const int32_t *scol = nullptr;
     const void *sval = nullptr;
+    row_patterns pat;
 };
 // The fused products take partials of kFusedMaxSums * kFusedMaxBlocks doubles.
 // CG: q = A p with p.q, then alpha (or NOT_SPD).

@@ -87,40 +87,44 @@ __global__ __launch_bounds__(BLOCK) void spmv_csr_kernel(int64_t n, const int32_
 
 // Row-per-thread CSR (csr_rowthread_sum with G lanes per row), chosen for
 // short regular rows.
-template <typename V, int G>
+template <typename V, int G, int M>
 __global__ __launch_bounds__(kRowThreadBlock) void spmv_csr_rowthread_kernel(
     int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ val, const V *__restrict__ x, V alpha, V beta, V *__restrict__ y) {
-    __shared__ rowthread_lds<V> L;
+    const V *__restrict__ val, row_patterns pat, const V *__restrict__ x, V alpha, V beta,
+    V *__restrict__ y) {
+    __shared__ rowthread_lds<V, G, M> L;
     // up to kXcdRowsMax rows each XCD takes one contiguous range of rows, so
     // the x lines that neighbouring rows share are fetched into one L2
     const int64_t r0 = row_block_order(n) * (kRowThreadBlock / G);
-    const V s = csr_rowthread_sum<V, G>(n, r0, rp, col, val, x, L);
+    const V s = csr_rowthread_sum<V, G, M>(n, r0, rp, col, val, x, pat, L);
     const int64_t i = r0 + threadIdx.x / G;
     if (i < n && threadIdx.x % G == 0) y[i] = (beta == V(0)) ? alpha * s : alpha * s + beta * y[i];
 }
 
 template <typename V, int G>
 static hipError_t launch_csr_rowthread_g(hipStream_t s, int64_t n, const int32_t *rp,
-                                         const int32_t *col, const void *val, const void *x,
-                                         double alpha, double beta, void *y) {
+                                         const int32_t *col, const void *val,
+                                         const row_patterns &pat, const void *x, double alpha,
+                                         double beta, void *y) {
     constexpr int64_t rows = kRowThreadBlock / G;
-    spmv_csr_rowthread_kernel<V, G><<<dim3((unsigned)((n + rows - 1) / rows)),
-                                      dim3(kRowThreadBlock), 0, s>>>(
-        n, rp, col, static_cast<const V *>(val), static_cast<const V *>(x), (V)alpha, (V)beta,
-        static_cast<V *>(y));
-    return hipGetLastError();
+    return with_csr_mode<G>(pat, [&](auto m) {
+        spmv_csr_rowthread_kernel<V, G, decltype(m)::value>
+            <<<dim3((unsigned)((n + rows - 1) / rows)), dim3(kRowThreadBlock), 0, s>>>(
+                n, rp, col, static_cast<const V *>(val), pat, static_cast<const V *>(x), (V)alpha,
+                (V)beta, static_cast<V *>(y));
+        return hipGetLastError();
+    });
 }
 
 template <typename V>
 static hipError_t launch_csr_rowthread(hipStream_t s, int64_t n, const int32_t *rp,
-                                       const int32_t *col, const void *val, const void *x,
-                                       double alpha, double beta, void *y, int lanes) {
+                                       const int32_t *col, const void *val, const row_patterns &pat,
+                                       const void *x, double alpha, double beta, void *y, int lanes) {
     switch (lanes) {
-        case 1: return launch_csr_rowthread_g<V, 1>(s, n, rp, col, val, x, alpha, beta, y);
-        case 2: return launch_csr_rowthread_g<V, 2>(s, n, rp, col, val, x, alpha, beta, y);
-        case 4: return launch_csr_rowthread_g<V, 4>(s, n, rp, col, val, x, alpha, beta, y);
-        case 8: return launch_csr_rowthread_g<V, 8>(s, n, rp, col, val, x, alpha, beta, y);
+        case 1: return launch_csr_rowthread_g<V, 1>(s, n, rp, col, val, pat, x, alpha, beta, y);
+        case 2: return launch_csr_rowthread_g<V, 2>(s, n, rp, col, val, pat, x, alpha, beta, y);
+        case 4: return launch_csr_rowthread_g<V, 4>(s, n, rp, col, val, pat, x, alpha, beta, y);
+        case 8: return launch_csr_rowthread_g<V, 8>(s, n, rp, col, val, pat, x, alpha, beta, y);
         default: return hipErrorInvalidValue;
     }
 }
@@ -241,12 +245,12 @@ static hipError_t launch_csr(hipStream_t s, int64_t n, const int32_t *rp, const 
 
 hipError_t spmv_csr(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
                     const void *val, const void *x, double alpha, double beta, void *y, int w,
-                    int lanes, int64_t n_long, const int32_t *long_rows) {
+                    int lanes, int64_t n_long, const int32_t *long_rows, const row_patterns &pat) {
     if (n == 0) return hipSuccess;
     if (w == kCsrRowThread)
         return t == vt::f64
-                   ? launch_csr_rowthread<double>(s, n, rp, col, val, x, alpha, beta, y, lanes)
-                   : launch_csr_rowthread<float>(s, n, rp, col, val, x, alpha, beta, y, lanes);
+                   ? launch_csr_rowthread<double>(s, n, rp, col, val, pat, x, alpha, beta, y, lanes)
+                   : launch_csr_rowthread<float>(s, n, rp, col, val, pat, x, alpha, beta, y, lanes);
     const int32_t long_t = n_long > 0 ? csr_long_threshold(w) : INT_MAX;
     return t == vt::f64
                ? launch_csr<double>(s, n, rp, col, val, x, alpha, beta, y, w, long_t, n_long, long_rows)

@@ -384,6 +384,25 @@ def test_midsize_iterations_match_oracle(g, orc, gen_mod, ctx, n, h, fmt):
         assert np.linalg.norm(host(x) - xo) <= 1e-11 * np.linalg.norm(xo), bs
 
 
+@pytest.mark.parametrize("h", [1, 5, 13])
+@pytest.mark.parametrize("fmt", ["csr", "ell", "sellp"])
+def test_large_iterations_match_oracle(g, orc, gen_mod, ctx, h, fmt):
+    """Iterations above the mid-size limits, whose products take the columns of
+    a banded matrix from its repeated rows (row lengths of 3, 11 and 27: a lane
+    and four lanes per CSR row).  Bounds as for the mid-size iterations."""
+    n = 2_100_001 if h < 13 else 560_003
+    A = band_spd(n, h)
+    b = orc.spmv(A, gen_mod.uniform(19, n))
+    M = g.Matrix.from_csr(*A).convert(fmt)
+    ctx.set_solver_opts(check_every=4, single_workgroup=0)
+    for solver, k, bound in (("cg", 6, 1e-11), ("bicgstab", 4, 1e-9), ("cgs", 3, 1e-9), ("pipecg", 5, 1e-11)):
+        rc, xo, info_o = getattr(orc, solver)(A, b, tol=1e-14, maxit=k)
+        x = dev(np.zeros(n))
+        info = getattr(g, solver)(M, dev(b), x, tol=1e-14, maxit=k)
+        assert info["iterations"] == info_o["iters"], (solver, info, info_o)
+        assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo), solver
+
+
 # --------------------------------------------------------------------------- shared edge cases
 def test_nonzero_initial_guess_and_long_restart(g, orc, gen_mod, ctx):
     A = gen_mod.convdiff2d(30, 0.5)

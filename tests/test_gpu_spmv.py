@@ -272,6 +272,61 @@ def test_conversions_at_tile_and_chunk_edges(g, orc, name, f32):
         back("sellp")
 
 
+def _pattern_rows(name):
+    """(n, m, rp, col) with at least a million entries whose rows repeat a few lists of column offsets."""
+    lists, length, n = (int(v) for v in name.replace("odd", "").split("x"))
+    rng = np.random.default_rng(lists * 1000 + length)
+    spread = 2 * length + 40
+    offs = [np.sort(rng.choice(np.arange(-spread, spread), size=l, replace=False))
+            for l in rng.integers(max(0, length - 2), length + 1, lists)]
+    offs[0] = np.sort(rng.choice(np.arange(-spread, spread), size=length, replace=False))
+    if lists > 2:
+        offs[1] = np.zeros(0, np.int64)                      # empty rows
+    pat = np.where(np.arange(n) < lists, np.arange(n) % lists, rng.integers(0, lists, n))
+    m = n + 2 * spread                                       # every list fits in every row
+    lens = np.array([len(o) for o in offs])[pat]
+    rp = np.zeros(n + 1, np.int64)
+    rp[1:] = np.cumsum(lens)
+    padded = np.zeros((lists, length), np.int64)
+    for k, o in enumerate(offs):
+        padded[k, :len(o)] = o
+    inside = np.arange(length)[None, :] < lens[:, None]
+    col = ((np.arange(n) + spread)[:, None] + padded[pat])[inside]
+    if name.endswith("odd"):                                 # one more list: a row of its own
+        r = n - 70
+        col[rp[r]:rp[r + 1]] = np.arange(lens[r])
+    assert rp[-1] >= 1_000_000
+    return n, m, rp.astype(np.int32), col.astype(np.int32)
+
+
+@pytest.mark.parametrize("name", ["1x5x230001", "2x8x150079", "27x7x200063", "3x9x180064", "84x12x120065",
+                                  "30x13x120001", "35x28x70001", "27x27x60001odd", "127x5x300000", "127x6x300000odd",
+                                  "128x4x400001", "128x5x300001odd", "129x5x300001", "1x64x20001", "2x70x20100",
+                                  "2x200x10127", "1x256x6001", "3x256x9001"])
+def test_repeated_rows(g, orc, name):
+    """Matrices whose rows repeat a few lists of column offsets, whose kernels take the columns from a table of
+    the lists: the numbers of lists (128) and of table entries (1024) at which that ends, row lengths at the
+    sizes that kernels are compiled for (8, 12, 28), rows in the last tile, an empty list, one odd row."""
+    n, m, rp, col = _pattern_rows(name)
+    rng = np.random.default_rng(5)
+    val, lens = rng.uniform(-1, 1, len(col)), np.diff(rp)
+    x, y0 = rng.uniform(-1, 1, m), rng.uniform(-1, 1, n)
+    for f32 in (False, True):
+        t = np.float32 if f32 else np.float64
+        A = make(g, (n, m, rp, col, val.astype(t)), f32)
+        xs, ys, vs = (v.astype(t).astype(np.float64) for v in (x, y0, val))
+        terms = np.append(vs * xs[col], 0.0).astype(np.longdouble)
+        want, size = (np.where(lens > 0, np.add.reduceat(v, rp[:-1]), 0.0) for v in (terms, np.abs(terms)))
+        want, size = (1.5 * want + 0.5 * ys).astype(np.float64), (1.5 * size + 0.5 * np.abs(ys)).astype(np.float64)
+        for fmt in ("csr", "ell", "sellp", "hybrid"):
+            C = A.clone().convert(fmt)
+            y = dev(y0.astype(t))
+            g.spmv(C, 1.5, dev(x.astype(t)), 0.5, y)
+            assert_spmv_close(host(y), want, size, lens, f32, "%s %s" % (name, fmt))
+            C.close()
+        A.close()
+
+
 def test_auto_picks_a_format(g, cases):
     A = make(g, cases["stencil27_14"])
     A.convert("auto")
