@@ -259,29 +259,51 @@ __global__ __launch_bounds__(kRowThreadBlock) void fused_csr_rowthread_kernel(
 }
 
 // ELL, two adjacent rows per thread (as in the plain SpMV).
-template <typename V, typename P, bool PAT>
+// STRIDE: with patterns, the grid is smaller than the row pairs (as for
+// SELL-P: without the loop the FP32 kernel needs 96 VGPRs instead of 115, and
+// takes 123 instead of 138 us on the 7-point stencil 256^3; held to 80 by
+// spilling it took 139).
+template <typename V, typename P, bool PAT, bool STRIDE>
 __global__ __launch_bounds__(kB) void fused_ell_kernel(int64_t n, int64_t K, int64_t ld,
                                                        const int32_t *__restrict__ ecol,
                                                        const V *__restrict__ eval, row_patterns pat,
                                                        const V *__restrict__ in, V *__restrict__ out,
                                                        P pol, red_args ra) {
-    __shared__ pattern_lds L;
     if (pol.skip()) return;
-    if constexpr (PAT) {
-        pattern_stage<kB>(pat, L);
-        __syncthreads();
-    }
     double acc[P::NV] = {};
-    // workgroup order as in the plain SpMV (row_block_order)
-    for (int64_t i = 2 * (row_block_order(n) * kB + threadIdx.x); i < n;
-         i += 2 * (int64_t)gridDim.x * kB) {
-        V s0, s1;
-        ell_pair_rows<PAT>(K, ld, i, ecol, eval, in, pat, L, s0, s1);
+    const auto store = [&](int64_t i, V in0, V in1, V s0, V s1) {
         out[i] = s0;
-        pol.add(acc, i, in[i], s0);
+        pol.add(acc, i, in0, s0);
         if (i + 1 < n) {
             out[i + 1] = s1;
-            pol.add(acc, i + 1, in[i + 1], s1);
+            pol.add(acc, i + 1, in1, s1);
+        }
+    };
+    // workgroup order as in the plain SpMV (row_block_order)
+    int64_t i = 2 * (row_block_order(n) * kB + threadIdx.x);
+    V s0, s1;
+    if constexpr (PAT) {
+        __shared__ pattern_lds L;
+        pattern_stage<kB> stage;
+        ell_pattern_pair<V> rows;
+        stage.load(pat);
+        rows.load(n, K, ld, i, eval, pat);
+        stage.store(L);
+        __syncthreads();
+        const int lane = threadIdx.x % kWave;
+        do {
+            const V in0 = in[i < n ? i : 0], in1 = in[i + 1 < n ? i + 1 : 0];
+            rows.sum(n, K, ld, i, eval, in, pat, L, s0, s1);
+            if (i < n) store(i, in0, in1, s0, s1);
+            if constexpr (!STRIDE) break;
+            i += 2 * (int64_t)gridDim.x * kB;
+            if (i - 2 * lane >= n) break;  // a whole wavefront
+            rows.load(n, K, ld, i, eval, pat);
+        } while (true);
+    } else {
+        for (; i < n; i += 2 * (int64_t)gridDim.x * kB) {
+            ell_pair_rows(K, ld, i, ecol, eval, in, s0, s1);
+            store(i, in[i], in[i + 1 < n ? i + 1 : i], s0, s1);
         }
     }
     grid_sum_apply<kB, P::NV>(acc, ra, pol.op);
@@ -300,24 +322,40 @@ __global__ __launch_bounds__(kB) void fused_sellp_kernel(int64_t n, const int64_
                                                          const V *__restrict__ in,
                                                          V *__restrict__ out, P pol, red_args ra) {
     static_assert(kB % kSellpSlice == 0, "whole slices per workgroup");
-    __shared__ pattern_lds L;
     if (pol.skip()) return;
-    if constexpr (PAT) {
-        pattern_stage<kB>(pat, L);
-        __syncthreads();
-    }
     double acc[P::NV] = {};
+    const auto store = [&](int64_t i, V in_i, V s) {
+        out[i] = s;
+        pol.add(acc, i, in_i, s);
+    };
     int64_t i = row_block_order(n) * kB + threadIdx.x;
-    if constexpr (STRIDE) {
+    if constexpr (PAT) {
+        __shared__ pattern_lds L;
+        pattern_stage<kB> stage;
+        sellp_pattern_row<V> row;
+        stage.load(pat);
+        if (i < n) row.load(i, sets, sval, pat);
+        stage.store(L);
+        __syncthreads();
+        if constexpr (STRIDE) {
+            while (i < n) {
+                const V in_i = in[i];
+                store(i, in_i, row.sum(i, in, pat, L));
+                i += (int64_t)gridDim.x * kB;
+                if (i < n) row.load(i, sets, sval, pat);
+            }
+        } else if (i < n) {
+            const V in_i = in[i];
+            store(i, in_i, row.sum(i, in, pat, L));
+        }
+    } else if constexpr (STRIDE) {
         for (; i < n; i += (int64_t)gridDim.x * kB) {
-            const V s0 = sellp_row<PAT>(i, sets, scol, sval, in, pat, L);
-            out[i] = s0;
-            pol.add(acc, i, in[i], s0);
+            const V s = sellp_row(i, sets, scol, sval, in);
+            store(i, in[i], s);
         }
     } else if (i < n) {
-        const V s0 = sellp_row<PAT>(i, sets, scol, sval, in, pat, L);
-        out[i] = s0;
-        pol.add(acc, i, in[i], s0);
+        const V s = sellp_row(i, sets, scol, sval, in);
+        store(i, in[i], s);
     }
     grid_sum_apply<kB, P::NV>(acc, ra, pol.op);
 }
@@ -439,8 +477,14 @@ static hipError_t launch_fused(hipStream_t s, const fused_matrix &A, const void 
         const int g = fused_blocks((A.n + 1) / 2);
         const red_args ra = red_for(g, partials, ticket);
         (void)with_patterns(A.pat, [&](auto p) {
-            fused_ell_kernel<V, P, decltype(p)::value><<<g, kB, 0, s>>>(
-                A.n, A.K, A.ld, A.ecol, static_cast<const V *>(A.eval), A.pat, in, out, pol, ra);
+            constexpr bool PAT = decltype(p)::value;
+            const V *val = static_cast<const V *>(A.eval);
+            if (PAT && (int64_t)g * kB < (A.n + 1) / 2)
+                fused_ell_kernel<V, P, PAT, PAT>
+                    <<<g, kB, 0, s>>>(A.n, A.K, A.ld, A.ecol, val, A.pat, in, out, pol, ra);
+            else
+                fused_ell_kernel<V, P, PAT, false>
+                    <<<g, kB, 0, s>>>(A.n, A.K, A.ld, A.ecol, val, A.pat, in, out, pol, ra);
             return hipSuccess;
         });
         return red_finish<P::NV>(s, g, ra, pol.op);

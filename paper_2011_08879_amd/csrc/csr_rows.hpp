@@ -116,7 +116,11 @@ __device__ inline V csr_chunks_sum(int64_t n, int64_t r0, const int32_t *__restr
                                    const V *__restrict__ x, const row_patterns &pat,
                                    rowthread_lds<V, G, M> &L) {
     constexpr bool PAT = M == kByPattern;
-    if constexpr (PAT) pattern_stage<kRowThreadBlock>(pat, L.tab);  // ends at the first barrier
+    if constexpr (PAT) {
+        pattern_stage<kRowThreadBlock> stage;
+        stage.load(pat);
+        stage.store(L.tab);  // completed by the first chunk's barrier
+    }
     constexpr int T = kRowThreadBlock, C = kRowThreadChunk, RT = T / G;
     const int g = threadIdx.x % G;
     const int64_t i = r0 + threadIdx.x / G;
@@ -186,19 +190,14 @@ template <typename V, int N, int G>
 __device__ inline V csr_rowwave_sum(int64_t n, int64_t r0, const int32_t *__restrict__ rp,
                                     const V *__restrict__ val, const V *__restrict__ x,
                                     const row_patterns &pat, rowthread_lds<V, G, N> &L) {
-    constexpr int T = kRowThreadBlock;
-    constexpr int RW = kWave / G, LPL = N / G, TI = kPatternInts / T;  // rows, and loads of a lane
+    constexpr int RW = kWave / G, LPL = N / G;  // rows, and loads of a lane
     const int lane = threadIdx.x % kWave, g = lane / RW;
     const int64_t i = r0 + threadIdx.x / kWave * RW + lane % RW;
     V *vals = L.val[threadIdx.x / kWave];
     const int32_t b = rp[i < n ? i : n], e = rp[i < n ? i + 1 : n];
     const int id = i < n ? pat.id[i] : 0;
-    int32_t tt[TI];
-#pragma unroll
-    for (int j = 0; j < TI; ++j) {
-        const int t = threadIdx.x + j * T;
-        tt[j] = t < pat.ints ? pat.tab[t] : 0;
-    }
+    pattern_stage<kRowThreadBlock> stage;
+    stage.load(pat);
     const int32_t kb = __builtin_amdgcn_readfirstlane(b), cn = __shfl(e, kWave - 1) - kb;
     V vv[LPL];
 #pragma unroll
@@ -206,8 +205,7 @@ __device__ inline V csr_rowwave_sum(int64_t n, int64_t r0, const int32_t *__rest
         const int t = lane + j * kWave;
         vv[j] = t < cn ? load_stream(val + kb + t) : V(0);
     }
-#pragma unroll
-    for (int j = 0; j < TI; ++j) L.tab.off[threadIdx.x + j * T] = tt[j];
+    stage.store(L.tab);
 #pragma unroll
     for (int j = 0; j < LPL; ++j) vals[lane + j * kWave] = vv[j];
     __syncthreads();

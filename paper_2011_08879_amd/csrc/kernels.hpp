@@ -18,8 +18,8 @@ namespace gko {
 // an entry for each row up to a multiple of kPatternRows; rows past the last
 // have an empty list.  id null: the matrix has no patterns.  Measured with
 // columns and with patterns (FP64 / FP32, us): 27-point stencil 128^3, ELL 124
-// / 89 -> 87 / 62, SELL-P 119 / 84 -> 99 / 63, CSR 143 / 96 -> 107 / 63;
-// 7-point stencil 160^3, ELL 72 / 52 -> 53 / 35, SELL-P 74 / 53 -> 60 / 40, CSR
+// / 89 -> 87 / 46, SELL-P 119 / 84 -> 101 / 43, CSR 143 / 96 -> 107 / 63;
+// 7-point stencil 160^3, ELL 72 / 52 -> 53 / 32, SELL-P 74 / 53 -> 54 / 30, CSR
 // 78 / 52 -> 56 / 33.
 constexpr int32_t kPatternPad = INT32_MIN;
 constexpr int kPatternMost = 128;   // lists of a matrix

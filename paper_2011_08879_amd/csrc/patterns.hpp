@@ -12,11 +12,26 @@ struct pattern_lds {
     alignas(16) int32_t off[kPatternInts];
 };
 
-// Copies the table; the caller's next barrier completes it.
+// Copies the table in two parts, so that a kernel's other loads are issued in
+// between: the table's come first, load, and the barrier after store completes
+// the copy.
 template <int T>
-__device__ inline void pattern_stage(const row_patterns &p, pattern_lds &L) {
-    for (int t = threadIdx.x; t < p.ints; t += T) L.off[t] = p.tab[t];
-}
+struct pattern_stage {
+    static constexpr int N = (kPatternInts + T - 1) / T;
+    int32_t t[N];
+    __device__ void load(const row_patterns &p) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int k = threadIdx.x + j * T;
+            t[j] = k < p.ints ? p.tab[k] : 0;
+        }
+    }
+    __device__ void store(pattern_lds &L) const {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (threadIdx.x + j * T < kPatternInts) L.off[threadIdx.x + j * T] = t[j];
+    }
+};
 
 // Columns of slots j .. j + 3 of row i with pattern offsets at `tab` (a
 // multiple of 4); negative for padding.

@@ -30,18 +30,25 @@ __global__ __launch_bounds__(kSellpBlock) void spmv_sellp_kernel(int64_t n,
                                                                  row_patterns pat,
                                                                  const V *__restrict__ x, V alpha,
                                                                  V beta, V *__restrict__ y) {
-    __shared__ pattern_lds L;
-    if constexpr (PAT) {
-        pattern_stage<kSellpBlock>(pat, L);
-        __syncthreads();
-    }
     // up to kXcdRowsMax rows each XCD takes one contiguous range of slices
     const int64_t i = row_block_order(n) * kSellpBlock + threadIdx.x;
-    if (i >= n) return;
-    const sellp_slice_of sl = sellp_slice(i, sets);
-    if (sl.w > kSellpWide) return;  // the whole wavefront: the wide-slice kernels
-    const int tab = PAT ? pat.id[i] * pat.stride : 0;
-    const V s0 = sellp_slots_sum<PAT>(sl.base, sl.r, 0, sl.w, scol, sval, x, L, tab, (int32_t)i);
+    V s0;
+    if constexpr (PAT) {
+        __shared__ pattern_lds L;
+        pattern_stage<kSellpBlock> stage;
+        sellp_pattern_row<V> row;
+        stage.load(pat);
+        if (i < n) row.load(i, sets, sval, pat);
+        stage.store(L);
+        __syncthreads();
+        if (i >= n || row.w > kSellpWide) return;
+        s0 = row.sum(i, x, pat, L);
+    } else {
+        if (i >= n) return;
+        const sellp_slice_of sl = sellp_slice(i, sets);
+        if (sl.w > kSellpWide) return;  // the whole wavefront: the wide-slice kernels
+        s0 = sellp_slots_sum(sl.base, sl.r, 0, sl.w, scol, sval, x);
+    }
     y[i] = (beta == V(0)) ? alpha * s0 : alpha * s0 + beta * y[i];
 }
 
@@ -61,8 +68,7 @@ __global__ __launch_bounds__(kSellpBlock) void sellp_wide_kernel(int64_t n_items
     const int64_t sl = items[2 * q], j0 = items[2 * q + 1];
     const int64_t base = sets[sl], w = (sets[sl + 1] - base) / kSellpSlice;
     const int64_t j1 = j0 + kSellpWideChunk < w ? j0 + kSellpWideChunk : w;
-    __shared__ pattern_lds L;  // not used
-    partial[q * kSellpSlice + r] = sellp_slots_sum<false>(base, r, j0, j1, scol, sval, x, L, 0, 0);
+    partial[q * kSellpSlice + r] = sellp_slots_sum(base, r, j0, j1, scol, sval, x);
 }
 
 // Wide slice q (a wavefront): row r's partials in item order, then y.

@@ -18,17 +18,24 @@ __global__ __launch_bounds__(kEllBlock) void spmv_ell_kernel(int64_t n, int64_t 
                                                              row_patterns pat,
                                                              const V *__restrict__ x, V alpha,
                                                              V beta, V *__restrict__ y) {
-    __shared__ pattern_lds L;
-    if constexpr (PAT) {
-        pattern_stage<kEllBlock>(pat, L);
-        __syncthreads();
-    }
     // Up to kXcdRowsMax rows each XCD takes one contiguous range of rows, so
     // the x lines that neighbouring rows share are fetched into one L2.
     const int64_t i = 2 * (row_block_order(n) * kEllBlock + threadIdx.x);
-    if (i >= n) return;
     V s0, s1;
-    ell_pair_rows<PAT>(K, ld, i, ecol, eval, x, pat, L, s0, s1);
+    if constexpr (PAT) {
+        __shared__ pattern_lds L;
+        pattern_stage<kEllBlock> stage;
+        ell_pattern_pair<V> rows;
+        stage.load(pat);
+        rows.load(n, K, ld, i, eval, pat);
+        stage.store(L);
+        __syncthreads();
+        rows.sum(n, K, ld, i, eval, x, pat, L, s0, s1);
+        if (i >= n) return;
+    } else {
+        if (i >= n) return;
+        ell_pair_rows(K, ld, i, ecol, eval, x, s0, s1);
+    }
     y[i] = (beta == V(0)) ? alpha * s0 : alpha * s0 + beta * y[i];
     if (i + 1 < n) y[i + 1] = (beta == V(0)) ? alpha * s1 : alpha * s1 + beta * y[i + 1];
 }
