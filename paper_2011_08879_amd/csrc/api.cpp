@@ -1096,9 +1096,9 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
                         spmv_dispatch(A, v, 1.0, w.p, 0.0, w.q);
                         HIPC(cg_pq(st, v.t, n, w.p, w.q, S, w.partials, w.ticket));
                     }
-                    HIPC(cg_update(st, v.t, n, x, w.r, zz, w.p, w.q, inv, bs, S, w.partials,
-                                   w.ticket, flexible));
-                    HIPC(cg_direction(st, v.t, n, zz, w.p, S));
+                    HIPC(cg_update(st, v.t, n, w.r, zz, w.q, inv, bs, S, w.partials, w.ticket,
+                                   flexible));
+                    HIPC(cg_direction(st, v.t, n, zz, w.p, x, S));
                 }
             });
             h = read_back(c, S);

@@ -36,6 +36,31 @@ __device__ inline void bj_tile_stage(int64_t n, int64_t base, const V *__restric
         L.inv[t] = (off + t < nb * P) ? inv[off + t] : V(0);
 }
 
+// bj_tile_stage in two parts: the loads of a tile's blocks, issued while
+// another tile is worked on, and their way into LDS.
+template <typename V, int BS, int T>
+struct bj_ahead {
+    static constexpr int P = bj_packed<BS>(), N = (T / BS * P + T - 1) / T;
+    V v[N];
+    __device__ void load(int64_t n, int64_t base, const V *__restrict__ inv) {
+        const int64_t nb = (n + BS - 1) / BS, off = (base / BS) * P;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int t = threadIdx.x + j * T;
+            v[j] = t < T / BS * P && off + t < nb * P ? load_stream(inv + off + t) : V(0);
+        }
+    }
+    __device__ void store(bj_lds<V, BS, T> &L) const {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int t = threadIdx.x + j * T;
+            if (t < T / BS * P) L.inv[t] = v[j];
+        }
+    }
+};
+template <typename V, int T>
+struct bj_ahead<V, 0, T> {};
+
 template <typename V, int BS, int T>
 __device__ inline V bj_tile_apply(V ri, bj_lds<V, BS, T> &L) {
     constexpr int P = bj_packed<BS>();

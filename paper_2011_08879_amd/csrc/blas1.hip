@@ -373,34 +373,54 @@ __global__ __launch_bounds__(kB) void cg_pq_kernel(int64_t n, const V *__restric
     grid_sum_apply<kB, 1>(v, ra, cg_alpha_op{sc});
 }
 
-// x += alpha p; r -= alpha q; z = M^-1 r; rho' = r.z; rr = r.r; then beta.
+// r -= alpha q; z = M^-1 r; rho' = r.z; rr = r.r; then beta.  Bound by memory.
+// The loads of a workgroup's next rows are on their way while it works on
+// these.  x += alpha p is left to the direction kernel, which reads p anyway;
+// sc->half says that it is due.
 template <typename V, int BS, bool FLEX>
-__global__ __launch_bounds__(kB) void cg_update_kernel(int64_t n, V *__restrict__ x,
-                                                       V *__restrict__ r, V *__restrict__ z,
-                                                       const V *__restrict__ p,
-                                                       const V *__restrict__ q,
+__global__ __launch_bounds__(kB) void cg_update_kernel(int64_t n, V *__restrict__ r,
+                                                       V *__restrict__ z, const V *__restrict__ q,
                                                        const V *__restrict__ inv,
                                                        krylov_scalars *sc, red_args ra) {
     __shared__ bj_lds<V, BS, kB> L;
-    if (sc->done) return;
-    const double alpha = sc->alpha;
+    const int64_t step = (int64_t)gridDim.x * kB;
     double a_rz = 0.0, a_rr = 0.0, a_zt = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * kB; base < n; base += (int64_t)gridDim.x * kB) {
+    V r_next = V(0), q_next = V(0);
+    bj_ahead<V, BS, kB> blocks;
+    const auto load = [&](int64_t base) {
+        const int64_t i = base + threadIdx.x;
+        if (i < n) {
+            r_next = r[i];
+            q_next = q[i];
+        }
+        if constexpr (BS > 0)
+            if (base < n) blocks.load(n, base, inv);
+    };
+    int64_t base = (int64_t)blockIdx.x * kB;
+    load(base);
+    if (sc->done) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) sc->half = 0;
+        return;
+    }
+    const double alpha = sc->alpha;
+    for (; base < n; base += step) {
         const int64_t i = base + threadIdx.x;
         V ri = V(0), ro = V(0);
         if (i < n) {
-            x[i] = (V)((double)x[i] + alpha * (double)p[i]);
-            ro = r[i];
-            ri = (V)((double)ro - alpha * (double)q[i]);
+            ro = r_next;
+            ri = (V)((double)ro - alpha * (double)q_next);
             r[i] = ri;
         }
         V zi = ri;
         if constexpr (BS > 0) {
-            bj_tile_stage<V, BS, kB>(n, base, inv, L);
+            blocks.store(L);
+            load(base + step);
             zi = bj_tile_apply<V, BS, kB>(ri, L);
+            if (i < n) z[i] = zi;
+        } else {
+            load(base + step);
         }
         if (i < n) {
-            if constexpr (BS > 0) z[i] = zi;
             a_rz += (double)ri * (double)zi;
             a_rr += (double)ri * (double)ri;
             if constexpr (FLEX) a_zt += (double)zi * ((double)ri - (double)ro);
@@ -415,15 +435,59 @@ __global__ __launch_bounds__(kB) void cg_update_kernel(int64_t n, V *__restrict_
     }
 }
 
-// p = z + beta p  (z = r without a preconditioner).
-template <typename V>
+// x += alpha p where it is due, then p = z + beta p (z = r without a
+// preconditioner).  VEC: 16 bytes of each vector per thread, all of them
+// aligned.
+template <typename V, bool VEC>
 __global__ __launch_bounds__(kB) void cg_direction_kernel(int64_t n, const V *__restrict__ z,
-                                                          V *__restrict__ p,
+                                                          V *__restrict__ p, V *__restrict__ x,
                                                           const krylov_scalars *sc) {
-    if (sc->done) return;
-    const double beta = sc->beta;
-    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB)
-        p[i] = (V)((double)z[i] + beta * (double)p[i]);
+    constexpr int W = VEC ? 16 / sizeof(V) : 1;
+    typedef V vec __attribute__((ext_vector_type(16 / sizeof(V))));
+    using U = std::conditional_t<VEC, vec, V>;
+    const int64_t units = n / W, first = (int64_t)blockIdx.x * kB + threadIdx.x;
+    const U *zu = reinterpret_cast<const U *>(z);
+    U *pu = reinterpret_cast<U *>(p), *xu = reinterpret_cast<U *>(x);
+    U pv{}, zv{}, xv{};
+    if (first < units) {  // on their way while the state is read
+        pv = pu[first];
+        zv = zu[first];
+        xv = xu[first];
+    }
+    if (!sc->half) return;
+    const bool done = sc->done != 0;
+    const double alpha = sc->alpha, beta = sc->beta;
+    const auto one = [&](V &pi, V zi, V &xi) {
+        xi = (V)((double)xi + alpha * (double)pi);
+        pi = (V)((double)zi + beta * (double)pi);
+    };
+    for (int64_t u = first; u < units; u += (int64_t)gridDim.x * kB) {
+        if (u != first) {
+            pv = pu[u];
+            zv = zu[u];
+            xv = xu[u];
+        }
+        if constexpr (VEC) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                V pi = pv[w], xi = xv[w];
+                one(pi, zv[w], xi);
+                pv[w] = pi;
+                xv[w] = xi;
+            }
+        } else {
+            one(pv, zv, xv);
+        }
+        xu[u] = xv;
+        if (!done) pu[u] = pv;
+    }
+    if constexpr (VEC)
+        if (const int64_t i = units * W + first; i < n) {
+            V pi = p[i], xi = x[i];
+            one(pi, z[i], xi);
+            x[i] = xi;
+            if (!done) p[i] = pi;
+        }
 }
 
 template <typename V>
@@ -578,49 +642,54 @@ hipError_t cg_pq(hipStream_t s, vt t, int64_t n, const void *p, const void *q, k
 }
 
 template <typename V, bool FLEX>
-static hipError_t launch_cg_update(hipStream_t s, int64_t n, void *x, void *r, void *z,
-                                   const void *p, const void *q, const void *inv, int bs,
-                                   krylov_scalars *sc, double *partials, unsigned *ticket) {
+static hipError_t launch_cg_update(hipStream_t s, int64_t n, void *r, void *z, const void *q,
+                                   const void *inv, int bs, krylov_scalars *sc, double *partials,
+                                   unsigned *ticket) {
     const int g = reduction_blocks(n);
     const red_args ra = red_for(g, partials, ticket);
-    V *X = static_cast<V *>(x), *R = static_cast<V *>(r), *Z = static_cast<V *>(z);
-    const V *P = static_cast<const V *>(p), *Q = static_cast<const V *>(q);
-    const V *I = static_cast<const V *>(inv);
+    V *R = static_cast<V *>(r), *Z = static_cast<V *>(z);
+    const V *Q = static_cast<const V *>(q), *I = static_cast<const V *>(inv);
     switch (bs) {
-        case 0: cg_update_kernel<V, 0, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
-        case 1: cg_update_kernel<V, 1, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
-        case 2: cg_update_kernel<V, 2, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
-        case 4: cg_update_kernel<V, 4, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
-        case 8: cg_update_kernel<V, 8, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
-        case 16: cg_update_kernel<V, 16, FLEX><<<g, kB, 0, s>>>(n, X, R, Z, P, Q, I, sc, ra); break;
+        case 0: cg_update_kernel<V, 0, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
+        case 1: cg_update_kernel<V, 1, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
+        case 2: cg_update_kernel<V, 2, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
+        case 4: cg_update_kernel<V, 4, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
+        case 8: cg_update_kernel<V, 8, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
+        case 16: cg_update_kernel<V, 16, FLEX><<<g, kB, 0, s>>>(n, R, Z, Q, I, sc, ra); break;
         default: return hipErrorInvalidValue;
     }
     if constexpr (FLEX) return red_finish<3>(s, g, ra, cg_update_op{sc, true});
     return red_finish<2>(s, g, ra, cg_update_op{sc, false});
 }
 
-hipError_t cg_update(hipStream_t s, vt t, int64_t n, void *x, void *r, void *z, const void *p,
-                     const void *q, const void *inv, int bs, krylov_scalars *sc, double *partials,
-                     unsigned *ticket, bool flexible) {
+hipError_t cg_update(hipStream_t s, vt t, int64_t n, void *r, void *z, const void *q,
+                     const void *inv, int bs, krylov_scalars *sc, double *partials, unsigned *ticket,
+                     bool flexible) {
     if (flexible)
-        return t == vt::f64
-                   ? launch_cg_update<double, true>(s, n, x, r, z, p, q, inv, bs, sc, partials, ticket)
-                   : launch_cg_update<float, true>(s, n, x, r, z, p, q, inv, bs, sc, partials, ticket);
-    return t == vt::f64
-               ? launch_cg_update<double, false>(s, n, x, r, z, p, q, inv, bs, sc, partials, ticket)
-               : launch_cg_update<float, false>(s, n, x, r, z, p, q, inv, bs, sc, partials, ticket);
+        return t == vt::f64 ? launch_cg_update<double, true>(s, n, r, z, q, inv, bs, sc, partials, ticket)
+                            : launch_cg_update<float, true>(s, n, r, z, q, inv, bs, sc, partials, ticket);
+    return t == vt::f64 ? launch_cg_update<double, false>(s, n, r, z, q, inv, bs, sc, partials, ticket)
+                        : launch_cg_update<float, false>(s, n, r, z, q, inv, bs, sc, partials, ticket);
 }
 
-hipError_t cg_direction(hipStream_t s, vt t, int64_t n, const void *z, void *p,
-                        const krylov_scalars *sc) {
-    const int g = stream_blocks(n);
-    if (t == vt::f64)
-        cg_direction_kernel<double><<<g, kB, 0, s>>>(n, static_cast<const double *>(z),
-                                                     static_cast<double *>(p), sc);
-    else
-        cg_direction_kernel<float><<<g, kB, 0, s>>>(n, static_cast<const float *>(z),
-                                                    static_cast<float *>(p), sc);
+template <typename V>
+static hipError_t launch_cg_direction(hipStream_t s, int64_t n, const void *z, void *p, void *x,
+                                      const krylov_scalars *sc) {
+    const V *Z = static_cast<const V *>(z);
+    V *P = static_cast<V *>(p), *X = static_cast<V *>(x);
+    if ((((uintptr_t)z | (uintptr_t)p | (uintptr_t)x) & 15) == 0) {
+        constexpr int W = 16 / sizeof(V);
+        cg_direction_kernel<V, true><<<stream_blocks((n + W - 1) / W), kB, 0, s>>>(n, Z, P, X, sc);
+    } else {
+        cg_direction_kernel<V, false><<<stream_blocks(n), kB, 0, s>>>(n, Z, P, X, sc);
+    }
     return hipGetLastError();
+}
+
+hipError_t cg_direction(hipStream_t s, vt t, int64_t n, const void *z, void *p, void *x,
+                        const krylov_scalars *sc) {
+    return t == vt::f64 ? launch_cg_direction<double>(s, n, z, p, x, sc)
+                        : launch_cg_direction<float>(s, n, z, p, x, sc);
 }
 
 // ------------------------------------------------------------------ pipelined CG

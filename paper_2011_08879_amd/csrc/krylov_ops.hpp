@@ -32,6 +32,7 @@ struct cg_update_step {
     bool flex;
     __device__ void operator()(krylov_scalars &s, const double *o) const {
         s.iter += 1;
+        s.half = 1;
         s.rr = o[1];
         if (!std::isfinite(o[1]) || !std::isfinite(o[0])) {
             s.done = kBreakdown;

@@ -70,10 +70,10 @@ hipError_t cgs_spmv_alpha(hipStream_t s, const fused_matrix &A, const void *p, v
 hipError_t cg_pq(hipStream_t s, vt t, int64_t n, const void *p, const void *q, krylov_scalars *sc,
                  double *partials, unsigned *ticket);
 // flexible: beta = z.(r - r_old) / rho (flexible CG) instead of r.z / rho.
-hipError_t cg_update(hipStream_t s, vt t, int64_t n, void *x, void *r, void *z, const void *p,
-                     const void *q, const void *inv, int bs, krylov_scalars *sc, double *partials,
-                     unsigned *ticket, bool flexible);
-hipError_t cg_direction(hipStream_t s, vt t, int64_t n, const void *z, void *p,
+hipError_t cg_update(hipStream_t s, vt t, int64_t n, void *r, void *z, const void *q,
+                     const void *inv, int bs, krylov_scalars *sc, double *partials, unsigned *ticket,
+                     bool flexible);
+hipError_t cg_direction(hipStream_t s, vt t, int64_t n, const void *z, void *p, void *x,
                         const krylov_scalars *sc);
 
 // Pipelined (P)CG (Ghysels and Vanroose).  Start from r = b - A x:

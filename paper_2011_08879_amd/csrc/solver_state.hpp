@@ -28,7 +28,8 @@ struct krylov_scalars {
     int32_t iter;     // completed iterations
     int32_t maxit;    // iteration cap
     int32_t done;     // solver_flag
-    int32_t half;     // BiCGSTAB: converged at the half step, x += alpha p pending
+    int32_t half;     // x += alpha p pending.  BiCGSTAB: converged at the half step; CG of large
+                      // systems: since the update of r, until the direction kernel
 };
 
 // How a kernel of a mid-size iteration gets its scalars (midsize.hip): state
