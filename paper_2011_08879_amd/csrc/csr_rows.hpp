@@ -85,8 +85,8 @@ struct rowthread_lds {
 };
 template <typename V, int G>
 struct rowthread_lds<V, G, kByColumn> {
-    V val[kRowThreadChunk];
     int32_t col[kRowThreadChunk];
+    V val[kRowThreadChunk];
 };
 template <typename V, int G>
 struct rowthread_lds<V, G, kByPattern> {
