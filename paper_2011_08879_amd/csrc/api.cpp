@@ -343,7 +343,7 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
                             static_cast<int32_t *>(A->carry_a), A->carry_b, A->merge_rows));
             break;
         case GKO_FMT_COO:
-            HIPC(spmv_coo(s, v.t, A->n, A->nnz, A->row, A->col, v.val, x, alpha, beta, y, false,
+            HIPC(spmv_coo(s, v.t, A->n, A->nnz, A->max_len, A->row, A->col, v.val, x, alpha, beta, y, false,
                           A->carry_a, A->carry_b));
             break;
         case GKO_FMT_ELL:
@@ -354,7 +354,7 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
             HIPC(spmv_ell(s, v.t, A->n, A->K, A->ld, A->ecol, v.eval, A->patterns(), x, alpha,
                           beta, y));
             if (A->tnnz > 0)
-                HIPC(spmv_coo(s, v.t, A->n, A->tnnz, A->trow, A->tcol, v.tval, x, alpha, 1.0, y,
+                HIPC(spmv_coo(s, v.t, A->n, A->tnnz, A->max_len - A->K, A->trow, A->tcol, v.tval, x, alpha, 1.0, y,
                               true, A->carry_a, A->carry_b));
             break;
         case GKO_FMT_SELLP:

@@ -101,8 +101,9 @@ bool merge_rows_parallel(int64_t n, int64_t nnz, int64_t max_len);
 // COO: equal nonzero chunks per wavefront.  accumulate: y += alpha A x, rows
 // without entries untouched (used for the HYB tail).
 int64_t coo_chunks(int64_t nnz);
-// head/tail: coo_chunks(nnz) values of type t each.
-hipError_t spmv_coo(hipStream_t s, vt t, int64_t n, int64_t nnz, const int32_t *row,
+// longest: the most entries of one row.  head/tail: coo_chunks(nnz) values of
+// type t each.
+hipError_t spmv_coo(hipStream_t s, vt t, int64_t n, int64_t nnz, int64_t longest, const int32_t *row,
                     const int32_t *col, const void *val, const void *x, double alpha, double beta,
                     void *y, bool accumulate, void *head, void *tail);
 

@@ -327,6 +327,49 @@ def test_repeated_rows(g, orc, name):
         A.close()
 
 
+def _coo_lens(name):
+    rng = np.random.default_rng(len(name))
+    kind, n, l = name.split("x")
+    n, l = int(n), int(l)
+    if kind == "even":
+        return np.full(n, l)
+    lens = rng.integers(0, l + 1, n)
+    if kind == "gaps":                                       # runs of empty rows, also first and last
+        lens[:n // 5] = 0
+        lens[n // 3:n // 2] = 0
+        lens[-(n // 6):] = 0
+    return lens
+
+
+@pytest.mark.parametrize("name", ["evenx1x1", "evenx4x64", "evenx5x64", "evenx4x63", "evenx64x16", "evenx65x16", "evenx33x31",
+                                  "evenx256x1", "evenx257x1", "evenx1025x3", "evenx40x65", "evenx7x300", "randx900x64",
+                                  "randx900x5", "gapsx2000x12", "gapsx3000x64", "randx3000x66", "randx500x256",
+                                  "randx500x300", "evenx46876x64", "gapsx300000x33"])
+@pytest.mark.parametrize("f32", [False, True])
+def test_coo_rows_at_batch_and_chunk_edges(g, name, f32):
+    """COO rows at the ends of batches (64 entries), of a wavefront's chunks (256 and, from 3 million entries on,
+    512) and at 64 entries, up to which a wavefront keeps its rows whole; 256, from which on loads go eight deep."""
+    lens = _coo_lens(name)
+    n, m = len(lens), 1000
+    rng = np.random.default_rng(3)
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    start = rng.integers(0, m - 301, n)
+    row = np.repeat(np.arange(n), lens)
+    col = (start[row] + np.arange(len(row)) - rp[:-1][row]).astype(np.int32)
+    t = np.float32 if f32 else np.float64
+    val, x, y0 = (rng.uniform(-1, 1, k).astype(t) for k in (len(col), m, n))
+    A = make(g, (n, m, rp, col, val), f32).convert("coo")
+    terms = np.append(val.astype(np.float64) * x.astype(np.float64)[col], 0.0).astype(np.longdouble)
+    at = np.minimum(rp[:-1], len(col))
+    sums, size = (np.where(lens > 0, np.add.reduceat(v, at), 0.0) for v in (terms, np.abs(terms)))
+    for alpha, beta in ((1.0, 0.0), (-1.5, 0.5)):
+        y = dev(y0)
+        g.spmv(A, alpha, dev(x), beta, y)
+        assert_spmv_close(host(y), (alpha * sums + beta * y0).astype(np.float64),
+                          (abs(alpha) * size + beta * np.abs(y0)).astype(np.float64), lens, f32, name)
+
+
 def test_auto_picks_a_format(g, cases):
     A = make(g, cases["stencil27_14"])
     A.convert("auto")
