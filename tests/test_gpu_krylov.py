@@ -403,6 +403,27 @@ def test_large_iterations_match_oracle(g, orc, gen_mod, ctx, h, fmt):
         assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo), solver
 
 
+@pytest.mark.parametrize("maxit", [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65])
+@pytest.mark.parametrize("solver", ["cg", "pipecg", "bicgstab", "cgs"])
+def test_caps_at_polling_intervals(g, orc, gen_mod, ctx, solver, maxit):
+    """Iteration caps around multiples of the 16 iterations between two looks at
+    the state: intervals are enqueued before the state of the one before is
+    known, and none may go past the cap or past convergence.  The matrix has
+    condition at most 6, so the bounds are those of the mid-size iterations
+    times the longer run (5 k u kappa, squared for CGS and BiCGSTAB)."""
+    A = band_spd(3001, 1)
+    b = orc.spmv(A, gen_mod.uniform(19, 3001))
+    M = g.Matrix.from_csr(*A).convert("ell")
+    ctx.set_solver_opts(single_workgroup=0)
+    rc, xo, info_o = getattr(orc, solver)(A, b, tol=1e-9, maxit=maxit)
+    x = dev(np.zeros(3001))
+    info = getattr(g, solver)(M, dev(b), x, tol=1e-9, maxit=maxit)
+    assert abs(info["iterations"] - info_o["iters"]) <= (0 if info_o["iters"] == maxit else 1)
+    assert info["iterations"] <= maxit
+    bound = 1e-10 if info["iterations"] == info_o["iters"] else 1e-8
+    assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo)
+
+
 # --------------------------------------------------------------------------- shared edge cases
 def test_nonzero_initial_guess_and_long_restart(g, orc, gen_mod, ctx):
     A = gen_mod.convdiff2d(30, 0.5)
