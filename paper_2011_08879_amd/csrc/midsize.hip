@@ -77,11 +77,18 @@ inline int mid_parts(int64_t terms, int grid, int terms_per_block) {
 constexpr int kSumSlots = kFinalizeBlock / kWave;
 constexpr int kSumRounds = (kMidBlocks * (kT / kPart) + kFinalizeBlock - 1) / kFinalizeBlock;
 
+// The state k.in comes with them, a word per thread: read by the one thread
+// that works on it, after the sums, it was a second wait for memory.
+constexpr int kStateWords = sizeof(krylov_scalars) / sizeof(uint64_t);
+static_assert(sizeof(krylov_scalars) % sizeof(uint64_t) == 0 && kStateWords <= kWave, "whole words");
+
 template <int T, int NV>
 struct mid_totals {
     static constexpr int S = kFinalizeBlock / T;
     double t[NV][S][kSumRounds];
+    uint64_t word;  // of the state
     __device__ void load(const scalar_link &k) {
+        if (threadIdx.x < kStateWords) word = reinterpret_cast<const uint64_t *>(k.in)[threadIdx.x];
         if (!k.out) return;
 #pragma unroll
         for (int j = 0; j < NV; ++j)
@@ -116,25 +123,21 @@ template <int T, int NV, typename Step>
 __device__ inline bool mid_enter(const scalar_link &k, const mid_totals<T, NV> &totals,
                                  const Step &step, krylov_scalars &st) {
     __shared__ double slots[NV][kSumSlots];
-    if (k.out) {  // uniform
-        totals.to_slots(slots);
-        __syncthreads();
-    }
+    uint64_t *words = reinterpret_cast<uint64_t *>(&st);
+    if (threadIdx.x < kStateWords) words[threadIdx.x] = totals.word;
+    if (k.out) totals.to_slots(slots);  // uniform
+    __syncthreads();
+    if (!k.out) return st.done == 0;
     if (threadIdx.x < kWave) {
         double o[NV] = {};
-        if (k.out)
 #pragma unroll
-            for (int j = 0; j < NV; ++j)
-                o[j] = wave_total(threadIdx.x < kSumSlots ? slots[j][threadIdx.x] : 0.0);
-        if (threadIdx.x == 0) {
-            st = *k.in;
-            if (k.out) {
-                if (st.done == 0) step(st, o);
-                if (blockIdx.x == 0) *k.out = st;
-            }
-        }
+        for (int j = 0; j < NV; ++j)
+            o[j] = wave_total(threadIdx.x < kSumSlots ? slots[j][threadIdx.x] : 0.0);
+        if (threadIdx.x == 0 && st.done == 0) step(st, o);
     }
     __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x < kStateWords)
+        reinterpret_cast<uint64_t *>(k.out)[threadIdx.x] = words[threadIdx.x];
     return st.done == 0;
 }
 
