@@ -707,10 +707,17 @@ inline double *md(void *p) { return static_cast<double *>(p); }
 // SELL-P walk a row by one thread: BiCGSTAB on 50,000 banded rows of 20 entries
 // 117 / 100, of 70 entries 184 / 179 (SELL-P 166 / 176), of 120 entries 212 /
 // 239, while CSR with 8 or 32 lanes per row takes 155 / 122 and 181 / 152.
+// Matrices with row patterns: the kernels for large systems leave out the
+// column indices, these do not, so the line lies lower: 7-point 1M rows, 6.9M
+// entries 45 / 39 (CSR 46 / 44); 2M rows, 13.6M entries 66 / 70 (CSR 68 / 79,
+// block-Jacobi 77 / 107); 5-point 2M rows, 9.8M entries CG 60 / 60, BiCGSTAB 106
+// / 112, CGS in CSR 105 / 113; FP32 with block-Jacobi 1M rows, 6.9M entries 35 /
+// 33, in CSR 34 / 42.
 bool mid_fits(const fused_matrix &A, int64_t nnz) {
-    const int64_t scale = A.t == vt::f64 ? 1 : 2;
-    return A.n <= kMidRows / scale && nnz <= 14000000 / scale &&
-           (A.format == fused_matrix::csr || nnz <= 48 * A.n);
+    const bool f64 = A.t == vt::f64, csr = A.format == fused_matrix::csr;
+    int64_t most = f64 ? 14000000 : 7000000;
+    if (A.pat.id) most = f64 ? 8000000 : csr ? 4000000 : 7000000;
+    return A.n <= kMidRows / (f64 ? 1 : 2) && nnz <= most && (csr || nnz <= 48 * A.n);
 }
 
 hipError_t mid_cg_product(hipStream_t s, const fused_matrix &A, const void *z, const void *p_old,
