@@ -774,39 +774,73 @@ __global__ __launch_bounds__(kB) void pipe_update_kernel(
     V *__restrict__ p, V *__restrict__ x, V *__restrict__ r, V *__restrict__ u, V *__restrict__ w,
     V *__restrict__ m, const V *__restrict__ inv, krylov_scalars *sc, red_args ra) {
     __shared__ bj_lds<V, BS, kB> L;
+    // FP64 with a preconditioner: the next rows' loads are on their way while
+    // these are worked on.  160^3 rows, blocks of 2, 4, 8 and 16, us per
+    // iteration: 200, 211, 236, 262 -> 188, 196, 205, 230; without blocks 136 ->
+    // 138, FP32 with blocks of 8 (120^3) 51 -> 54.
+    constexpr bool kAhead = BS > 0 && sizeof(V) == 8;
+    struct {
+        V n, z, w, s, p, x, r, m, q, u;
+    } a, c;
+    bj_ahead<V, BS, kB> blocks;
+    const int64_t step = (int64_t)gridDim.x * kB;
+    const auto load = [&](int64_t base) {
+        const int64_t i = base + threadIdx.x;
+        if (i < n) {
+            a.n = nv[i];
+            a.z = z[i];
+            a.w = w[i];
+            a.s = s[i];
+            a.p = p[i];
+            a.x = x[i];
+            a.r = r[i];
+            if constexpr (BS > 0) {
+                a.m = m[i];
+                a.q = q[i];
+                a.u = u[i];
+            }
+        }
+        if constexpr (BS > 0)
+            if (base < n) blocks.load(n, base, inv);
+    };
+    int64_t base = (int64_t)blockIdx.x * kB;
+    if constexpr (kAhead) load(base);
     if (sc->done) return;
     const double alpha = sc->alpha, beta = sc->beta;
     double a_g = 0.0, a_d = 0.0, a_rr = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * kB; base < n; base += (int64_t)gridDim.x * kB) {
+    for (; base < n; base += step) {
         const int64_t i = base + threadIdx.x;
+        if constexpr (!kAhead) load(base);
+        c = a;
+        if constexpr (BS > 0) blocks.store(L);
+        if constexpr (kAhead) load(base + step);
         V wi = V(0), ri = V(0), ui = V(0);
         if (i < n) {
-            const double zi = (double)nv[i] + beta * (double)z[i];
-            const double si = (double)w[i] + beta * (double)s[i];
+            const double zi = (double)c.n + beta * (double)c.z;
+            const double si = (double)c.w + beta * (double)c.s;
             z[i] = (V)zi;
             s[i] = (V)si;
             if constexpr (BS > 0) {
-                const double qi = (double)m[i] + beta * (double)q[i];
-                const double pi = (double)u[i] + beta * (double)p[i];
+                const double qi = (double)c.m + beta * (double)c.q;
+                const double pi = (double)c.u + beta * (double)c.p;
                 q[i] = (V)qi;
                 p[i] = (V)pi;
-                x[i] = (V)((double)x[i] + alpha * (double)(V)pi);
-                ri = (V)((double)r[i] - alpha * (double)(V)si);
-                ui = (V)((double)u[i] - alpha * (double)(V)qi);
+                x[i] = (V)((double)c.x + alpha * (double)(V)pi);
+                ri = (V)((double)c.r - alpha * (double)(V)si);
+                ui = (V)((double)c.u - alpha * (double)(V)qi);
                 u[i] = ui;
             } else {
-                const double pi = (double)r[i] + beta * (double)p[i];
+                const double pi = (double)c.r + beta * (double)c.p;
                 p[i] = (V)pi;
-                x[i] = (V)((double)x[i] + alpha * (double)(V)pi);
-                ri = (V)((double)r[i] - alpha * (double)(V)si);
+                x[i] = (V)((double)c.x + alpha * (double)(V)pi);
+                ri = (V)((double)c.r - alpha * (double)(V)si);
                 ui = ri;
             }
             r[i] = ri;
-            wi = (V)((double)w[i] - alpha * (double)(V)zi);
+            wi = (V)((double)c.w - alpha * (double)(V)zi);
             w[i] = wi;
         }
         if constexpr (BS > 0) {
-            bj_tile_stage<V, BS, kB>(n, base, inv, L);
             const V mi = bj_tile_apply<V, BS, kB>(wi, L);
             if (i < n) m[i] = mi;
         }
