@@ -50,7 +50,12 @@ namespace gko {
 
 namespace {
 
-constexpr int kT = 1024;          // threads of a workgroup
+// Threads of a workgroup: 1024, and 512 where these still are one round of the
+// 256 compute units: 1024 would leave half of them idle.  us per iteration with
+// 1024 and with 512: CG 48^3 rows 13.1 / 11.1, 30^3 15.6 / 13.0, 50^3 in CSR
+// 16.7 / 14.3; BiCGSTAB 211 x 307 rows 26.2 / 22.2; CGS 200^2 33.0 / 26.4.
+constexpr int kT = 1024, kHalfT = 512;
+inline bool half_blocks(int64_t threads) { return threads <= 256 * kHalfT; }
 constexpr int kPart = 256;        // threads that share one partial
 constexpr int kEntries = 8;       // a row's entries loaded before the totals are waited for
 
@@ -167,7 +172,8 @@ __device__ inline void mid_store_sums(const double (&acc)[NV], int g, int64_t bl
         }
     }
     __syncthreads();
-    if (g == (int)gridDim.x) {
+    // (a workgroup of kHalfT threads with one partial has one row to a thread)
+    if (P > 1 && g == (int)gridDim.x) {
         if (threadIdx.x < NV) {
             double s = 0.0;
 #pragma unroll
@@ -221,11 +227,11 @@ __device__ inline row_walk walk_of(const fused_matrix &A, int64_t i, int g) {
 // partials.  A view W holds the pointers and says how an entry of the vector
 // comes from the RAW vectors it is formed from, and which products x y its NV
 // sums are of.
-template <fused_matrix::kind F, int G, typename W>
-__global__ __launch_bounds__(kT) void mid_product_kernel(fused_matrix A, W view, scalar_link k,
+template <fused_matrix::kind F, int G, int T, typename W>
+__global__ __launch_bounds__(T) void mid_product_kernel(fused_matrix A, W view, scalar_link k,
                                                          int parts, double *__restrict__ partials) {
     using V = typename W::value_type;
-    constexpr int RT = kT / G;
+    constexpr int RT = T / G;
     constexpr bool PAIR = F == fused_matrix::ell && W::kFused;
     __shared__ krylov_scalars st;
     const int32_t *__restrict__ col = F == fused_matrix::csr   ? A.col
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(kT) void mid_product_kernel(fused_matrix A, W view,
                                                        : F == fused_matrix::ell ? A.eval
                                                                                 : A.sval);
     const int g = threadIdx.x % G;
-    mid_totals<kT, W::Step::NV> totals;
+    mid_totals<T, W::Step::NV> totals;
     totals.load(k);
     double acc[W::NV] = {};
     bool entered = false;
@@ -258,7 +264,7 @@ __global__ __launch_bounds__(kT) void mid_product_kernel(fused_matrix A, W view,
 #pragma unroll
         for (int u = 0; u < kEntries; ++u) view.load(c[u] >= 0 ? c[u] : 0, raw[u]);
         if (!entered) {
-            if (!mid_enter<kT>(k, totals, view.step, st)) return;
+            if (!mid_enter<T>(k, totals, view.step, st)) return;
             entered = true;
         }
         V s = V(0);
@@ -294,7 +300,7 @@ __global__ __launch_bounds__(kT) void mid_product_kernel(fused_matrix A, W view,
             else acc[j] += x[j] * y[j];
         }
     }
-    mid_store_sums<kT, W::NV, W::kFused, PAIR>(acc, parts, block, partials);
+    mid_store_sums<T, W::NV, W::kFused, PAIR>(acc, parts, block, partials);
 }
 
 // CG: p = z + beta p_old, q = A p, p.q.
@@ -513,16 +519,12 @@ struct pipe_view {
 
 // ------------------------------------------------------------ updates
 // x += alpha p; r -= alpha q; z = M^-1 r; r.z, r.r (and z.(r - r_old)).
-// Blocks of 16 rows of doubles in half-size workgroups, for their LDS.
-template <typename V, int BS>
-constexpr int mid_update_threads() { return BS == 16 && sizeof(V) == 8 ? kT / 2 : kT; }
-
-template <typename V, int BS, bool FLEX>
-__global__ __launch_bounds__((mid_update_threads<V, BS>())) void mid_cg_update_kernel(
+// Blocks of 16 rows of doubles always in half-size workgroups, for their LDS.
+template <typename V, int BS, bool FLEX, int T>
+__global__ __launch_bounds__(T) void mid_cg_update_kernel(
     int64_t n, V *__restrict__ x, V *__restrict__ r, V *__restrict__ z, const V *__restrict__ p,
     const V *__restrict__ q, const V *__restrict__ inv, scalar_link k, int parts,
     double *__restrict__ partials) {
-    constexpr int T = mid_update_threads<V, BS>();
     __shared__ krylov_scalars st;
     __shared__ bj_lds<V, BS, T> L;
     mid_totals<T, 1> totals;
@@ -569,22 +571,23 @@ struct bicg_half_step {
     }
 };
 
-__global__ __launch_bounds__(kT) void mid_bicg_update_kernel(
+template <int T>
+__global__ __launch_bounds__(T) void mid_bicg_update_kernel(
     int64_t n, double *__restrict__ x, double *__restrict__ r, const double *__restrict__ rh,
     const double *__restrict__ p, const double *__restrict__ v, const double *__restrict__ t,
     scalar_link k, int parts, double *__restrict__ partials) {
     __shared__ krylov_scalars st;
-    mid_totals<kT, 3> totals;
+    mid_totals<T, 3> totals;
     totals.load(k);
     double acc[2] = {};
     bool entered = false;
     const int64_t block = xcd_block(blockIdx.x, gridDim.x);
-    for (int64_t i = block * kT + threadIdx.x; i - threadIdx.x < n; i += (int64_t)gridDim.x * kT) {
+    for (int64_t i = block * T + threadIdx.x; i - threadIdx.x < n; i += (int64_t)gridDim.x * T) {
         const bool ok = i < n;
         const double xi = ok ? x[i] : 0.0, ro = ok ? r[i] : 0.0, rhi = ok ? rh[i] : 0.0;
         const double pi = ok ? p[i] : 0.0, vi = ok ? v[i] : 0.0, ti = ok ? t[i] : 0.0;
         if (!entered) {
-            if (!mid_enter<kT>(k, totals, bicg_half_step{}, st)) return;
+            if (!mid_enter<T>(k, totals, bicg_half_step{}, st)) return;
             entered = true;
         }
         if (!ok) continue;
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(kT) void mid_bicg_update_kernel(
             acc[1] += rhi * ri;
         }
     }
-    mid_store_sums<kT, 2, false, false>(acc, parts, block, partials);
+    mid_store_sums<T, 2, false, false>(acc, parts, block, partials);
 }
 
 // The scalar step on the sums that an interval's last kernel left.
@@ -616,39 +619,50 @@ template <typename W>
 hipError_t launch_product(hipStream_t s, const fused_matrix &A, const W &view, const scalar_link &k,
                           const mid_sums &out, int most = kMidBlocks / 2) {
     const int lanes = A.format == fused_matrix::csr ? A.lanes : 1;
-    const int g = mid_blocks(A.n, kT / lanes, most);
-    const bool pair = A.format == fused_matrix::ell && W::kFused;
-    const int parts = pair ? mid_parts((A.n + 1) / 2, g, kT / 2) : mid_parts(A.n * lanes, g, kT);
-    *out.parts = parts;
-    double *P = out.partials;
-    if (A.format == fused_matrix::ell)
-        mid_product_kernel<fused_matrix::ell, 1, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else if (A.format == fused_matrix::sellp)
-        mid_product_kernel<fused_matrix::sellp, 1, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else if (lanes == 1)
-        mid_product_kernel<fused_matrix::csr, 1, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else if (lanes == 4)
-        mid_product_kernel<fused_matrix::csr, 4, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else if (lanes == 8)
-        mid_product_kernel<fused_matrix::csr, 8, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else if (lanes == 32)
-        mid_product_kernel<fused_matrix::csr, 32, W><<<g, kT, 0, s>>>(A, view, k, parts, P);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    const auto launch = [&](auto threads) {
+        constexpr int T = decltype(threads)::value;
+        const int g = mid_blocks(A.n, T / lanes, most);
+        const bool pair = A.format == fused_matrix::ell && W::kFused;
+        const int parts = pair ? mid_parts((A.n + 1) / 2, g, T / 2) : mid_parts(A.n * lanes, g, T);
+        *out.parts = parts;
+        double *P = out.partials;
+        if (A.format == fused_matrix::ell)
+            mid_product_kernel<fused_matrix::ell, 1, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else if (A.format == fused_matrix::sellp)
+            mid_product_kernel<fused_matrix::sellp, 1, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else if (lanes == 1)
+            mid_product_kernel<fused_matrix::csr, 1, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else if (lanes == 4)
+            mid_product_kernel<fused_matrix::csr, 4, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else if (lanes == 8)
+            mid_product_kernel<fused_matrix::csr, 8, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else if (lanes == 32)
+            mid_product_kernel<fused_matrix::csr, 32, T, W><<<g, T, 0, s>>>(A, view, k, parts, P);
+        else
+            return hipErrorInvalidValue;
+        return hipGetLastError();
+    };
+    return half_blocks(A.n * lanes) ? launch(std::integral_constant<int, kHalfT>{})
+                                    : launch(std::integral_constant<int, kT>{});
 }
 
 template <typename V, bool FLEX, int BS>
 hipError_t launch_cg_update_bs(hipStream_t s, int64_t n, void *x, void *r, void *z, const void *p,
                                const void *q, const void *inv, const scalar_link &k,
                                const mid_sums &out) {
-    constexpr int T = mid_update_threads<V, BS>();
-    const int g = mid_blocks(n, T, kMidBlocks / 2), parts = mid_parts(n, g, T);
-    *out.parts = parts;
-    mid_cg_update_kernel<V, BS, FLEX><<<g, T, 0, s>>>(
-        n, static_cast<V *>(x), static_cast<V *>(r), static_cast<V *>(z), static_cast<const V *>(p),
-        static_cast<const V *>(q), static_cast<const V *>(inv), k, parts, out.partials);
-    return hipGetLastError();
+    const auto launch = [&](auto threads) {
+        constexpr int T = decltype(threads)::value;
+        const int g = mid_blocks(n, T, kMidBlocks / 2), parts = mid_parts(n, g, T);
+        *out.parts = parts;
+        mid_cg_update_kernel<V, BS, FLEX, T><<<g, T, 0, s>>>(
+            n, static_cast<V *>(x), static_cast<V *>(r), static_cast<V *>(z),
+            static_cast<const V *>(p), static_cast<const V *>(q), static_cast<const V *>(inv), k,
+            parts, out.partials);
+        return hipGetLastError();
+    };
+    constexpr int kMost = BS == 16 && sizeof(V) == 8 ? kHalfT : kT;
+    return half_blocks(n) ? launch(std::integral_constant<int, kHalfT>{})
+                          : launch(std::integral_constant<int, kMost>{});
 }
 
 template <typename V, bool FLEX>
@@ -768,11 +782,16 @@ hipError_t mid_bicg_t(hipStream_t s, const fused_matrix &A, const void *r, const
 
 hipError_t mid_bicg_update(hipStream_t s, int64_t n, void *x, void *r, const void *rh, const void *p,
                            const void *v, const void *t, const scalar_link &k, const mid_sums &out) {
-    const int g = mid_blocks(n, kT, kMidBlocks), parts = mid_parts(n, g, kT);
-    *out.parts = parts;
-    mid_bicg_update_kernel<<<g, kT, 0, s>>>(n, md(x), md(r), cd(rh), cd(p), cd(v), cd(t), k, parts,
-                                            out.partials);
-    return hipGetLastError();
+    const auto launch = [&](auto threads) {
+        constexpr int T = decltype(threads)::value;
+        const int g = mid_blocks(n, T, kMidBlocks), parts = mid_parts(n, g, T);
+        *out.parts = parts;
+        mid_bicg_update_kernel<T><<<g, T, 0, s>>>(n, md(x), md(r), cd(rh), cd(p), cd(v), cd(t), k,
+                                                  parts, out.partials);
+        return hipGetLastError();
+    };
+    return half_blocks(n) ? launch(std::integral_constant<int, kHalfT>{})
+                          : launch(std::integral_constant<int, kT>{});
 }
 
 hipError_t mid_bicg_close(hipStream_t s, const scalar_link &k) {
