@@ -12,6 +12,7 @@
 
 #include "device.hpp"
 #include "kernels.hpp"
+#include "offsets.hpp"
 
 namespace gko {
 
@@ -80,14 +81,14 @@ __global__ __launch_bounds__(256) void csr_rows_kernel(int64_t n, const int32_t 
         const int32_t b = rp[i], e = rp[i + 1];
         if (e - b > 16 * G) any_long = 1;
         else
-            for (int32_t k = b + threadIdx.x % G; k < e; k += G) row[k] = (int32_t)i;
+            for (entry_steps<G> k(b, e, threadIdx.x % G); k.more(); k.next()) row[k.at()] = (int32_t)i;
     }
     __syncthreads();
     if (!any_long) return;
     for (int64_t r = r0; r < r0 + R && r < n; ++r) {
         const int32_t b = rp[r], e = rp[r + 1];
         if (e - b > 16 * G)
-            for (int32_t k = b + threadIdx.x; k < e; k += 256) row[k] = (int32_t)r;
+            for (entry_steps<256> k(b, e, threadIdx.x); k.more(); k.next()) row[k.at()] = (int32_t)r;
     }
 }
 
@@ -354,8 +355,8 @@ __global__ __launch_bounds__(kSlotThreads) void csr_to_slots_kernel(
     const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
     const int32_t b = rp[i < n ? i : n], e = rp[i + 1 < n ? i + 1 : n];
     const int32_t kb = rp[r0 < n ? r0 : n], ke = rp[last];
-    for (int32_t c0 = kb; c0 < ke; c0 += kSlotChunk) {
-        const int32_t cn = ke - c0 < kSlotChunk ? ke - c0 : kSlotChunk;
+    for (entry_steps<kSlotChunk> chunk(kb, ke); chunk.more(); chunk.next()) {
+        const int32_t c0 = chunk.at(), cn = chunk.count();
         const slot_span p = span_of(b, e, T.width, c0, cn);
         if (p.first >= p.last) continue;  // all past their rows' slots (the same in every wavefront)
         int32_t cc[E];
@@ -409,8 +410,8 @@ __global__ __launch_bounds__(kSlotThreads) void slots_to_csr_kernel(
     const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
     const int32_t b = rp[i < n ? i : n], e = rp[i + 1 < n ? i + 1 : n];
     const int32_t kb = rp[r0], ke = rp[last];
-    for (int32_t c0 = kb; c0 < ke; c0 += kSlotChunk) {
-        const int32_t cn = ke - c0 < kSlotChunk ? ke - c0 : kSlotChunk;
+    for (entry_steps<kSlotChunk> chunk(kb, ke); chunk.more(); chunk.next()) {
+        const int32_t c0 = chunk.at(), cn = chunk.count();
         const slot_span p = span_of(b, e, T.width, c0, cn);
         if (p.first >= p.last) continue;  // the tail's (the same in every wavefront)
         if constexpr (TAIL) {

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "device.hpp"
+#include "offsets.hpp"
 #include "patterns.hpp"
 
 namespace gko {
@@ -31,23 +32,23 @@ __device__ inline void csr_rows_sum(int64_t n, int64_t row0, int lane,
     V v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int32_t k = b[u] + lane;
-        c[u] = k < e[u] ? load_stream(col + k) : -1;
-        v[u] = k < e[u] ? load_stream(val + k) : V(0);
+        const entry_steps<W> k(b[u], e[u], lane);
+        c[u] = k.more() ? load_stream(col + k.at()) : -1;
+        v[u] = k.more() ? load_stream(val + k.at()) : V(0);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) s[u] = c[u] >= 0 ? v[u] * x[c[u]] : V(0);
     // rows longer than W: the rest in strides of 4W, four loads in flight
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        for (int32_t k = b[u] + W + lane; k < e[u]; k += 4 * W) {
+        for (entry_steps<4 * W> k(b[u], e[u], W + lane); k.more(); k.next()) {
             int32_t cc[4];
             V vv[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int32_t kj = k + j * W;
-                cc[j] = kj < e[u] ? load_stream(col + kj) : -1;
-                vv[j] = kj < e[u] ? load_stream(val + kj) : V(0);
+                const bool ok = j * W < k.left();
+                cc[j] = ok ? load_stream(col + k.at() + j * W) : -1;
+                vv[j] = ok ? load_stream(val + k.at() + j * W) : V(0);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -130,8 +131,8 @@ __device__ inline V csr_chunks_sum(int64_t n, int64_t r0, const int32_t *__restr
     int tab = 0;
     if constexpr (PAT) tab = i < n ? pat.id[i] * pat.stride : 0;
     V s = V(0);
-    for (int32_t c0 = kb; c0 < ke; c0 += C) {
-        const int32_t cn = ke - c0 < C ? ke - c0 : C;
+    for (entry_steps<C> chunk(kb, ke); chunk.more(); chunk.next()) {
+        const int32_t c0 = chunk.at(), cn = chunk.count();
         int32_t cc[C / T];
         V vv[C / T];
 #pragma unroll

@@ -7,6 +7,8 @@
 // lists share is found and the matrix is then used without patterns.
 #include "patterns.hpp"
 
+#include "offsets.hpp"
+
 namespace gko {
 
 namespace {
@@ -39,8 +41,8 @@ __device__ inline void each_entry(int64_t n, int64_t r0, const int32_t *__restri
                                   const int32_t *__restrict__ col, int32_t (&L)[kColChunk],
                                   int32_t b, int32_t e, F f) {
     const int32_t kb = rp[r0], ke = rp[r0 + kPB < n ? r0 + kPB : n];
-    for (int32_t c0 = kb; c0 < ke; c0 += kColChunk) {
-        const int32_t cn = ke - c0 < kColChunk ? ke - c0 : kColChunk;
+    for (entry_steps<kColChunk> chunk(kb, ke); chunk.more(); chunk.next()) {
+        const int32_t c0 = chunk.at(), cn = chunk.count();
         int32_t cc[kColChunk / kPB];
 #pragma unroll
         for (int u = 0; u < kColChunk / kPB; ++u) {

@@ -15,6 +15,7 @@
 #include <cmath>
 
 #include "device.hpp"
+#include "offsets.hpp"
 #include "selector_kernels.hpp"
 
 namespace gko {
@@ -52,8 +53,8 @@ __global__ __launch_bounds__(256) void feature_counts_kernel(int64_t n, int64_t 
             c[10] += (unsigned long long)((int64_t)col[e - 1] - col[b] + 1);
             c[11] += 1;
         }
-        for (int32_t k = b + lane; k < e; k += kFeatW) {
-            const int32_t cj = col[k];
+        for (entry_steps<kFeatW> step(b, e, lane); step.more(); step.next()) {
+            const int32_t k = step.at(), cj = col[k];
             int64_t d = (int64_t)cj - i;
             if (d < 0) d = -d;
             c[0] += (unsigned long long)d;

@@ -24,14 +24,14 @@ __device__ inline void csr_long_row(int32_t r, const int32_t *__restrict__ rp,
                                     V *lds) {
     const int32_t b = rp[r], e = rp[r + 1];
     V s = V(0);
-    for (int32_t k = b + threadIdx.x; k < e; k += 4 * kLongBlock) {
+    for (entry_steps<4 * kLongBlock> k(b, e, threadIdx.x); k.more(); k.next()) {
         int32_t cc[4];
         V vv[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int32_t kj = k + j * kLongBlock;
-            cc[j] = kj < e ? load_stream(col + kj) : -1;
-            vv[j] = kj < e ? load_stream(val + kj) : V(0);
+            const bool ok = j * kLongBlock < k.left();
+            cc[j] = ok ? load_stream(col + k.at() + j * kLongBlock) : -1;
+            vv[j] = ok ? load_stream(val + k.at() + j * kLongBlock) : V(0);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
