@@ -1035,6 +1035,10 @@ constexpr int64_t kGraphMaxRows = int64_t(1) << 20;
 // body(stop) enqueues an interval; it may end early where stop() says so.
 constexpr auto never_stop = [] { return false; };
 
+// Entries up to which a product that runs in vain, behind the end of a solve,
+// costs less than the device's wait for the host that it saves.
+constexpr int64_t kAheadNnz = 2000000;
+
 class interval_graph {
   public:
     interval_graph(gko_context c, int64_t n)
@@ -3030,7 +3034,12 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
         HIPC(hipMemcpyAsync(S, &h, sizeof(h), hipMemcpyHostToDevice, s));
         c->sync();   // h is reused as the read-back buffer below
         double *V0 = V.as<double>();
-        state_reader reader(c, true);
+        // A cycle may end before its last step; the steps behind its end do
+        // nothing, but their products run.  Where a product is short the
+        // device does not wait while the host looks at the state: the steps of
+        // the next interval are added until it is here.  Otherwise they wait.
+        const bool ahead = compact && c->opts.graphs && A->nnz <= kAheadNnz;
+        state_reader reader(c, ahead);
         for (;;) {
             HIPC(hipMemcpyAsync(V0, b, n * 8, hipMemcpyDeviceToDevice, s));
             spmv_dispatch(A, v, -1.0, x, 1.0, V0);
@@ -3043,21 +3052,12 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
                 spmv_dispatch(A, v, 1.0, V0 + (int64_t)j * ldv, 0.0, V0 + (int64_t)(j + 1) * ldv);
                 HIPC(gmres_arnoldi_step(s, n, m, j, V0, ldv, S, S2, wk));
                 if (compact) std::swap(S, S2);
-                // The cycle may end before its last step, and the steps behind
-                // its end do nothing: the state is looked at once it is here,
-                // the device does not wait for it.
-                if (!reader) {
-                    if ((j + 1) % check_every != 0 || j + 1 >= m) continue;
-                    h = read_back(c, S);
-                } else {
-                    if ((j + 1) % check_every == 0 && j + 1 < m) {
-                        if (reader.waiting()) h = reader.get<gmres_state>();
-                        reader.ask(S);
-                    }
-                    if (!reader.ready()) continue;
-                    h = reader.get<gmres_state>();
+                const bool poll = (j + 1) % check_every == 0 && j + 1 < m;
+                if (reader ? reader.ready() || (poll && reader.waiting()) : poll) {
+                    h = reader ? reader.get<gmres_state>() : read_back(c, S);
+                    if (h.cycle_done) break;
                 }
-                if (h.cycle_done) break;
+                if (reader && poll) reader.ask(S);
             }
             if (reader.waiting()) (void)reader.get<gmres_state>();
             HIPC(gmres_cycle_end(s, n, m, V0, ldv, static_cast<double *>(x), S, wk));

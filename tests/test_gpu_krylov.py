@@ -538,3 +538,60 @@ def test_graphs_option_validated(g, ctx):
         ctx.set_solver_opts(graphs=2)
     assert e.value.status == g.ERR_INVALID_ARG
     assert ctx.solver_opts()["graphs"] == 1
+
+
+# --------------------------------------------------------------------------- what a solve costs behind its end
+def scattered(n, per, dominance):
+    """Rows of about per + 1 entries, -1 in random columns and a diagonal of
+    `dominance` times the others' sum, made on the device."""
+    import torch
+    r = torch.Generator(device="cuda").manual_seed(n + per)
+    i = torch.arange(n, device="cuda")
+    j = torch.randint(0, n, (n, per), generator=r, device="cuda")
+    key = torch.unique(torch.cat([(i[:, None] * n + j).reshape(-1), i * (n + 1)]))
+    row, col = key // n, key % n
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(torch.bincount(row, minlength=n), 0, out=rp[1:])
+    others = (rp[1:] - rp[:-1] - 1).clamp(min=1).double()
+    val = torch.where(row == col, dominance * others[row], torch.full_like(row, -1).double())
+    return rp.int(), col.int(), val
+
+
+def best_of(runs, f):
+    import time
+
+    import torch
+    best = float("inf")
+    for _ in range(runs):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("n,graphs", [(600_001, 1), (600_001, 0), (500_001, 1), (500_001, 0)])
+def test_gmres_products_behind_a_cycles_end(g, ctx, n, graphs):
+    """A cycle of up to 128 steps that ends after a few, on systems whose
+    product (18 million scattered entries) takes much longer than enqueuing a
+    step: the solve takes no more products than the polling interval of 16
+    steps has, as seen from its time (40 products and 4 ms are allowed; all 128
+    would be three times that)."""
+    import torch
+    M = g.Matrix.from_csr(*scattered(n, 30, 4.0))
+    b = torch.rand(n, dtype=torch.float64, device="cuda")
+    x, y = torch.zeros_like(b), torch.empty_like(b)
+    ctx.set_solver_opts(krylov_dim=128, graphs=graphs)
+
+    def products():
+        for _ in range(16):
+            g.spmv(M, 1.0, b, 0.0, y)
+
+    def solve():
+        x.zero_()
+        return g.gmres(M, b, x, tol=1e-3, maxit=500)
+
+    info = solve()
+    assert info["status"] == g.OK and info["iterations"] < 16 and info["true_rel_residual"] <= 1e-3
+    assert best_of(3, solve) <= best_of(3, products) * 40 / 16 + 0.004
