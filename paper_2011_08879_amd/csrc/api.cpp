@@ -1035,10 +1035,6 @@ constexpr int64_t kGraphMaxRows = int64_t(1) << 20;
 // body(stop) enqueues an interval; it may end early where stop() says so.
 constexpr auto never_stop = [] { return false; };
 
-// Entries up to which a product that runs in vain, behind the end of a solve,
-// costs less than the device's wait for the host that it saves.
-constexpr int64_t kAheadNnz = 2000000;
-
 class interval_graph {
   public:
     interval_graph(gko_context c, int64_t n)
@@ -1092,17 +1088,22 @@ class interval_graph {
 };
 
 // Runs intervals of `interval` iterations until the state S says that the
-// solve has ended; returns that state.  With graphs an interval is enqueued
-// while the one before it runs, so the device does not wait for the host
-// (25-35 us a time).  The first two are enqueued launch by launch, the second
-// only as far as the first has not ended the solve; the capture, which takes
-// the host about 100 us, is left for the third, while the second runs.  Where
-// the solve ends in an interval the kernels of the next return at once, at
-// about 2 us each, so larger systems, whose intervals take milliseconds, do
-// without.  CG on 48^3 rows (219 iterations) 3.20 -> 2.96 ms, 32 iterations of
-// BiCGSTAB on 211 x 307 rows 1.06 -> 0.85, 12 of them 0.71 -> 0.47.
+// solve has ended; returns that state.  With graphs the first interval is
+// enqueued launch by launch, and the capture, which takes the host 100-150 us,
+// is made while it runs.
+// ahead: an interval is also enqueued while the one before it runs, so that
+// the device does not wait for the host (25-35 us a time); then the second one
+// is enqueued launch by launch too, only as far as the first is not known to
+// have ended the solve, and the capture is left for the third.  CG on 48^3 rows
+// (219 iterations) 3.20 -> 2.96 ms, 32 iterations of BiCGSTAB on 211 x 307 rows
+// 1.06 -> 0.85, 12 of them 0.71 -> 0.47.  For iterations whose kernels all
+// return at once behind the end of the solve (about 2 us each): where the
+// product does not (spmv_dispatch), an interval that runs in vain costs more
+// than the waits.  Pipelined block-Jacobi CG that ends in 20 iterations on
+// 200,000 scattered rows of 9 entries 1.55 ms ahead, 1.17 with the waits; CG in
+// 27 on 300,000 rows of 31 entries in COO 4.3, 3.2.
 template <typename F>
-krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader &reader,
+krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader &reader, bool ahead,
                              const krylov_scalars *S, int interval, int32_t maxit, F body) {
     krylov_scalars h = read_back(c, S);
     if (!graph.enabled() || !reader) {
@@ -1112,6 +1113,7 @@ krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader 
         }
         return h;
     }
+    const int most = ahead ? 2 : 1;  // intervals under way, and launch by launch
     int enqueued = 0, under_way = 0;
     const auto get = [&] {
         h = reader.template get<krylov_scalars>();
@@ -1121,8 +1123,9 @@ krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader 
         if (under_way > 0 && reader.ready()) get();
         return h.done != kRunning;
     };
+    const auto left = [&] { return h.iter + (int64_t)under_way * interval < maxit; };
     const auto enqueue = [&] {
-        if (enqueued < 2) {
+        if (enqueued < most) {
             body(over);
         } else {
             graph.prepare(body);
@@ -1133,11 +1136,10 @@ krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader 
         if (h.done != kRunning) return;
         reader.ask(S);
         ++under_way;
+        if (!ahead && left()) graph.prepare(body);
     };
     while (h.done == kRunning) {
-        while (!over() && under_way < 2 &&
-               (under_way == 0 || h.iter + (int64_t)under_way * interval < maxit))
-            enqueue();
+        while (!over() && under_way < most && (under_way == 0 || left())) enqueue();
         if (under_way > 0) get();
     }
     while (under_way > 0) {
@@ -1210,7 +1212,8 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
         spmv_dispatch(A, v, -1.0, x, 1.0, w.r);
         HIPC(cg_init(s, v.t, n, b, w.r, zz, w.p, inv, bs, tol, S, w.partials, w.ticket));
         const int interval = mid ? mid_interval(check_every) : check_every;
-        h = run_intervals(c, graph, reader, S, interval, maxit, [&](auto stop) {
+        const bool ahead = mid || fused;
+        h = run_intervals(c, graph, reader, ahead, S, interval, maxit, [&](auto stop) {
             const hipStream_t st = c->stream;
             if (mid) {
                 void *p[2] = {w.p, w.p2};
@@ -1299,7 +1302,8 @@ solve_result pipecg_core(gko_matrix A, const values &v, const void *b, void *x, 
         HIPC(pipe_init(s, v.t, n, b, r.p, pv.u, w.p, pv.m, inv, bs, tol, S, partials.as<double>(),
                        ticket.as<unsigned>()));
         const int interval = mid ? mid_interval(check_every) : check_every;
-        h = run_intervals(c, graph, reader, S, interval, maxit, [&](auto stop) {
+        const bool ahead = mid;
+        h = run_intervals(c, graph, reader, ahead, S, interval, maxit, [&](auto stop) {
             if (mid) {  // w alternates between its buffer and that of n = A m
                 void *wb[2] = {w.p, nn.p};
                 int cur = 0;
@@ -2886,7 +2890,9 @@ gko_status gko_bicgstab_solve(gko_matrix A, const void *b, void *x, double tol, 
         state_reader reader(c, graph.enabled());
         const int check_every = c->opts.check_every;
         const int interval = mid ? mid_interval(check_every) : check_every;
-        const krylov_scalars h = run_intervals(c, graph, reader, S, interval, maxit, [&](auto stop) {
+        const bool ahead = mid || fused;
+        const krylov_scalars h = run_intervals(c, graph, reader, ahead, S, interval, maxit,
+            [&](auto stop) {
             const hipStream_t st = c->stream;
             if (mid) {  // p alternates with s's buffer, v with v2
                 void *pb[2] = {p.p, sv.p}, *vb[2] = {vv.p, v2.p};
@@ -2948,7 +2954,9 @@ gko_status gko_cgs_solve(gko_matrix A, const void *b, void *x, double tol, int32
         state_reader reader(c, graph.enabled());
         const int check_every = c->opts.check_every;
         const int interval = mid ? mid_interval(check_every) : check_every;
-        const krylov_scalars h = run_intervals(c, graph, reader, S, interval, maxit, [&](auto stop) {
+        const bool ahead = mid;
+        const krylov_scalars h = run_intervals(c, graph, reader, ahead, S, interval, maxit,
+            [&](auto stop) {
             const hipStream_t st = c->stream;
             if (mid) {  // p alternates with w's buffer
                 void *pb[2] = {p.p, w.p};
@@ -2979,6 +2987,14 @@ gko_status gko_cgs_solve(gko_matrix A, const void *b, void *x, double tol, int32
         return h.done;
     });
 }
+
+namespace {
+// Entries up to which the products that GMRES runs in vain behind the end of a
+// cycle cost less than the waits for the host: 100,000 scattered rows of 9
+// entries, m = 100, ended by step 10 0.83 ms (0.91 with the waits), by step 48
+// 2.67.
+constexpr int64_t kAheadNnz = 2000000;
+}  // namespace
 
 gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int32_t maxit) {
     return nonsym_solve("gmres", A, b, x, tol, maxit, [&](double bnorm, double *, unsigned *) {

@@ -595,3 +595,45 @@ def test_gmres_products_behind_a_cycles_end(g, ctx, n, graphs):
     info = solve()
     assert info["status"] == g.OK and info["iterations"] < 16 and info["true_rel_residual"] <= 1e-3
     assert best_of(3, solve) <= best_of(3, products) * 40 / 16 + 0.004
+
+
+@pytest.mark.parametrize("solver,fmt,block", [("cg", "coo", 0), ("bicgstab", "hybrid", 0), ("cgs", "csr", 0),
+                                              ("fcg", "csr_merge", 0), ("pipecg", "csr", 4)])
+def test_products_behind_a_solves_end(g, ctx, solver, fmt, block):
+    """A solve that ends in its second polling interval, on a system whose
+    product (18 million scattered entries) does not return at once behind the
+    end: with graphs it takes as many products as without, two intervals, as
+    seen from the times (a quarter is allowed; a third interval would be a
+    half)."""
+    import torch
+    n = 300_001
+    rp, col, val = scattered(n, 30, 1.5)
+    key = torch.repeat_interleave(torch.arange(n, device="cuda"), (rp[1:] - rp[:-1]).long()) * n + col
+    if solver != "bicgstab" and solver != "cgs":              # symmetric: A + A^T
+        both = torch.cat([key, key % n * n + key // n])
+        key, place = torch.unique(both, return_inverse=True)
+        val = torch.zeros(key.numel(), dtype=torch.float64, device="cuda").index_add_(0, place, torch.cat([val, val]))
+        rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        torch.cumsum(torch.bincount(key // n, minlength=n), 0, out=rp[1:])
+        row, col = key // n, (key % n)
+        others = torch.zeros(n, dtype=torch.float64, device="cuda").index_add_(0, row, torch.where(row == col, 0.0, -val))
+        val = torch.where(row == col, 1.5 * others[row], val)
+        rp, col = rp.int(), col.int()
+    M = g.Matrix.from_csr(rp, col, val).convert(fmt)
+    b = torch.rand(n, dtype=torch.float64, device="cuda")
+    x = torch.zeros_like(b)
+    pre = dict(precond=g.PRECOND_BLOCK_JACOBI, block_size=block) if block else {}
+
+    def solve():
+        x.zero_()
+        return getattr(g, solver)(M, b, x, tol=1e-9, maxit=500)
+
+    ctx.set_solver_opts(graphs=0, **pre)
+    k = solve()["iterations"]
+    times = []
+    for graphs in (0, 1):
+        ctx.set_solver_opts(graphs=graphs, check_every=k // 2 + 1, **pre)
+        info = solve()
+        assert info["status"] == g.OK and info["iterations"] == k
+        times.append(best_of(5, solve))
+    assert times[1] <= 1.25 * times[0], (k, times)
