@@ -372,6 +372,14 @@ void spmv_dispatch(gko_matrix A, const values &v, double alpha, const void *x, d
     }
 }
 
+template <typename T>
+T read_back(gko_context c, const T *d) {
+    T h;
+    HIPC(hipMemcpyAsync(&h, d, sizeof(T), hipMemcpyDeviceToHost, c->stream));
+    c->sync();
+    return h;
+}
+
 // ---------------------------------------------------------------- conversions
 slot_layout slots_of(gko_matrix A) {
     return A->fmt == GKO_FMT_SELLP ? slot_layout{A->sset, 0, 0} : slot_layout{nullptr, A->K, A->ld};
@@ -466,43 +474,46 @@ void if_memory_allows(F f) {
     }
 }
 
-// The row patterns of a CSR matrix, found when it is created, from
-// kPatternNnz entries on: smaller products stay in the caches and gained
-// nothing (7-point stencil with 0.76M entries 5.3 us with and without, with
-// 1.8M in FP64 5.2 -> 5.0, 64^3 rows of 27 19.5 -> 14.5).  The search costs two
-// readings of the columns: 27-point stencil 128^3, creation 1.40 -> 1.51 ms.
-constexpr int64_t kPatternNnz = 1000000;
+// Which matrices are searched for row patterns when they are created.  At
+// least kPatternNnz entries, from which on a few dozen products return the
+// search (without and with patterns: 5-point stencil 500^2, 1.2M entries,
+// product 4.2 us either way; 27-point 40^3, 1.6M, creation 81 -> 130 us, CSR 5.8
+// -> 4.7, ELL 8.0 -> 5.4; 7-point 100^3, 6.9M, creation 148 -> 173, CSR 19.4 ->
+// 15.1; 27-point 128^3, 56M, creation 1.38 -> 1.46 ms, CSR 141 -> 104).  Three
+// entries a row: with one or two, the table takes longer than the columns (4M
+// rows of one entry, CSR 28.0 -> 32.7, SELL-P 22.7 -> 30.6 us).
+constexpr int64_t kPatternNnz = 1500000;
+bool may_have_patterns(int64_t n, int64_t nnz) {
+    return n >= 1 && nnz >= kPatternNnz && nnz / n >= 3;
+}
 
-void find_patterns(gko_matrix A) {
+// The row patterns of a CSR matrix from the keys of its rows' lists.
+void make_patterns(gko_matrix A, const pattern_keys &h) {
     const int stride = (int)((A->max_len + 3) / 4 * 4);
-    if (A->n < 1 || A->nnz < kPatternNnz || A->max_len > kPatternInts / 2) return;
+    if (h.too_many || A->max_len > kPatternLongest) return;
     gko_context c = A->ctx;
     hipStream_t s = c->stream;
-    dbuf found(c, sizeof(pattern_keys));
-    HIPC(pattern_collect(s, A->n, A->rp, A->col, found.as<pattern_keys>()));
-    pattern_keys h;
-    HIPC(hipMemcpyAsync(&h, found.p, sizeof(h), hipMemcpyDeviceToHost, s));
-    c->sync();
-    if (h.too_many) return;
     std::vector<std::pair<unsigned long long, unsigned>> lists;
     for (int t = 0; t < kPatternKeys; ++t)
-        if (h.key[t] != 0) lists.emplace_back(h.key[t], h.first[t]);
+        if (h.key[t] != 0) lists.emplace_back(h.key[t], ~h.first[t]);
     const int count = (int)lists.size(), ints = (count + 1) * stride;
     if (count > kPatternMost || ints > kPatternInts) return;
     std::sort(lists.begin(), lists.end());
-    std::vector<unsigned long long> key(count);
-    std::vector<unsigned> first(count);
+    struct {
+        unsigned long long key[kPatternMost];
+        unsigned first[kPatternMost];
+        int wrong;
+    } sorted{};
     for (int p = 0; p < count; ++p) {
-        key[p] = lists[p].first;
-        first[p] = lists[p].second;
+        sorted.key[p] = lists[p].first;
+        sorted.first[p] = lists[p].second;
     }
-    dbuf dkey(c, count * 8), dfirst(c, count * 4), wrong(c, 4), tab(c, ints * 4), id(c, pattern_ids(A->n));
-    HIPC(hipMemcpyAsync(dkey.p, key.data(), count * 8, hipMemcpyHostToDevice, s));
-    HIPC(hipMemcpyAsync(dfirst.p, first.data(), count * 4, hipMemcpyHostToDevice, s));
-    HIPC(hipMemsetAsync(wrong.p, 0, 4, s));
-    HIPC(pattern_assign(s, A->n, A->rp, A->col, count, stride, dkey.as<unsigned long long>(),
-                        dfirst.as<unsigned>(), tab.as<int32_t>(), id.as<uint8_t>(), wrong.as<int>()));
-    if (read_int(c, wrong.as<int>()) != 0) return;
+    dbuf given(c, sizeof(sorted)), tab(c, ints * 4), id(c, pattern_ids(A->n));
+    auto *d = given.as<decltype(sorted)>();
+    HIPC(hipMemcpyAsync(d, &sorted, sizeof(sorted), hipMemcpyHostToDevice, s));
+    HIPC(pattern_assign(s, A->n, A->rp, A->col, count, stride, d->key, d->first, tab.as<int32_t>(),
+                        id.as<uint8_t>(), &d->wrong));
+    if (read_int(c, &d->wrong) != 0) return;
     A->pat_id = static_cast<uint8_t *>(id.release());
     A->pat_tab = static_cast<int32_t *>(tab.release());
     A->pat_stride = stride;
@@ -850,14 +861,6 @@ void ensure_block_jacobi(gko_matrix A, int bs, bool need32) {
 }
 
 // ---------------------------------------------------------------- solver drivers
-template <typename T>
-T read_back(gko_context c, const T *d) {
-    T h;
-    HIPC(hipMemcpyAsync(&h, d, sizeof(T), hipMemcpyDeviceToHost, c->stream));
-    c->sync();
-    return h;
-}
-
 // Copies of a solver's device state that the host looks at later: ask()
 // enqueues one on the context stream, get() waits for the oldest, and what is
 // enqueued in between runs while the host waits.  At most two are under way.
@@ -2186,19 +2189,25 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
         require(nnz == 0 || (col_idx && values), GKO_ERR_INVALID_ARG, "null col_idx or values");
         hipStream_t s = ctx->stream;
         const size_t vb = dt == GKO_F64 ? 8 : 4;
-        dbuf rp(ctx, (n_rows + 1) * 4), col(ctx, nnz * 4), val(ctx, nnz * vb), err(ctx, 4);
-        HIPC(hipMemsetAsync(err.p, 0, 4, s));
+        dbuf rp(ctx, (n_rows + 1) * 4), col(ctx, nnz * 4), val(ctx, nnz * vb);
+        dbuf facts(ctx, sizeof(csr_facts));
+        auto *f = facts.as<csr_facts>();
+        HIPC(hipMemsetAsync(f, 0, sizeof(csr_facts), s));
         if (row_ptr_type == GKO_I64)
             HIPC(narrow_row_ptr(s, n_rows, static_cast<const int64_t *>(row_ptr), rp.as<int32_t>(),
-                                err.as<int>()));
+                                &f->err));
         else
             HIPC(hipMemcpyAsync(rp.p, row_ptr, (n_rows + 1) * 4, hipMemcpyDeviceToDevice, s));
         if (nnz > 0) {
             HIPC(hipMemcpyAsync(col.p, col_idx, nnz * 4, hipMemcpyDeviceToDevice, s));
             HIPC(hipMemcpyAsync(val.p, values, nnz * vb, hipMemcpyDeviceToDevice, s));
         }
-        HIPC(validate_csr(s, n_rows, n_cols, nnz, rp.as<int32_t>(), col.as<int32_t>(), err.as<int>()));
-        const int64_t e = read_int(ctx, err.as<int>());
+        HIPC(validate_csr(s, n_rows, n_cols, nnz, rp.as<int32_t>(), col.as<int32_t>(), &f->err));
+        HIPC(max_row_len(s, n_rows, rp.as<int32_t>(), &f->max_len));
+        if (may_have_patterns(n_rows, nnz))
+            HIPC(pattern_collect(s, n_rows, rp.as<int32_t>(), col.as<int32_t>(), f));
+        const csr_facts h = read_back(ctx, f);
+        const int e = h.err;
         if (e & 1) fail(GKO_ERR_INVALID_ARG, "row_ptr must start at 0, be non-decreasing and end at nnz");
         if (e & 2) fail(GKO_ERR_INVALID_ARG, "column index out of range");
         if (e & 4) fail(GKO_ERR_INVALID_ARG, "column indices must be strictly increasing within a row");
@@ -2213,8 +2222,10 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
         A->col = static_cast<int32_t *>(col.release());
         A->val = val.release();
         try {
+            A->max_len = h.max_len;
             analyse_csr(A);
-            if_memory_allows([&] { find_patterns(A); });
+            if (may_have_patterns(A->n, A->nnz))
+                if_memory_allows([&] { make_patterns(A, h.patterns); });
         } catch (...) {
             A->drop_all();
             delete A;

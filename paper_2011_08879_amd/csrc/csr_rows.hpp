@@ -101,14 +101,20 @@ struct rowthread_lds<V, G, kByPattern> {
 // 107 / 63.
 template <int G, typename F>
 hipError_t with_csr_mode(const row_patterns &p, F launch) {
-    if (!p.id) return launch(std::integral_constant<int, kByColumn>{});
-    if constexpr (G == 1) {
-        if (p.stride <= 8) return launch(std::integral_constant<int, 8>{});
-        if (p.stride <= 12) return launch(std::integral_constant<int, 12>{});
+    // rows of kPatternLongest take one or four lanes (csr_row_lanes)
+    static_assert(kPatternLongest < 56, "no rows with patterns take eight lanes");
+    if constexpr (G == 1 || G == 4) {
+        if (p.id) {
+            if constexpr (G == 1) {
+                if (p.stride <= 8) return launch(std::integral_constant<int, 8>{});
+                if (p.stride <= 12) return launch(std::integral_constant<int, 12>{});
+            } else if (p.stride <= 28) {
+                return launch(std::integral_constant<int, 28>{});
+            }
+            return launch(std::integral_constant<int, kByPattern>{});
+        }
     }
-    if constexpr (G == 4)
-        if (p.stride <= 28) return launch(std::integral_constant<int, 28>{});
-    return launch(std::integral_constant<int, kByPattern>{});
+    return launch(std::integral_constant<int, kByColumn>{});
 }
 
 template <typename V, int G, int M>

@@ -24,6 +24,11 @@ namespace gko {
 constexpr int32_t kPatternPad = INT32_MIN;
 constexpr int kPatternMost = 128;   // lists of a matrix
 constexpr int kPatternInts = 1024;  // the table's size in LDS
+// Rows longer than this have none: lists that long with scattered columns are
+// slower from the table (SELL-P in FP32, rows of 48 that take one of 18 lists
+// at random 31.4 -> 35.6 us, of 64 26.8 -> 31.1), and no stencil has them (27
+// points with two unknowns each: 54 lists of 54).
+constexpr int kPatternLongest = 40;
 constexpr int64_t kPatternRows = 128;
 struct row_patterns {
     const uint8_t *id = nullptr;
@@ -33,15 +38,26 @@ struct row_patterns {
 };
 inline int64_t pattern_ids(int64_t n) { return (n + kPatternRows - 1) / kPatternRows * kPatternRows; }
 
-// The distinct lists' keys, each with the first row that has it.
+// The distinct lists' keys, each with the complement of the first row that has
+// it, so that all zeros is an empty table.
 constexpr int kPatternKeys = 512;
 struct pattern_keys {
     unsigned long long key[kPatternKeys];  // 0: an empty entry
     unsigned first[kPatternKeys];
     int too_many;
 };
+
+// What the creation of a matrix asks the device for, read back at once; zeros
+// on entry.
+struct csr_facts {
+    int err;      // validate_csr, narrow_row_ptr
+    int max_len;  // max_row_len
+    pattern_keys patterns;
+};
+// Collects the lists of a matrix without errors and without rows longer than
+// kPatternLongest (facts from the kernels before).
 hipError_t pattern_collect(hipStream_t s, int64_t n, const int32_t *rp, const int32_t *col,
-                           pattern_keys *out);
+                           csr_facts *facts);
 // key (ascending) and first: count device entries.  Writes tab ((count + 1) *
 // stride ints) and id (pattern_ids(n) bytes), and sets *wrong (zero on entry)
 // where a row differs from its list.

@@ -58,10 +58,11 @@ __device__ inline void each_entry(int64_t n, int64_t r0, const int32_t *__restri
     }
 }
 
-// Enters key h of row i into a table of N entries; false when there is no room.
+// Enters key h with the complement of its row into a table of N entries (the
+// largest complement stays); false when there is no room.
 template <int N>
 __device__ inline bool enter(unsigned long long *keys, unsigned *first, unsigned long long h,
-                             unsigned row, bool &added) {
+                             unsigned inv_row, bool &added) {
     added = false;
     for (int q = 0, t = (int)(h >> 40) % N; q < N; ++q, t = (t + 1) % N) {
         unsigned long long k = keys[t];
@@ -70,7 +71,7 @@ __device__ inline bool enter(unsigned long long *keys, unsigned *first, unsigned
             added = k == 0;
         }
         if (k == 0 || k == h) {
-            atomicMin(first + t, row);
+            atomicMax(first + t, inv_row);
             return true;
         }
     }
@@ -82,14 +83,16 @@ __device__ inline bool enter(unsigned long long *keys, unsigned *first, unsigned
 // share.  Matrices without patterns end after the first rows.
 __global__ __launch_bounds__(kPB) void pattern_keys_kernel(int64_t n, const int32_t *__restrict__ rp,
                                                            const int32_t *__restrict__ col,
-                                                           pattern_keys *out) {
+                                                           csr_facts *facts) {
     __shared__ unsigned long long keys[kLocalKeys];
     __shared__ unsigned first[kLocalKeys];
     __shared__ int count;
     __shared__ int32_t C[kColChunk];
+    pattern_keys *out = &facts->patterns;
+    if (facts->err != 0 || facts->max_len > kPatternLongest) return;
     for (int t = threadIdx.x; t < kLocalKeys; t += kPB) {
         keys[t] = 0;
-        first[t] = 0xffffffffu;
+        first[t] = 0;
     }
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(kPB) void pattern_keys_kernel(int64_t n, const int3
         each_entry(n, base, rp, col, C, b, e, [&](int32_t, int32_t c) { key.add(c - (int32_t)i); });
         if (i < n) {
             bool added;
-            if (!enter<kLocalKeys>(keys, first, key.get(), (unsigned)i, added) || added)
+            if (!enter<kLocalKeys>(keys, first, key.get(), ~(unsigned)i, added) || added)
                 atomicAdd(&count, 1);
         }
         __syncthreads();
@@ -172,12 +175,9 @@ __global__ __launch_bounds__(kPB) void pattern_ids_kernel(int64_t n, int64_t n_i
 }  // namespace
 
 hipError_t pattern_collect(hipStream_t s, int64_t n, const int32_t *rp, const int32_t *col,
-                           pattern_keys *out) {
-    hipError_t e = hipMemsetAsync(out, 0, sizeof(pattern_keys), s);
-    if (e == hipSuccess) e = hipMemsetAsync(out->first, 0xff, sizeof(out->first), s);
-    if (e != hipSuccess) return e;
+                           csr_facts *facts) {
     const int64_t g = (n + kPB - 1) / kPB;
-    pattern_keys_kernel<<<(unsigned)(g < 1024 ? g : 1024), kPB, 0, s>>>(n, rp, col, out);
+    pattern_keys_kernel<<<(unsigned)(g < 1024 ? g : 1024), kPB, 0, s>>>(n, rp, col, facts);
     return hipGetLastError();
 }
 

@@ -41,7 +41,8 @@ __global__ __launch_bounds__(kSellpBlock) void spmv_sellp_kernel(int64_t n,
         if (i < n) row.load(i, sets, sval, pat);
         stage.store(L);
         __syncthreads();
-        if (i >= n || row.w > kSellpWide) return;
+        static_assert(kPatternLongest <= kSellpWide, "no wide slices with patterns");
+        if (i >= n) return;
         s0 = row.sum(i, x, pat, L);
     } else {
         if (i >= n) return;

@@ -511,3 +511,134 @@ def test_sellp_wide_slices(g, orc, gen_mod, f32):
         info = g.cg(A, dev(b), xg, tol=1e-10)
         assert info["status"] == g.OK and abs(info["iterations"] - info_o["iters"]) <= 2
         assert np.linalg.norm(b - orc.spmv((rp, col, val), host(xg))) <= 1e-10 * np.linalg.norm(b)
+
+
+def _counting_context(g):
+    """A context whose allocator notes the size of every buffer the library holds."""
+    import torch
+    ctx, sizes, device = g.Context(use_torch_allocator=False), {}, torch.cuda.current_device()
+
+    def alloc(nbytes, stream, user):
+        p = torch.cuda.caching_allocator_alloc(int(nbytes), device, stream or 0)
+        sizes[p] = nbytes
+        return p
+
+    def dealloc(p, stream, user):
+        del sizes[p]
+        torch.cuda.caching_allocator_delete(p)
+
+    ctx._cbs = (g.ALLOC_FN(alloc), g.DEALLOC_FN(dealloc))
+    assert g._lib.gko_context_set_allocator(ctx.handle, ctx._cbs[0], ctx._cbs[1], None) == g.OK
+    return ctx, sizes
+
+
+@pytest.mark.parametrize("n,length,scattered,kept", [
+    (299_999, 5, False, False),      # 1.5 million entries, from which on a matrix is searched for row patterns
+    (300_001, 5, False, True),
+    (700_001, 3, False, True),       # three entries a row
+    (1_200_001, 2, False, False),    # two
+    (60_001, 40, False, True),       # the longest rows with patterns
+    (60_001, 41, False, False),
+    (60_001, 30, True, False)])
+def test_which_matrices_keep_row_patterns(g, n, length, scattered, kept):
+    """A matrix whose rows are one list of column offsets keeps its patterns (a
+    byte per row and the table) only where products gain from them; one of
+    scattered columns has none."""
+    import torch
+    i = torch.arange(n, device="cuda")[:, None]
+    j = torch.arange(length, device="cuda")
+    m = 2 * n + length
+    col = torch.sort(torch.randint(0, n // length, (n, length), device="cuda") * length, 1).values + j if scattered else i + j
+    rp = torch.arange(n + 1, device="cuda", dtype=torch.int32) * length
+    val = torch.ones(n * length, dtype=torch.float64, device="cuda")
+    ctx, sizes = _counting_context(g)
+    M = g.Matrix.from_csr(rp, col.reshape(-1).int(), val, n_cols=m, ctx=ctx)
+    extra = sum(sizes.values()) - 4 * (n + 1) - 12 * n * length
+    assert (extra >= n) if kept else extra == 0, extra
+    M.close()
+    assert not sizes
+
+
+def test_creation_without_gain_from_patterns_is_not_searched(g):
+    """Creating the 5-point matrix of 500 x 500, whose products gain nothing
+    from row patterns, takes about as long as any matrix of its size."""
+    import statistics
+    import time
+
+    import torch
+    n = 250_000
+    i = torch.arange(n, device="cuda")
+    star = i[:, None] + torch.tensor([-500, -1, 0, 1, 500], device="cuda")
+    other = torch.sort(torch.randint(0, n // 8, (n, 5), device="cuda") * 5, 1).values + torch.arange(5, device="cuda")
+    ctx = g.Context()
+
+    def seconds(col):
+        ok = (col >= 0) & (col < n)
+        rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        torch.cumsum(ok.sum(1), 0, out=rp[1:])
+        rp, col = rp.int(), col[ok].int()
+        val = torch.ones(col.numel(), dtype=torch.float64, device="cuda")
+        times = []
+        for _ in range(40):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            M = g.Matrix.from_csr(rp, col, val, ctx=ctx)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+            M.close()
+        return statistics.median(times)
+
+    seconds(star)
+    a, b = seconds(star), seconds(other)
+    assert a <= 1.4 * b, (a, b)
+
+
+def _uneven_rows(lists, length, n):
+    """As _pattern_rows, with lists from one entry to `length`, most of them short."""
+    rng = np.random.default_rng(lists)
+    spread = 2 * length + 40
+    sizes = np.maximum(1, (length * rng.uniform(0, 1, lists) ** 2).astype(int))
+    sizes[0], sizes[1] = length, 1
+    pat = rng.integers(0, lists, n)
+    pat[:lists] = np.arange(lists)
+    padded = np.zeros((lists, length), np.int64)
+    for k, l in enumerate(sizes):
+        padded[k, :l] = np.sort(rng.choice(np.arange(-spread, spread), size=l, replace=False))
+    lens = sizes[pat]
+    inside = np.arange(length)[None, :] < lens[:, None]
+    col = ((np.arange(n) + spread)[:, None] + padded[pat])[inside]
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    return n, n + 2 * spread, rp.astype(np.int32), col.astype(np.int32)
+
+
+@pytest.mark.parametrize("name", ["1x5x400001", "27x7x350063", "3x9x300064", "30x13x150001", "35x28x90001",
+                                  "27x27x90001odd", "126x6x400000odd", "127x6x400000odd", "128x4x700001",
+                                  "22x40x60001", "8x12x400001u", "30x13x400001u", "20x40x160001u", "24x32x200064u"])
+def test_repeated_rows_above_the_search_limit(g, name):
+    """As test_repeated_rows, with at least 1.5 million entries, and ("u") with
+    rows of very different lengths, which end at different slots."""
+    uneven = name.endswith("u")
+    if uneven:
+        n, m, rp, col = _uneven_rows(*(int(v) for v in name[:-1].split("x")))
+    else:
+        n, m, rp, col = _pattern_rows(name)
+    assert len(col) >= 1_500_000
+    rng = np.random.default_rng(6)
+    val, lens = rng.uniform(-1, 1, len(col)), np.diff(rp)
+    x, y0 = rng.uniform(-1, 1, m), rng.uniform(-1, 1, n)
+    for f32 in (False, True):
+        t = np.float32 if f32 else np.float64
+        A = make(g, (n, m, rp, col, val.astype(t)), f32)
+        xs, ys, vs = (v.astype(t).astype(np.float64) for v in (x, y0, val))
+        terms = np.append(vs * xs[col], 0.0).astype(np.longdouble)
+        want, size = (np.where(lens > 0, np.add.reduceat(v, rp[:-1]), 0.0) for v in (terms, np.abs(terms)))
+        want, size = (1.5 * want + 0.5 * ys).astype(np.float64), (1.5 * size + 0.5 * np.abs(ys)).astype(np.float64)
+        for fmt in ("csr", "ell", "sellp", "hybrid"):
+            if uneven and fmt == "ell" and ell_infeasible((n, m, rp, col, val.astype(t)), 4 if f32 else 8):
+                continue
+            C = A.clone().convert(fmt)
+            y = dev(y0.astype(t))
+            g.spmv(C, 1.5, dev(x.astype(t)), 0.5, y)
+            assert_spmv_close(host(y), want, size, lens, f32, "%s %s" % (name, fmt))
+            C.close()
+        A.close()
