@@ -175,6 +175,7 @@ struct ell_pattern_pair<float> {
                     const float t = s[h] + v[h][u] * xs[h][u];
                     s[h] = c[h][u] >= 0 ? t : s[h];
                 }
+            if (__all(c[0][B - 1] < 0 && c[1][B - 1] < 0)) break;  // all rows' padding has begun
         }
         // lane l's pair is rows 2l and 2l + 1 of the 128
         const int lane = threadIdx.x % kWave, from = 2 * lane % kWave;

@@ -642,3 +642,43 @@ def test_repeated_rows_above_the_search_limit(g, name):
             assert_spmv_close(host(y), want, size, lens, f32, "%s %s" % (name, fmt))
             C.close()
         A.close()
+
+
+def _seconds(f, reps=20):
+    import torch
+    for _ in range(3):
+        f()
+    best = float("inf")
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / reps * 1e-3)
+    return best
+
+
+def test_ell_rows_end_at_their_padding(g):
+    """ELL with row patterns, 28 slots a row for rows of 7 entries (one of 4096
+    has 28): the FP32 product, too, stops where a wavefront's rows have ended,
+    as seen from its time, which is below the FP64 product's (reading all
+    slots, it took 1.2 times as long)."""
+    import torch
+    n = 2_000_003
+    i = torch.arange(n, device="cuda")
+    lens = torch.where(i % 4096 == 0, 28, 7)
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=rp[1:])
+    row = torch.repeat_interleave(i, lens)
+    col = (row + torch.arange(row.numel(), device="cuda") - rp[row]).int()
+    times = []
+    for dt in (torch.float32, torch.float64):
+        A = g.Matrix.from_csr(rp.int(), col, torch.ones(col.numel(), dtype=dt, device="cuda"), n_cols=n + 28)
+        A.convert("ell")
+        x, y = torch.ones(n + 28, dtype=dt, device="cuda"), torch.empty(n, dtype=dt, device="cuda")
+        times.append(_seconds(lambda: g.spmv(A, 1.0, x, 0.0, y)))
+        assert torch.equal(y, lens.to(dt))
+        A.close()
+    assert times[0] <= 0.9 * times[1], times
