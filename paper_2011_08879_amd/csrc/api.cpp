@@ -211,7 +211,9 @@ struct gko_matrix_s {
     int64_t slices() const { return (n + kSellpSlice - 1) / kSellpSlice; }
     // elements of ecol / eval
     int64_t ell_elems() const { return fmt == GKO_FMT_SELLP ? slots : K * ld; }
-    row_patterns patterns() const { return {pat_id, pat_tab, pat_stride, pat_ints}; }
+    row_patterns patterns() const {
+        return {pat_id, pat_tab, pat_stride, pat_ints, (int)((nnz + n / 2) / std::max<int64_t>(n, 1))};
+    }
     sellp_wide wide() const {
         sellp_wide w;
         w.n_wide = n_wide;

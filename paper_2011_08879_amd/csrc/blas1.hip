@@ -575,7 +575,7 @@ static hipError_t launch_fused(hipStream_t s, const fused_matrix &A, const void 
         const red_args ra = red_for(g, partials, ticket);
         const auto launch = [&](auto lanes) {
             constexpr int G = decltype(lanes)::value;
-            (void)with_csr_mode<G>(A.pat, [&](auto m) {
+            (void)with_csr_mode<V, G>(A.pat, [&](auto m) {
                 fused_csr_rowthread_kernel<V, P, G, decltype(m)::value><<<g, kB, 0, s>>>(
                     A.n, A.rp, A.col, static_cast<const V *>(A.val), A.pat, in, out, pol, ra);
                 return hipSuccess;

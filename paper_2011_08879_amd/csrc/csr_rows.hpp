@@ -98,13 +98,17 @@ struct rowthread_lds<V, G, kByPattern> {
 // The kernel for G lanes per row.  Measured (FP64 / FP32, us; column indices,
 // patterns in chunks, csr_rowwave_sum): 7-point stencil 160^3 (1 lane) 78 /
 // 52, 60 / 40, 56 / 33; 27-point stencil 128^3 (4 lanes) 143 / 96, 127 / 88,
-// 107 / 63.
-template <int G, typename F>
+// 107 / 63.  FP32 rows of 12 and of 16 entries, four lanes a row, keep the column
+// indices: sixteen such rows meet in a few LDS banks, which costs more without
+// the columns' loads beside it (column indices, patterns: rows of 16 37 / 42,
+// blocks of 16 40 / 46, rows of 12 with one of 1,000 of 40 47 / 57; but rows of
+// 13, 14 and 15 47 / 45, 44 / 42 and 44 / 40, FP64 rows of 16 61 / 57).
+template <typename V, int G, typename F>
 hipError_t with_csr_mode(const row_patterns &p, F launch) {
     // rows of kPatternLongest take one or four lanes (csr_row_lanes)
     static_assert(kPatternLongest < 56, "no rows with patterns take eight lanes");
     if constexpr (G == 1 || G == 4) {
-        if (p.id) {
+        if (p.id && !(G == 4 && sizeof(V) == 4 && (p.mean == 12 || p.mean == 16))) {
             if constexpr (G == 1) {
                 if (p.stride <= 8) return launch(std::integral_constant<int, 8>{});
                 if (p.stride <= 12) return launch(std::integral_constant<int, 12>{});

@@ -35,6 +35,7 @@ struct row_patterns {
     const int32_t *tab = nullptr;
     int stride = 0;  // a multiple of 4, at least the longest row
     int ints = 0;    // of the table
+    int mean = 0;    // entries of a row, rounded
 };
 inline int64_t pattern_ids(int64_t n) { return (n + kPatternRows - 1) / kPatternRows * kPatternRows; }
 

@@ -107,7 +107,7 @@ static hipError_t launch_csr_rowthread_g(hipStream_t s, int64_t n, const int32_t
                                          const row_patterns &pat, const void *x, double alpha,
                                          double beta, void *y) {
     constexpr int64_t rows = kRowThreadBlock / G;
-    return with_csr_mode<G>(pat, [&](auto m) {
+    return with_csr_mode<V, G>(pat, [&](auto m) {
         spmv_csr_rowthread_kernel<V, G, decltype(m)::value>
             <<<dim3((unsigned)((n + rows - 1) / rows)), dim3(kRowThreadBlock), 0, s>>>(
                 n, rp, col, static_cast<const V *>(val), pat, static_cast<const V *>(x), (V)alpha,
