@@ -384,7 +384,8 @@ T read_back(gko_context c, const T *d) {
 
 // ---------------------------------------------------------------- conversions
 slot_layout slots_of(gko_matrix A) {
-    return A->fmt == GKO_FMT_SELLP ? slot_layout{A->sset, 0, 0} : slot_layout{nullptr, A->K, A->ld};
+    return A->fmt == GKO_FMT_SELLP ? slot_layout{A->sset, A->max_len, 0}
+                                   : slot_layout{nullptr, A->K, A->ld};
 }
 
 // Writes the logical matrix as CSR (n+1 offsets, nnz columns, nnz values of
@@ -694,7 +695,7 @@ void csr_to_format(gko_matrix A, gko_format fmt, const sellp_layout *known) {
             dbuf scol(c, L.sets[ns] * 4), sval(c, L.sets[ns] * A->vs());
             HIPC(hipMemcpyAsync(sets.p, L.sets.data(), (ns + 1) * 8, hipMemcpyHostToDevice, s));
             HIPC(hipMemcpyAsync(widths.p, L.widths.data(), ns * 4, hipMemcpyHostToDevice, s));
-            HIPC(csr_to_slots(s, A->type(), A->n, A->rp, A->col, A->val, {sets.as<int64_t>(), 0, 0},
+            HIPC(csr_to_slots(s, A->type(), A->n, A->rp, A->col, A->val, {sets.as<int64_t>(), A->max_len, 0},
                               scol.as<int32_t>(), sval.p));
             // wide slices: (slice, first column) work items of kSellpWideChunk columns
             std::vector<int32_t> wsl, wfirst, witems;

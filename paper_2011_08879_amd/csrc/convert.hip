@@ -296,9 +296,19 @@ hipError_t gather_probe(hipStream_t s, int64_t n, const double *x, int64_t m, co
 // or written in its own order, the slot side by wavefronts with a lane per
 // row, so both sides are coalesced (a thread per row walking its CSR entries:
 // 500,000 rows of 16 entries CSR -> ELL 132 us, ELL -> CSR 255 us).
+// A chunk holds few rows of a tile with long ones, and most lanes of a
+// wavefront then have none: tiles of more than kSlotWide slots per row are
+// converted in blocks of 64 rows and kSlotCols slots instead, by as many
+// workgroups as the grid has for a tile.  16M entries, CSR -> ELL / ELL -> CSR
+// with the library's host work, chunks and blocks: rows of 65 94 / 147 and 106 /
+// 114 us (a third block with one slot), of 80 94 / 167 and 89 / 93, of 256 135 /
+// 320 and 77 / 92, of 3,000 4,840 / 21,900 and 98 / 95; a million lognormal rows
+// sorted by length in SELL-P 5,520 / 23,800 and 329 / 301.
 constexpr int kSlotRows = kWave;
 constexpr int kSlotThreads = 256;
 constexpr int kSlotChunk = 2048;
+constexpr int64_t kSlotWide = 72;
+constexpr int kSlotCols = 32;
 
 static_assert(kSlotRows == kSellpSlice, "a SELL-P slice is a tile");
 
@@ -350,6 +360,7 @@ __global__ __launch_bounds__(kSlotThreads) void csr_to_slots_kernel(
     __shared__ slot_lds<V> L;
     const int64_t r0 = (int64_t)blockIdx.x * kSlotRows;
     const slot_tile T = slot_tile_of(S, blockIdx.x);
+    if (T.width > kSlotWide) return;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     constexpr int NW = kSlotThreads / kWave, E = kSlotChunk / kSlotThreads;
     const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
@@ -405,6 +416,7 @@ __global__ __launch_bounds__(kSlotThreads) void slots_to_csr_kernel(
     __shared__ slot_lds<V> L;
     const int64_t r0 = (int64_t)blockIdx.x * kSlotRows;
     const slot_tile T = slot_tile_of(S, blockIdx.x);
+    if (T.width > kSlotWide) return;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     constexpr int NW = kSlotThreads / kWave, E = kSlotChunk / kSlotThreads;
     const int64_t i = r0 + lane, last = r0 + kSlotRows < n ? r0 + kSlotRows : n;
@@ -438,6 +450,108 @@ __global__ __launch_bounds__(kSlotThreads) void slots_to_csr_kernel(
     }
 }
 
+// A block of a wide tile in LDS; b and len: the rows' first entry and slots.
+template <typename V>
+struct slot_block {
+    int32_t col[kSlotRows][kSlotCols + 1];
+    V val[kSlotRows][kSlotCols + 1];
+    int32_t b[kSlotRows], len[kSlotRows];
+    __device__ void load_rows(int64_t n, int64_t r0, int64_t width, const int32_t *__restrict__ rp) {
+        if (threadIdx.x < kSlotRows) {
+            const int64_t i = r0 + threadIdx.x;
+            const int32_t first = rp[i < n ? i : n], l = rp[i + 1 < n ? i + 1 : n] - first;
+            b[threadIdx.x] = first;
+            len[threadIdx.x] = l < width ? l : (int32_t)width;
+        }
+        __syncthreads();
+    }
+};
+
+template <typename V>
+__global__ __launch_bounds__(kSlotThreads) void csr_to_wide_slots_kernel(
+    int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ val, slot_layout S, int32_t *__restrict__ scol, V *__restrict__ sval) {
+    __shared__ slot_block<V> L;
+    const slot_tile T = slot_tile_of(S, blockIdx.x);
+    if (T.width <= kSlotWide) return;
+    constexpr int NR = kSlotThreads / kSlotCols, U = kSlotRows / NR, NW = kSlotThreads / kWave;
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    const int r = threadIdx.x / kSlotCols, q = threadIdx.x % kSlotCols;
+    L.load_rows(n, (int64_t)blockIdx.x * kSlotRows, T.width, rp);
+    for (int64_t j0 = (int64_t)blockIdx.y * kSlotCols; j0 < T.width; j0 += (int64_t)gridDim.y * kSlotCols) {
+        int32_t cc[U];
+        V vv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // padding where a row has ended
+            const int row = r + u * NR;
+            const bool ok = j0 + q < L.len[row];
+            cc[u] = ok ? load_stream(col + L.b[row] + j0 + q) : -1;
+            vv[u] = ok ? load_stream(val + L.b[row] + j0 + q) : V(0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            L.col[r + u * NR][q] = cc[u];
+            L.val[r + u * NR][q] = vv[u];
+        }
+        __syncthreads();
+        for (int k = wv; k < kSlotCols && j0 + k < T.width; k += NW) {
+            const int64_t slot = T.start + (j0 + k) * T.stride + lane;
+            scol[slot] = L.col[lane][k];
+            sval[slot] = L.val[lane][k];
+        }
+        __syncthreads();
+    }
+}
+
+template <typename V>
+__global__ __launch_bounds__(kSlotThreads) void wide_slots_to_csr_kernel(
+    int64_t n, slot_layout S, const int32_t *__restrict__ scol, const V *__restrict__ sval,
+    const int32_t *__restrict__ rp, int32_t *__restrict__ col, V *__restrict__ val) {
+    __shared__ slot_block<V> L;
+    const slot_tile T = slot_tile_of(S, blockIdx.x);
+    if (T.width <= kSlotWide) return;
+    constexpr int NR = kSlotThreads / kSlotCols, U = kSlotRows / NR, NW = kSlotThreads / kWave;
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    const int r = threadIdx.x / kSlotCols, q = threadIdx.x % kSlotCols;
+    L.load_rows(n, (int64_t)blockIdx.x * kSlotRows, T.width, rp);
+    int32_t longest = L.len[lane];
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) longest = max(longest, __shfl_xor(longest, s));
+    for (int64_t j0 = (int64_t)blockIdx.y * kSlotCols; j0 < longest; j0 += (int64_t)gridDim.y * kSlotCols) {
+        int32_t cc[kSlotCols / NW];
+        V vv[kSlotCols / NW];
+#pragma unroll
+        for (int u = 0; u < kSlotCols / NW; ++u) {
+            const int64_t j = j0 + wv + u * NW, slot = T.start + j * T.stride + lane;
+            const bool ok = j < L.len[lane];
+            cc[u] = ok ? load_stream(scol + slot) : 0;
+            vv[u] = ok ? load_stream(sval + slot) : V(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kSlotCols / NW; ++u) {
+            L.col[lane][wv + u * NW] = cc[u];
+            L.val[lane][wv + u * NW] = vv[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = r + u * NR;
+            if (j0 + q < L.len[row]) {
+                col[L.b[row] + j0 + q] = L.col[row][q];
+                val[L.b[row] + j0 + q] = L.val[row][q];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The grid of the wide tiles' kernels: up to 65,536 workgroups over the tiles,
+// those of the others end at once.  S.K: the widest tile.
+static dim3 wide_grid(unsigned tiles, const slot_layout &S) {
+    const int64_t blocks = (S.K + kSlotCols - 1) / kSlotCols, y = 65536 / (int64_t)tiles;
+    return dim3(tiles, (unsigned)(y < 1 ? 1 : y < blocks ? y : blocks));
+}
+
 // A row's entries are its slots up to the first padding slot, found by
 // bisection (reading every slot of 500,000 rows of 34: 24 us).
 __global__ void slot_len_kernel(int64_t n, slot_layout S, const int32_t *__restrict__ scol,
@@ -455,17 +569,26 @@ __global__ void slot_len_kernel(int64_t n, slot_layout S, const int32_t *__restr
     len[i] = (int32_t)lo + (tail_ptr ? tail_ptr[i + 1] - tail_ptr[i] : 0);
 }
 
+template <typename V>
+static hipError_t launch_csr_to_slots(hipStream_t s, int64_t n, const int32_t *rp, const int32_t *col,
+                                      const void *val_, const slot_layout &S, int32_t *scol,
+                                      void *sval_) {
+    const unsigned tiles = grid_for(n, kSlotRows);
+    const V *val = static_cast<const V *>(val_);
+    V *sval = static_cast<V *>(sval_);
+    if (S.sets || S.K <= kSlotWide)
+        csr_to_slots_kernel<V><<<tiles, kSlotThreads, 0, s>>>(n, rp, col, val, S, scol, sval);
+    if (S.K > kSlotWide)
+        csr_to_wide_slots_kernel<V>
+            <<<wide_grid(tiles, S), kSlotThreads, 0, s>>>(n, rp, col, val, S, scol, sval);
+    return hipGetLastError();
+}
+
 hipError_t csr_to_slots(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int32_t *col,
                         const void *val, const slot_layout &S, int32_t *scol, void *sval) {
-    const unsigned tiles = grid_for(n, kSlotRows);
-    if (tiles == 0 || (!S.sets && S.K == 0)) return hipSuccess;
-    if (t == vt::f64)
-        csr_to_slots_kernel<double><<<tiles, kSlotThreads, 0, s>>>(
-            n, rp, col, static_cast<const double *>(val), S, scol, static_cast<double *>(sval));
-    else
-        csr_to_slots_kernel<float><<<tiles, kSlotThreads, 0, s>>>(
-            n, rp, col, static_cast<const float *>(val), S, scol, static_cast<float *>(sval));
-    return hipGetLastError();
+    if (n == 0 || S.K == 0) return hipSuccess;
+    return t == vt::f64 ? launch_csr_to_slots<double>(s, n, rp, col, val, S, scol, sval)
+                        : launch_csr_to_slots<float>(s, n, rp, col, val, S, scol, sval);
 }
 
 hipError_t slot_lengths(hipStream_t s, int64_t n, const slot_layout &S, const int32_t *scol,
@@ -480,18 +603,23 @@ static hipError_t launch_slots_to_csr(hipStream_t s, int64_t n, const slot_layou
                                       const int32_t *scol, const void *sval, bool tail,
                                       const int32_t *rp, int32_t *col, void *val) {
     const unsigned tiles = grid_for(n, kSlotRows);
-    if (tail)
-        slots_to_csr_kernel<V, true><<<tiles, kSlotThreads, 0, s>>>(
-            n, S, scol, static_cast<const V *>(sval), rp, col, static_cast<V *>(val));
-    else
-        slots_to_csr_kernel<V, false><<<tiles, kSlotThreads, 0, s>>>(
-            n, S, scol, static_cast<const V *>(sval), rp, col, static_cast<V *>(val));
+    const V *from = static_cast<const V *>(sval);
+    V *to = static_cast<V *>(val);
+    if (S.sets || S.K <= kSlotWide) {
+        if (tail)
+            slots_to_csr_kernel<V, true><<<tiles, kSlotThreads, 0, s>>>(n, S, scol, from, rp, col, to);
+        else
+            slots_to_csr_kernel<V, false><<<tiles, kSlotThreads, 0, s>>>(n, S, scol, from, rp, col, to);
+    }
+    if (S.K > kSlotWide)
+        wide_slots_to_csr_kernel<V>
+            <<<wide_grid(tiles, S), kSlotThreads, 0, s>>>(n, S, scol, from, rp, col, to);
     return hipGetLastError();
 }
 
 hipError_t slots_to_csr(hipStream_t s, vt t, int64_t n, const slot_layout &S, const int32_t *scol,
                         const void *sval, bool tail, const int32_t *rp, int32_t *col, void *val) {
-    if (n == 0) return hipSuccess;
+    if (n == 0 || S.K == 0) return hipSuccess;
     return t == vt::f64 ? launch_slots_to_csr<double>(s, n, S, scol, sval, tail, rp, col, val)
                         : launch_slots_to_csr<float>(s, n, S, scol, sval, tail, rp, col, val);
 }

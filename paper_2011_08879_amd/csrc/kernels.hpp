@@ -175,7 +175,7 @@ hipError_t gather_probe(hipStream_t s, int64_t n, const double *x, int64_t m, co
 hipError_t stream_op(hipStream_t s, int op, int64_t n, const double *a, const double *b, double sc,
                      double *c);
 // Column-major slots: ELL (K slots of leading dimension ld, sets null) or
-// SELL-P (slice k at sets[k], its width from the next offset).
+// SELL-P (slice k at sets[k], its width from the next offset; K: the widest).
 struct slot_layout {
     const int64_t *sets;
     int64_t K, ld;

@@ -705,3 +705,68 @@ def test_fp32_rows_that_share_lds_banks(g, length):
         assert bool((y == length).all())
         A.close()
     assert times[0] <= 1.03 * times[1], times
+
+
+@pytest.mark.parametrize("name", ["even64x72", "even64x73", "even63x95", "even65x96", "even130x97", "even3x2500",
+                                  "even200x129", "even1x9000"])
+@pytest.mark.parametrize("f32", [False, True])
+def test_conversions_of_wide_tiles(g, orc, name, f32):
+    """Rows on both sides of 72 slots, from which on a tile is converted in
+    blocks of 64 rows and 32 slots, at the blocks' edges."""
+    test_conversions_at_tile_and_chunk_edges(g, orc, name, f32)
+
+
+@pytest.mark.parametrize("n,longest", [(64, 200), (333, 300), (2000, 120), (129, 3000)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_conversions_of_uneven_wide_tiles(g, orc, n, longest, f32):
+    """Rows of any length up to `longest`, the longest first: wide tiles beside
+    narrow ones in SELL-P, tails behind wide tiles in HYB."""
+    rng = np.random.default_rng(n)
+    lens = np.sort((longest * rng.uniform(0, 1, n) ** 1.5).astype(int))[::-1]
+    lens[0] = longest
+    m = longest + 500
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    col = np.concatenate([np.sort(rng.choice(m, size=l, replace=False)) for l in lens]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(col)).astype(np.float32 if f32 else np.float64)
+    A = make(g, (n, m, rp, col, vals.astype(np.float64)), f32)
+    Ah = (rp, col, vals.astype(np.float64))
+    s = A.convert("sellp").export_sellp()
+    w, sets, sc, sv = orc.csr_to_sellp(Ah)
+    assert np.array_equal(host(s["widths"]), w) and np.array_equal(host(s["sets"]), sets)
+    assert np.array_equal(host(s["col"]), sc) and np.array_equal(bits(host(s["val"])), bits(sv.astype(vals.dtype)))
+    s = A.convert("hybrid").export_storage()
+    K, ld, ec, ev, tr, tc, tv = orc.csr_to_hyb(Ah, value_bytes=4 if f32 else 8)
+    for key, want in (("ell_col", ec), ("coo_row", tr), ("coo_col", tc)):
+        assert np.array_equal(host(s[key]), want), key
+    for key, want in (("ell_val", ev), ("coo_val", tv)):
+        assert np.array_equal(bits(host(s[key])), bits(want.astype(vals.dtype))), key
+    s = A.convert("ell").export_storage()
+    assert np.array_equal(host(s["ell_col"]), orc.csr_to_ell(Ah)[2])
+    for fmt in ("ell", "sellp", "hybrid"):
+        erp, ecol, evl = (host(t) for t in A.convert(fmt).convert("csr").export_csr())
+        assert np.array_equal(erp, rp) and np.array_equal(ecol, col) and np.array_equal(bits(evl), bits(vals)), fmt
+
+
+def test_conversion_time_does_not_grow_with_the_rows(g):
+    """16 million entries take about as long to and from ELL in rows of 3,000 as
+    in rows of 32 (they took 60 and 230 times as long)."""
+    import time
+
+    import torch
+    best = {}
+    for length in (32, 3000):
+        n = 16_000_000 // length
+        rp = torch.arange(n + 1, device="cuda", dtype=torch.int32) * length
+        col = (torch.arange(n, device="cuda")[:, None] + torch.arange(length, device="cuda")).int().reshape(-1)
+        A = g.Matrix.from_csr(rp, col, torch.ones(n * length, dtype=torch.float64, device="cuda"), n_cols=n + length)
+        best[length] = [float("inf")] * 2
+        for _ in range(5):
+            for k, fmt in enumerate(("ell", "csr")):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                A.convert(fmt)
+                torch.cuda.synchronize()
+                best[length][k] = min(best[length][k], time.perf_counter() - t)
+        A.close()
+    assert all(b <= 3 * a for a, b in zip(best[32], best[3000])), best
