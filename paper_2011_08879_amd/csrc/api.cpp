@@ -195,6 +195,7 @@ struct gko_matrix_s {
     uint8_t *pat_id = nullptr;
     int32_t *pat_tab = nullptr;
     int pat_stride = 0, pat_ints = 0;
+    column_spread spread;           // of the matrix, where may_be_mid
     int64_t n_long = 0;             // CSR rows handled by a workgroup each
     int32_t *long_rows = nullptr;
     void *carry_a = nullptr, *carry_b = nullptr;  // merge / COO carries
@@ -488,6 +489,11 @@ void if_memory_allows(F f) {
 constexpr int64_t kPatternNnz = 1500000;
 bool may_have_patterns(int64_t n, int64_t nnz) {
     return n >= 1 && nnz >= kPatternNnz && nnz / n >= 3;
+}
+
+// Square matrices that the kernels of mid-size systems may take.
+bool may_be_mid(int64_t n, int64_t m, int64_t nnz) {
+    return n == m && n >= 1024 && n <= kMidRows && nnz <= 14000000;
 }
 
 // The row patterns of a CSR matrix from the keys of its rows' lists.
@@ -987,7 +993,8 @@ bool fused_view(gko_matrix A, const values &v, fused_matrix &f) {
 
 // The same for the kernels of mid-size systems (midsize.hip): also CSR stored
 // for merge-path, whose arrays are CSR's, unless its rows are irregular.
-bool mid_view(gko_matrix A, const values &v, fused_matrix &f) {
+// gathers: as mid_fits.
+bool mid_view(gko_matrix A, const values &v, int gathers, fused_matrix &f) {
     if (A->n < 1 || A->nnz < 1) return false;
     if (A->fmt == GKO_FMT_CSR_MERGE && A->merge_rows) {
         f = fused_matrix{};
@@ -999,9 +1006,9 @@ bool mid_view(gko_matrix A, const values &v, fused_matrix &f) {
     } else if (!fused_view(A, v, f)) {
         return false;
     }
-    if (f.format == fused_matrix::csr)
-        f.lanes = A->nnz > 96 * A->n ? 32 : csr_row_lanes(A->n, A->nnz);
-    return mid_fits(f, A->nnz);
+    const mid_shape m{A->nnz, A->max_len, A->spread};
+    if (f.format == fused_matrix::csr) f.lanes = mid_lanes(A->n, m);
+    return mid_fits(f, m, gathers);
 }
 
 // The states and partials that the kernels of a mid-size iteration pass on:
@@ -1206,7 +1213,7 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
     HIPC(scalars_reset(s, S, maxit));
     void *zz = bs > 0 ? w.z : w.r;
     fused_matrix fm;
-    const bool mid = mid_view(A, v, fm);
+    const bool mid = mid_view(A, v, 1, fm);
     const bool fused = !mid && fused_view(A, v, fm);
     mid_flow fl{S, w.partials};
     interval_graph graph(c, w.graphs ? n : kGraphMaxRows + 1);
@@ -1292,7 +1299,7 @@ solve_result pipecg_core(gko_matrix A, const values &v, const void *b, void *x, 
     pv.m = bs > 0 ? m.p : w.p;
     pv.q = bs > 0 ? q.p : sv.p;
     fused_matrix fm;
-    const bool mid = bs == 0 && mid_view(A, v, fm);
+    const bool mid = bs == 0 && mid_view(A, v, 0, fm);
     mid_flow fl{S, partials.as<double>()};
     interval_graph graph(c, n);
     state_reader reader(c, graph.enabled());
@@ -2207,6 +2214,8 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
         }
         HIPC(validate_csr(s, n_rows, n_cols, nnz, rp.as<int32_t>(), col.as<int32_t>(), &f->err));
         HIPC(max_row_len(s, n_rows, rp.as<int32_t>(), &f->max_len));
+        if (may_be_mid(n_rows, n_cols, nnz))
+            HIPC(column_lines(s, n_rows, n_cols, rp.as<int32_t>(), col.as<int32_t>(), f));
         if (may_have_patterns(n_rows, nnz))
             HIPC(pattern_collect(s, n_rows, rp.as<int32_t>(), col.as<int32_t>(), f));
         const csr_facts h = read_back(ctx, f);
@@ -2226,6 +2235,8 @@ gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols
         A->val = val.release();
         try {
             A->max_len = h.max_len;
+            if (h.spread[0] > 0)
+                A->spread = {(float)h.spread[1] / (float)h.spread[0], (float)h.spread[2] / (float)h.spread[0]};
             analyse_csr(A);
             if (may_have_patterns(A->n, A->nnz))
                 if_memory_allows([&] { make_patterns(A, h.patterns); });
@@ -2259,6 +2270,7 @@ gko_status gko_matrix_clone(gko_matrix A, gko_matrix *out) {
             B->row_lanes = A->row_lanes;
             B->merge_rows = A->merge_rows;
             B->max_len = A->max_len;
+            B->spread = A->spread;
             B->slots = A->slots;
             auto copy = [&](const void *src, size_t bytes) -> void * {
                 if (!src) return nullptr;
@@ -2892,7 +2904,7 @@ gko_status gko_bicgstab_solve(gko_matrix A, const void *b, void *x, double tol, 
         dbuf sc(c, kStates * sizeof(krylov_scalars));
         auto *S = sc.as<krylov_scalars>();
         fused_matrix fm;
-        const bool mid = mid_view(A, v, fm);
+        const bool mid = mid_view(A, v, 3, fm);
         const bool fused = !mid && fused_view(A, v, fm);
         dbuf v2(c, mid ? n * 8 : 8);
         mid_flow fl{S, P};
@@ -2956,7 +2968,7 @@ gko_status gko_cgs_solve(gko_matrix A, const void *b, void *x, double tol, int32
         dbuf sc(c, kStates * sizeof(krylov_scalars));
         auto *S = sc.as<krylov_scalars>();
         fused_matrix fm;
-        const bool mid = mid_view(A, v, fm);
+        const bool mid = mid_view(A, v, 3, fm);
         const bool fused = !mid && fused_view(A, v, fm);
         mid_flow fl{S, P};
         HIPC(scalars_reset(s, S, maxit));

@@ -177,6 +177,66 @@ hipError_t row_len_hist(hipStream_t s, int64_t n, const int32_t *rp, int *hist, 
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ column spread
+// A workgroup per tile, at most kSpreadTiles of them evenly over the rows, the
+// first kSpreadEntries of each row, all in flight together: 8 us, whatever
+// the matrix.  The tile's lines are counted by a bit for each line of x in LDS.
+constexpr int kSpreadTiles = 256, kSpreadEntries = 16, kSpreadLine = 16;
+
+__global__ __launch_bounds__(256) void column_lines_kernel(int64_t n, int words,
+                                                           const int32_t *__restrict__ rp,
+                                                           const int32_t *__restrict__ col,
+                                                           csr_facts *facts) {
+    __shared__ unsigned seen[kSpreadCols / kSpreadLine / 32 + 1];
+    __shared__ unsigned sums[3];
+    if (facts->err != 0) return;
+    for (int t = threadIdx.x; t < words; t += 256) seen[t] = 0;
+    if (threadIdx.x < 3) sums[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t tiles = (n + 255) / 256, i = blockIdx.x * tiles / gridDim.x * 256 + threadIdx.x;
+    unsigned entries = 0, lines = 0, fresh = 0;
+    if (i < n) {
+        const int32_t b = rp[i], len = rp[i + 1] - b;
+        const bool first = threadIdx.x % kWave == 0;
+        const int32_t pb = first ? b : rp[i - 1], plen = first ? 0 : b - pb;
+        entries = len < kSpreadEntries ? len : kSpreadEntries;
+        int32_t own[kSpreadEntries], beside[kSpreadEntries];  // lines, -1: none
+#pragma unroll
+        for (int k = 0; k < kSpreadEntries; ++k) {
+            own[k] = k < len ? col[b + k] / kSpreadLine : -1;
+            beside[k] = k < len && k < plen ? col[pb + k] / kSpreadLine : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < kSpreadEntries; ++k)
+            if (own[k] != beside[k]) {  // a line of the neighbouring row's is noted by it
+                ++lines;
+                atomicOr(&seen[own[k] / 32], 1u << own[k] % 32);
+            }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < words; t += 256) fresh += __popc(seen[t]);
+    const unsigned part[3] = {entries, lines, fresh};
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        unsigned v = part[j];
+#pragma unroll
+        for (int s = 1; s < kWave; s <<= 1) v += __shfl_xor(v, s);
+        if (threadIdx.x % kWave == 0) atomicAdd(&sums[j], v);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) atomicAdd(&facts->spread[threadIdx.x], sums[threadIdx.x]);
+}
+
+hipError_t column_lines(hipStream_t s, int64_t n, int64_t m, const int32_t *rp, const int32_t *col,
+                        csr_facts *facts) {
+    if (n == 0 || m == 0) return hipSuccess;
+    if (m > kSpreadCols) return hipErrorInvalidValue;
+    const unsigned g = grid_for(n, 256);
+    const int words = (int)((m - 1) / kSpreadLine / 32 + 1);
+    column_lines_kernel<<<g < kSpreadTiles ? g : kSpreadTiles, 256, 0, s>>>(n, words, rp, col, facts);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ STREAM probe
 // Each thread moves one pair of doubles with 16-byte non-temporal loads and
 // stores, the access shape that measured fastest on MI355X (about 6.6 TB/s

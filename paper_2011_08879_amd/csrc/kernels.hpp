@@ -53,6 +53,7 @@ struct pattern_keys {
 struct csr_facts {
     int err;      // validate_csr, narrow_row_ptr
     int max_len;  // max_row_len
+    unsigned spread[3];  // column_lines: entries, lines, fresh lines
     pattern_keys patterns;
 };
 // Collects the lists of a matrix without errors and without rows longer than
@@ -163,6 +164,18 @@ hipError_t validate_csr(hipStream_t s, int64_t n, int64_t m, int64_t nnz, const 
 hipError_t narrow_row_ptr(hipStream_t s, int64_t n, const int64_t *rp64, int32_t *rp32, int *err);
 hipError_t csr_rows(hipStream_t s, int64_t n, int64_t nnz, const int32_t *rp, int32_t *row);
 hipError_t rows_to_ptr(hipStream_t s, int64_t n, int64_t nnz, const int32_t *row, int32_t *rp);
+// How far apart the lines of x (16 entries) are that a matrix gathers, over a
+// sample of its tiles of 256 rows: the entries looked at, the lines asked for by
+// wavefronts with a row per lane (an entry in the line of the neighbouring row's
+// asks for none), and the different (fresh) lines of each tile.  At most kSpreadCols
+// columns; facts without errors.
+constexpr int64_t kSpreadCols = 2000000;
+hipError_t column_lines(hipStream_t s, int64_t n, int64_t m, const int32_t *rp, const int32_t *col,
+                        csr_facts *facts);
+// The same per entry (none of a matrix that was not looked at).
+struct column_spread {
+    float lines = 0.0f, fresh = 0.0f;
+};
 // maxlen: one device int, must be zero on entry.
 hipError_t max_row_len(hipStream_t s, int64_t n, const int32_t *rp, int *maxlen);
 // hist: maxlen+1 device ints, zero on entry.

@@ -58,6 +58,7 @@ namespace {
 constexpr int kT = 1024, kHalfT = 512;
 inline bool half_blocks(int64_t threads) { return threads <= 256 * kHalfT; }
 constexpr int kPart = 256;        // threads that share one partial
+static_assert(kMidRows <= kSpreadCols, "the columns' spread is known");
 constexpr int kEntries = 8;       // a row's entries loaded before the totals are waited for
 
 // A grid over n rows: one workgroup for each rows_per_block rows if at most
@@ -711,6 +712,15 @@ inline double *md(void *p) { return static_cast<double *>(p); }
 
 }  // namespace
 
+// Four lanes instead of one where the columns are scattered, while the lanes are
+// one round of the chip.  us per iteration, many launches / one lane / four:
+// BiCGSTAB, 30,000 scattered rows of 9 entries 44 / 44 / 30.
+int mid_lanes(int64_t n, const mid_shape &m) {
+    if (m.nnz > 96 * n) return 32;
+    const int lanes = csr_row_lanes(n, m.nnz);
+    return lanes == 1 && n <= 65536 && m.spread.lines > 0.3f ? 4 : lanes;
+}
+
 // Where the gathers of two or three vectors per entry cost less than the
 // launches and vector passes they save (us per iteration, many launches
 // against these).  By rows and entries: CG 7-point 1.3M rows, 9.3M entries 62 /
@@ -728,11 +738,28 @@ inline double *md(void *p) { return static_cast<double *>(p); }
 // block-Jacobi 77 / 107); 5-point 2M rows, 9.8M entries CG 60 / 60, BiCGSTAB 106
 // / 112, CGS in CSR 105 / 113; FP32 with block-Jacobi 1M rows, 6.9M entries 35 /
 // 33, in CSR 34 / 42.
-bool mid_fits(const fused_matrix &A, int64_t nnz) {
+// All of these gather lines that neighbouring rows share.  Otherwise the
+// gathers are what the product waits for, and what they cost is the lines that
+// wavefronts ask for and those that are not in the caches yet (column_spread);
+// the weights and limits are fitted to CG, BiCGSTAB, CGS and pipelined CG on
+// symmetric matrices of 10,000 to 1.6M rows of 5 to 61 entries, columns within
+// 16, 200 or 5,000 of the diagonal or anywhere.  CG / BiCGSTAB, speed against
+// many launches: 100,000 rows of 9 anywhere 1.07 / 1.00, 200,000 rows of 9 0.84 /
+// 0.71 (within 200 1.16 / 1.07), 1M rows of 9 0.46 / 0.40, 400,000 rows of 31
+// 0.45 / 0.32 (pipelined CG, which gathers one vector as the others do, 0.88).
+// Long scattered rows walked by one thread in ELL and
+// SELL-P: 30,000 rows of 15 BiCGSTAB 0.92, 10,000 of 31 CG 0.94, BiCGSTAB 0.84.
+bool mid_fits(const fused_matrix &A, const mid_shape &m, int gathers) {
     const bool f64 = A.t == vt::f64, csr = A.format == fused_matrix::csr;
-    int64_t most = f64 ? 14000000 : 7000000;
+    const int64_t half = f64 ? 1 : 2;
+    int64_t most = 14000000 / half;
     if (A.pat.id) most = f64 ? 8000000 : csr ? 4000000 : 7000000;
-    return A.n <= kMidRows / (f64 ? 1 : 2) && nnz <= most && (csr || nnz <= 48 * A.n);
+    if (A.n > kMidRows / half || m.nnz > most || (!csr && m.nnz > 48 * A.n)) return false;
+    const double lines = m.spread.lines, fresh = m.spread.fresh;
+    const double cost = (double)m.nnz * half * (0.25 * lines * lines + 0.6 * fresh);
+    if (cost > (gathers == 0 ? 1.5e6 : gathers == 1 ? 0.7e6 : 0.42e6)) return false;
+    if (gathers == 0 || csr) return true;
+    return lines <= 0.6 || fresh <= 0.05 || m.longest <= (gathers == 1 ? 40 : 24);
 }
 
 hipError_t mid_cg_product(hipStream_t s, const fused_matrix &A, const void *z, const void *p_old,

@@ -128,8 +128,16 @@ hipError_t cgs_direction(hipStream_t s, int64_t n, const void *r, const void *q,
 constexpr int64_t kMidRows = 2000000;
 constexpr int kMidBlocks = 512;          // workgroups of a grid
 constexpr int kMidParts = 4 * kMidBlocks;  // partials of a sum
-// nnz: entries of A; A.lanes set.
-bool mid_fits(const fused_matrix &A, int64_t nnz);
+// A's rows and columns as the rule for these kernels sees them.
+struct mid_shape {
+    int64_t nnz, longest;
+    column_spread spread;
+};
+// Lanes per row of a CSR matrix in them.
+int mid_lanes(int64_t n, const mid_shape &m);
+// gathers: vectors gathered per entry and iteration beyond one per product;
+// A.lanes set.
+bool mid_fits(const fused_matrix &A, const mid_shape &m, int gathers);
 struct mid_sums {
     double *partials;
     int *parts;

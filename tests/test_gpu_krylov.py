@@ -637,3 +637,56 @@ def test_products_behind_a_solves_end(g, ctx, solver, fmt, block):
         assert info["status"] == g.OK and info["iterations"] == k
         times.append(best_of(5, solve))
     assert times[1] <= 1.25 * times[0], (k, times)
+
+
+# --------------------------------------------------------------------------- which systems take the mid-size kernels
+@pytest.mark.parametrize("solver,products", [("cg", 1), ("bicgstab", 2), ("cgs", 2)])
+def test_iterations_on_scattered_columns(g, ctx, solver, products):
+    """A million rows of 9 scattered entries, whose gathers miss the caches: an
+    iteration takes less than twice its products (it took 2.9 to 3.6 times them
+    where two or three vectors were gathered for each entry)."""
+    import torch
+    n = 1_000_000
+    M = g.Matrix.from_csr(*scattered(n, 8, 1.02))
+    b = torch.rand(n, dtype=torch.float64, device="cuda")
+    x, y = torch.zeros_like(b), torch.empty_like(b)
+
+    def product():
+        for _ in range(20):
+            g.spmv(M, 1.0, b, 0.0, y)
+
+    def solve():
+        x.zero_()
+        return getattr(g, solver)(M, b, x, tol=1e-30, maxit=16)
+
+    info = solve()
+    assert info["iterations"] == 16
+    assert best_of(3, solve) / 16 <= 2 * products * best_of(3, product) / 20
+
+
+@pytest.mark.parametrize("n,per,fmt", [(1500, 6, "csr"), (40_000, 6, "csr"), (40_000, 6, "ell"), (40_000, 3, "sellp"),
+                                       (65_536, 8, "csr"), (65_537, 8, "csr"), (90_000, 14, "csr"), (30_000, 30, "csr"),
+                                       (20_000, 14, "ell"), (250_000, 6, "csr_merge")])
+def test_scattered_systems_match_oracle(g, orc, gen_mod, ctx, n, per, fmt):
+    """Symmetric matrices with scattered columns on either side of the rule that
+    sends a solve to the mid-size kernels, with one and with four lanes per CSR
+    row: the k-step iterates are the oracle's.  Diagonally dominant by a half, so
+    the condition is at most 5 (Gershgorin); bounds as for the banded systems."""
+    rng = np.random.default_rng(n + per)
+    i, j = (rng.integers(0, n, n * per // 2) for _ in range(2))
+    key = np.unique(np.concatenate([i * n + j, j * n + i, np.arange(n) * (n + 1)]))
+    row, col = key // n, key % n
+    lens = np.bincount(row, minlength=n)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    val = np.where(row == col, 1.5 * np.maximum(lens[row] - 1, 1), -1.0)
+    A = (rp, col.astype(np.int32), val)
+    b = orc.spmv(A, gen_mod.uniform(23, n))
+    M = g.Matrix.from_csr(*A).convert(fmt)
+    ctx.set_solver_opts(check_every=5, single_workgroup=0)
+    for solver, k, bound in (("cg", 11, 1e-11), ("fcg", 11, 1e-11), ("pipecg", 9, 1e-11), ("bicgstab", 5, 1e-9),
+                             ("cgs", 4, 1e-9)):
+        rc, xo, info_o = getattr(orc, solver)(A, b, tol=1e-14, maxit=k)
+        x = dev(np.zeros(n))
+        info = getattr(g, solver)(M, dev(b), x, tol=1e-14, maxit=k)
+        assert info["iterations"] == info_o["iters"] == k, (solver, info, info_o)
+        assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo), solver
