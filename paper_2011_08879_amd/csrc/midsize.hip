@@ -712,13 +712,17 @@ inline double *md(void *p) { return static_cast<double *>(p); }
 
 }  // namespace
 
-// Four lanes instead of one where the columns are scattered, while the lanes are
-// one round of the chip.  us per iteration, many launches / one lane / four:
-// BiCGSTAB, 30,000 scattered rows of 9 entries 44 / 44 / 30.
+// A lane walks its share of a row eight entries at a time, then four.  Short
+// rows take the lanes that the mean row length asks for (csr_row_lanes); where
+// some rows are longer, or the columns scattered, four lanes instead of one,
+// while the lanes are one round of the chip.  us per iteration, many launches /
+// one lane / four: BiCGSTAB, 30,000 scattered rows of 9 entries 44 / 44 / 30;
+// CG, 50,000 rows of 5 with ten of 240 39 / 63 / 31, and above that size 200,000
+// such rows 42 / 61 / 39, 800,000 63 / 80 / 78.
 int mid_lanes(int64_t n, const mid_shape &m) {
     if (m.nnz > 96 * n) return 32;
     const int lanes = csr_row_lanes(n, m.nnz);
-    return lanes == 1 && n <= 65536 && m.spread.lines > 0.3f ? 4 : lanes;
+    return lanes == 1 && n <= 65536 && (m.longest > 16 || m.spread.lines > 0.3f) ? 4 : lanes;
 }
 
 // Where the gathers of two or three vectors per entry cost less than the
@@ -747,7 +751,11 @@ int mid_lanes(int64_t n, const mid_shape &m) {
 // many launches: 100,000 rows of 9 anywhere 1.07 / 1.00, 200,000 rows of 9 0.84 /
 // 0.71 (within 200 1.16 / 1.07), 1M rows of 9 0.46 / 0.40, 400,000 rows of 31
 // 0.45 / 0.32 (pipelined CG, which gathers one vector as the others do, 0.88).
-// Long scattered rows walked by one thread in ELL and
+// A CSR row that takes a lane more than one round of loads costs more: from 2M
+// entries on 0.36M rows of 9 0.92 / 0.81, 0.4M of 3 to 17 within 16 1.04 / 0.87,
+// with patterns also rows of 27 on four lanes 0.11M rows 0.95 / 0.83; and a few
+// long rows hold up one lane: 800,000 rows of 5 with ten of 60 entries 1.03 /
+// 0.98, of 100 0.96 / 0.90.  Long scattered rows walked by one thread in ELL and
 // SELL-P: 30,000 rows of 15 BiCGSTAB 0.92, 10,000 of 31 CG 0.94, BiCGSTAB 0.84.
 bool mid_fits(const fused_matrix &A, const mid_shape &m, int gathers) {
     const bool f64 = A.t == vt::f64, csr = A.format == fused_matrix::csr;
@@ -758,7 +766,9 @@ bool mid_fits(const fused_matrix &A, const mid_shape &m, int gathers) {
     const double lines = m.spread.lines, fresh = m.spread.fresh;
     const double cost = (double)m.nnz * half * (0.25 * lines * lines + 0.6 * fresh);
     if (cost > (gathers == 0 ? 1.5e6 : gathers == 1 ? 0.7e6 : 0.42e6)) return false;
-    if (gathers == 0 || csr) return true;
+    if (csr && A.lanes == 1 && m.longest > (gathers == 0 ? 64 : 40)) return false;
+    if (gathers == 0) return true;
+    if (csr) return m.nnz * half <= 2000000 || m.longest <= 8 || (A.lanes > 1 && !A.pat.id);
     return lines <= 0.6 || fresh <= 0.05 || m.longest <= (gathers == 1 ? 40 : 24);
 }
 

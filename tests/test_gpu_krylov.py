@@ -664,6 +664,41 @@ def test_iterations_on_scattered_columns(g, ctx, solver, products):
     assert best_of(3, solve) / 16 <= 2 * products * best_of(3, product) / 20
 
 
+@pytest.mark.parametrize("n", [50_000, 200_000])
+def test_iterations_with_a_few_long_rows(g, ctx, n):
+    """CSR rows of 5 entries, ten of them with 240: one lane may not walk a long
+    row while its workgroup waits.  The iteration takes at most 0.8 of SELL-P's,
+    whose long rows are walked by a thread (0.97 and 0.90 where CSR's were)."""
+    import torch
+    rng = torch.Generator(device="cuda").manual_seed(3)
+    i = torch.arange(n, device="cuda")
+    key = [i * (n + 1)]
+    for d in (1, 2):
+        key += [i[:-d] * n + i[:-d] + d, i[d:] * n + i[d:] - d]
+    hub = torch.randperm(n, generator=rng, device="cuda")[:10].repeat_interleave(240)
+    far = torch.randint(0, n, (2400,), generator=rng, device="cuda")
+    key = torch.unique(torch.cat(key + [hub * n + far, far * n + hub]))
+    row, col = key // n, key % n
+    lens = torch.bincount(row, minlength=n)
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=rp[1:])
+    val = torch.where(row == col, 1.02 * (lens[row] - 1).double(), torch.full_like(row, -1).double())
+    M = g.Matrix.from_csr(rp.int(), col.int(), val)
+    b = torch.rand(n, dtype=torch.float64, device="cuda")
+    x = torch.zeros_like(b)
+    times = []
+    for fmt in ("csr", "sellp"):
+        M.convert(fmt)
+
+        def solve():
+            x.zero_()
+            return g.cg(M, b, x, tol=1e-30, maxit=32)
+
+        assert solve()["iterations"] == 32
+        times.append(best_of(5, solve))
+    assert times[0] <= 0.8 * times[1], times
+
+
 @pytest.mark.parametrize("n,per,fmt", [(1500, 6, "csr"), (40_000, 6, "csr"), (40_000, 6, "ell"), (40_000, 3, "sellp"),
                                        (65_536, 8, "csr"), (65_537, 8, "csr"), (90_000, 14, "csr"), (30_000, 30, "csr"),
                                        (20_000, 14, "ell"), (250_000, 6, "csr_merge")])
