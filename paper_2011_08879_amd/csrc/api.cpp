@@ -3032,12 +3032,12 @@ gko_status gko_gmres_solve(gko_matrix A, const void *b, void *x, double tol, int
         const values v = own_values(A);
         const int64_t ldv = gmres_ld(n);
         dbuf V(c, (size_t)(m + 1) * ldv * 8);
-        if (c->opts.single_workgroup && gmres_small_fits(n, m) &&
+        if (c->opts.single_workgroup && gmres_small_fits(n, A->nnz, m) &&
             (A->fmt == GKO_FMT_CSR || A->fmt == GKO_FMT_CSR_MERGE)) {
             // the whole solve on one workgroup, one launch
             dbuf state(c, sizeof(gmres_state));
             auto *S = state.as<gmres_state>();
-            HIPC(gmres_small(s, n, m, A->rp, A->col, static_cast<const double *>(v.val),
+            HIPC(gmres_small(s, n, A->nnz, m, A->rp, A->col, static_cast<const double *>(v.val),
                              static_cast<const double *>(b), static_cast<double *>(x), V.as<double>(),
                              ldv, tol * bnorm, maxit, S));
             gmres_state h{};

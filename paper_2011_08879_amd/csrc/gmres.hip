@@ -1010,19 +1010,26 @@ hipError_t gmres_cycle_start(hipStream_t s, int64_t n, double *V, gmres_state *s
     return hipGetLastError();
 }
 
-// One workgroup against the compact passes, us per step: GMRES(15) 1,024 rows
-// 15.6 / 28.5, 2,916 rows 26.3 / 30.0, 4,096 rows 32.4 / 29.6; GMRES(30) 1,600
-// rows 28.6 / 29.4, 2,116 rows 34.8 / 30.2; GMRES(60) 1,024 rows 41.5 / 34.6.
-// The workgroup's time grows with the basis entries it passes over, n m.
-bool gmres_small_fits(int64_t n, int m) {
-    return n >= 1 && n <= (int64_t)kSGT * kSGRows && m >= 1 && m <= kGmresSmallKrylov &&
-           n * m <= 50000;
+// us per step, estimated.  One workgroup's time grows with the dots of a step,
+// the basis entries it passes over and the entries of its product (a least
+// squares fit, 5% rms); the compact passes are bound by their launches (31-38, by
+// the process), and pay once per cycle for the start, the update and the host's
+// look at the state.
+// Measured over two cycles, one workgroup / compact passes: 5-point, 400 rows
+// GMRES(50) 29 / 35, (64) 36 / 36; 1,024 rows (40) 29 / 36, (50) 34 / 34, (64)
+// 42 / 38; 2,025 rows (25) 27 / 33, (40) 38 / 35; 4,096 rows (15) 33 / 38, (30)
+// 50 / 33; scattered, 9 entries a row, 500 rows (50) 31 / 38, 1,500 (40) 38 / 36,
+// 4,096 (15) 50 / 40; 40 entries a row, 1,000 rows (10) 36 / 39, (25) 40 / 36.
+bool gmres_small_fits(int64_t n, int64_t nnz, int m) {
+    if (n < 1 || n > (int64_t)kSGT * kSGRows || m < 1 || m > kGmresSmallKrylov) return false;
+    const double one = 14.0 + 0.0044 * m * m + 0.000137 * n * m + 0.00052 * nnz;
+    return one <= 31.0 + 75.0 / m;
 }
 
-hipError_t gmres_small(hipStream_t s, int64_t n, int m, const int32_t *rp, const int32_t *col,
-                       const double *val, const double *b, double *x, double *V, int64_t ldv,
-                       double stop, int maxit, gmres_state *out) {
-    if (!gmres_small_fits(n, m)) return hipErrorInvalidValue;
+hipError_t gmres_small(hipStream_t s, int64_t n, int64_t nnz, int m, const int32_t *rp,
+                       const int32_t *col, const double *val, const double *b, double *x, double *V,
+                       int64_t ldv, double stop, int maxit, gmres_state *out) {
+    if (!gmres_small_fits(n, nnz, m)) return hipErrorInvalidValue;
     gmres_small_kernel<<<1, kSGT, 0, s>>>(n, m, rp, col, val, b, x, V, ldv, stop, maxit, out);
     return hipGetLastError();
 }

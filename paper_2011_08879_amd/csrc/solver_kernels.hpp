@@ -186,7 +186,7 @@ hipError_t mid_cgs_close(hipStream_t s, const scalar_link &k);
 // leave the new one in next (the caller swaps the two); otherwise they update
 // st in place.
 constexpr int kGmresMaxKrylov = 128;   // largest restart length
-constexpr int kGmresSmallKrylov = 40;  // largest restart length of the one-workgroup solve
+constexpr int kGmresSmallKrylov = 64;  // largest restart length of the one-workgroup solve
 constexpr int kGmresMaxBlocks = 2048;  // grid of the multi-vector passes (1024: 12% slower)
 struct gmres_state {
     double stop;        // tol * ||b||
@@ -221,13 +221,14 @@ hipError_t gmres_arnoldi_step(hipStream_t s, int64_t n, int m, int j, double *V,
                               gmres_state *st, gmres_state *next, const gmres_work &wk);
 hipError_t gmres_cycle_end(hipStream_t s, int64_t n, int m, const double *V, int64_t ldv, double *x,
                            gmres_state *st, const gmres_work &wk);
-// The whole solve of a small CSR system (gmres_small_fits(n, m)) in one launch of one workgroup, from x (in/out), with
-// the basis in V ((m + 1) ldv doubles).  out: iter, cycles, reorths, done,
-// est, beta, k as the multi-kernel path leaves them in gmres_state.
-bool gmres_small_fits(int64_t n, int m);
-hipError_t gmres_small(hipStream_t s, int64_t n, int m, const int32_t *rp, const int32_t *col,
-                       const double *val, const double *b, double *x, double *V, int64_t ldv,
-                       double stop, int maxit, gmres_state *out);
+// The whole solve of a small CSR system (gmres_small_fits) in one launch of one
+// workgroup, from x (in/out), with the basis in V ((m + 1) ldv doubles).  out:
+// iter, cycles, reorths, done, est, beta, k as the multi-kernel path leaves them
+// in gmres_state.
+bool gmres_small_fits(int64_t n, int64_t nnz, int m);
+hipError_t gmres_small(hipStream_t s, int64_t n, int64_t nnz, int m, const int32_t *rp,
+                       const int32_t *col, const double *val, const double *b, double *x, double *V,
+                       int64_t ldv, double stop, int maxit, gmres_state *out);
 
 // Mixed precision helpers.
 hipError_t scaled_cast(hipStream_t s, int64_t n, const double *r, const double *norm, float *rt);

@@ -597,6 +597,48 @@ def test_gmres_products_behind_a_cycles_end(g, ctx, n, graphs):
     assert best_of(3, solve) <= best_of(3, products) * 40 / 16 + 0.004
 
 
+class counting_context:
+    """A context whose allocator notes the bytes of every buffer handed out."""
+
+    def __init__(self, g):
+        import torch
+        self.ctx, self.sizes, device = g.Context(use_torch_allocator=False), [], torch.cuda.current_device()
+
+        def alloc(nbytes, stream, user):
+            self.sizes.append(nbytes)
+            return torch.cuda.caching_allocator_alloc(int(nbytes), device, stream or 0)
+
+        def dealloc(p, stream, user):
+            torch.cuda.caching_allocator_delete(p)
+
+        self.ctx._cbs = (g.ALLOC_FN(alloc), g.DEALLOC_FN(dealloc))
+        assert g._lib.gko_context_set_allocator(self.ctx.handle, self.ctx._cbs[0], self.ctx._cbs[1], None) == g.OK
+
+
+@pytest.mark.parametrize("N,m,one", [(16, 44, True), (20, 50, True), (32, 40, True), (45, 25, True), (64, 15, True),
+                                     (64, 20, False), (45, 40, False), (32, 64, False)])
+def test_gmres_one_workgroup_where_it_is_faster(g, orc, gen_mod, N, m, one):
+    """Which cycles run on one workgroup (seen from the buffers of the solve:
+    those that do need no partial sums): those of up to about 32 us a step,
+    also of more than 40 steps or 50,000 basis entries.  Two full cycles match
+    the oracle on either path."""
+    A = gen_mod.convdiff2d(N, 0.5)
+    n = N * N
+    b = gen_mod.uniform(5, n)
+    rc, xo, _ = orc.gmres(A, b, tol=1e-30, maxit=2 * m, m=m)
+    c = counting_context(g)
+    M, held = g.Matrix.from_csr(*A, ctx=c.ctx), {}
+    for single in (1, 0):
+        c.ctx.set_solver_opts(krylov_dim=m, single_workgroup=single)
+        x = dev(np.zeros(n))
+        c.sizes.clear()
+        info = g.gmres(M, dev(b), x, tol=1e-30, maxit=2 * m)
+        held[single] = sorted(c.sizes)
+        assert info["status"] == g.ERR_NOT_CONVERGED and info["iterations"] == 2 * m, info
+        assert np.linalg.norm(host(x) - xo) <= 1e-9 * np.linalg.norm(xo)
+    assert (sum(held[1]) < sum(held[0])) if one else held[1] == held[0], held
+
+
 @pytest.mark.parametrize("solver,fmt,block", [("cg", "coo", 0), ("bicgstab", "hybrid", 0), ("cgs", "csr", 0),
                                               ("fcg", "csr_merge", 0), ("pipecg", "csr", 4)])
 def test_products_behind_a_solves_end(g, ctx, solver, fmt, block):
