@@ -1172,7 +1172,7 @@ krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader 
 // kernel (no graph is instantiated).
 struct cg_workspace {
     void *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;
-    void *p2 = nullptr;  // mid-size systems: p's second buffer
+    void *p2 = nullptr;  // p's second buffer, of systems that take the mid-size kernels
     double *partials = nullptr, *nrm = nullptr;
     unsigned *ticket = nullptr;
     krylov_scalars *S = nullptr;
@@ -1181,17 +1181,18 @@ struct cg_workspace {
 
 struct cg_buffers {
     dbuf r, p, q, z, p2, partials, ticket, sc, nrm;
-    cg_buffers(gko_context c, int64_t n, size_t vb, int bs)
+    bool mid;
+    cg_buffers(gko_context c, int64_t n, size_t vb, int bs, bool mid)
         : r(c, n * vb), p(c, n * vb), q(c, n * vb), z(c, bs > 0 ? n * vb : 8),
-          p2(c, n <= kMidRows ? n * vb : 8), partials(c, kPartialBytes), ticket(c, 8),
-          sc(c, kStates * sizeof(krylov_scalars)), nrm(c, 8) {}
+          p2(c, mid ? n * vb : 8), partials(c, kPartialBytes), ticket(c, 8),
+          sc(c, kStates * sizeof(krylov_scalars)), nrm(c, 8), mid(mid) {}
     cg_workspace view() {
         cg_workspace w;
         w.r = r.p;
         w.p = p.p;
         w.q = q.p;
         w.z = z.p;
-        w.p2 = p2.p;
+        w.p2 = mid ? p2.p : nullptr;
         w.partials = partials.as<double>();
         w.nrm = nrm.as<double>();
         w.ticket = ticket.as<unsigned>();
@@ -1213,7 +1214,7 @@ solve_result cg_core(gko_matrix A, const values &v, const void *b, void *x, doub
     HIPC(scalars_reset(s, S, maxit));
     void *zz = bs > 0 ? w.z : w.r;
     fused_matrix fm;
-    const bool mid = mid_view(A, v, 1, fm);
+    const bool mid = w.p2 && mid_view(A, v, 1, fm);
     const bool fused = !mid && fused_view(A, v, fm);
     mid_flow fl{S, w.partials};
     interval_graph graph(c, w.graphs ? n : kGraphMaxRows + 1);
@@ -1361,7 +1362,8 @@ solve_result cg_variant_core(cg_variant var, gko_matrix A, const values &v, cons
                              bool true_check) {
     if (var == cg_variant::pipelined)
         return pipecg_core(A, v, b, x, tol, maxit, inv, bs, check_every, true_check);
-    cg_buffers buf(A->ctx, A->n, vsize(v.t), bs);
+    fused_matrix fm;
+    cg_buffers buf(A->ctx, A->n, vsize(v.t), bs, mid_view(A, v, 1, fm));
     return cg_core(A, v, b, x, tol, maxit, inv, bs, check_every, true_check,
                    var == cg_variant::flexible, buf.view());
 }

@@ -767,3 +767,20 @@ def test_scattered_systems_match_oracle(g, orc, gen_mod, ctx, n, per, fmt):
         info = getattr(g, solver)(M, dev(b), x, tol=1e-14, maxit=k)
         assert info["iterations"] == info_o["iters"] == k, (solver, info, info_o)
         assert np.linalg.norm(host(x) - xo) <= bound * np.linalg.norm(xo), solver
+
+
+@pytest.mark.parametrize("solver", ["cg", "fcg"])
+@pytest.mark.parametrize("fmt,second", [("csr", True), ("sellp", True), ("coo", False)])
+def test_second_direction_held_where_it_is_used(g, gen_mod, solver, fmt, second):
+    """A CG solve holds a second direction vector only where the kernels that
+    alternate between two run: on a COO matrix it holds r, p and q."""
+    N = 150
+    n = N * N
+    c = counting_context(g)
+    M = g.Matrix.from_csr(*gen_mod.laplace2d(N), ctx=c.ctx)
+    M.convert(fmt)
+    b, x = dev(gen_mod.uniform(6, n)), dev(np.zeros(n))
+    c.sizes.clear()
+    info = getattr(g, solver)(M, b, x, tol=1e-8, maxit=2000)
+    assert info["status"] == g.OK and info["true_rel_residual"] <= 1e-8, info
+    assert sum(z == 8 * n for z in c.sizes) == (4 if second else 3), sorted(c.sizes)
