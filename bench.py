@@ -19,7 +19,10 @@ The paper's own model (Sec. 6.1) counts only the matrix entries: 12 bytes per
 CSR entry and 16 per COO entry.  The padded formats count their stored slots,
 padding included, although their kernels stop at a row's first padding slot;
 per_kernel reports those unread bytes beside the figure (on the stencil
-10.6 MB, 1.5% of ELL's bytes: the shorter rows at the grid's faces).
+10.6 MB, 1.5% of ELL's bytes: the shorter rows at the grid's faces).  The
+bytes are those of the formats: the stencil's CSR, ELL and HYBRID products,
+which take the columns from its repeating lists of column offsets, do not
+read the 4 bytes of an entry's index that are counted here.
 
 After the timed sweep (outside it): CG on the 2D 5-point Laplacian 64x64
 (to 1e-10), and block-Jacobi PCG on the 3D 7-point Poisson 256^3 in FP64 and
@@ -830,6 +833,8 @@ def run_sweep(args, g, gen, torch, result):
                                "n=1e6 (mean 16, max 10000); one SpMV per format and matrix per step",
                    "frac_hbm_peak": round(value / HBM_PEAK_GBS, 4),
                    "step_alg_bytes": int(step_bytes),
+                   "byte_model": "bytes of the formats; the stencil's csr, ell and hybrid products "
+                                 "do not read the column indices counted here",
                    "wall_s_timed": round(wall, 4),
                    "skipped": skipped},
         "roofline": roofline,

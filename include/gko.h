@@ -112,10 +112,11 @@ gko_status gko_context_set_allocator(gko_context ctx, gko_alloc_fn alloc,
  *   col_idx : nnz int32 columns in [0, n_cols), strictly increasing per row.
  *   values  : nnz values of type dt.
  * The structure is validated on the device; a violation returns
- * GKO_ERR_INVALID_ARG and creates nothing.  Of a matrix with at least a
- * million entries whose rows repeat a few lists of column offsets (a stencil
- * on a grid) the handle also keeps these lists, a byte per row and 4 KB, for
- * products that need not read the columns; memory permitting. */
+ * GKO_ERR_INVALID_ARG and creates nothing.  Of a matrix with at least 1.5
+ * million entries, at least three per row and no row of more than 40, whose
+ * rows repeat a few lists of column offsets (a stencil on a grid), the handle
+ * also keeps these lists, a byte per row and up to 4 KB, for products that need
+ * not read the columns; memory permitting. */
 gko_status gko_matrix_create_csr(gko_context ctx, int64_t n_rows, int64_t n_cols, int64_t nnz,
                                  gko_dtype dt, const void *row_ptr, gko_itype row_ptr_type,
                                  const int32_t *col_idx, const void *values, gko_matrix *out);
@@ -221,7 +222,9 @@ typedef struct gko_solver_opts {
     int32_t precision;   /* gko_precision; MIXED_IR = FP64 refinement around an FP32 inner PCG */
     int32_t precond;     /* gko_precond */
     int32_t block_size;  /* block-Jacobi block size: 1, 2, 4, 8 or 16 (default 8) */
-    int32_t check_every; /* host convergence polls every this many iterations (default 16) */
+    int32_t check_every; /* host convergence polls every this many iterations (default 16;
+                            an odd number is rounded up by the kernels that alternate between
+                            two buffers of a vector); does not change the results */
     double inner_tol;    /* MIXED_IR: inner relative tolerance (default 1e-5) */
     int32_t max_inner;   /* MIXED_IR: inner iteration cap per outer step (default 1000) */
     int32_t max_outer;   /* MIXED_IR: outer step cap (default 20) */
@@ -234,11 +237,16 @@ typedef struct gko_solver_opts {
                                  Same steps and stopping tests either way. */
     int32_t krylov_dim;  /* GMRES restart length m, 1..128 (default 30) */
     int32_t graphs;      /* 1 (default): on matrices of at most 2^20 rows, the multi-kernel
-                            CG, flexible CG, pipelined CG, BiCGSTAB and CGS loops capture one
-                            polling interval (check_every iterations of kernel launches) into
-                            a HIP graph once per solve and replay it on the context stream;
-                            0: always launch kernel by kernel.  The graph holds the same
-                            kernels with the same arguments, so results are identical. */
+                            CG, flexible CG, pipelined CG, BiCGSTAB and CGS loops launch their
+                            first polling interval (check_every iterations) kernel by kernel,
+                            and their second too where it is enqueued before the first one's
+                            outcome is known (loops whose kernels all return at once after the
+                            solve's end).  The next one is captured into a HIP graph, once per
+                            solve, and replayed on the context stream from then on.  GMRES
+                            stays kernel by kernel, but goes on enqueuing steps while it reads
+                            its state (up to 2 million entries and 524,288 rows).  0: always
+                            launch kernel by kernel and wait at every poll.  The same kernels
+                            with the same arguments either way, so results are identical. */
 } gko_solver_opts;
 
 typedef struct gko_solve_info {

@@ -873,8 +873,8 @@ void ensure_block_jacobi(gko_matrix A, int bs, bool need32) {
 // Copies of a solver's device state that the host looks at later: ask()
 // enqueues one on the context stream, get() waits for the oldest, and what is
 // enqueued in between runs while the host waits.  At most two are under way.
-// They land in pinned memory of the context; a solve that finds it taken (by a
-// solve on another thread) does without, as does one that asked for none.
+// They land in pinned memory of the context, which one reader has at a time;
+// a second one does without, as does one that was not wanted.
 class state_reader {
   public:
     static constexpr size_t kSlot = 256;
@@ -1035,10 +1035,10 @@ static_assert(3 * 3 * kMidParts * sizeof(double) <= kPartialBytes, "three region
 int mid_interval(int check_every) { return check_every + check_every % 2; }
 
 // One polling interval of a solver loop (check_every iterations of kernel
-// launches) as a HIP graph: the first run() captures the body's launches on a
-// stream of its own, which the body sees as the context stream, and every
-// run() replays them on the context stream with one call instead of one
-// enqueue per kernel.  The body must only launch kernels: no allocation, copy,
+// launches) as a HIP graph: prepare(), or the first run(), captures the body's
+// launches on a stream of its own, which the body sees as the context stream,
+// and every run() replays them on the context stream with one call instead of
+// one enqueue per kernel.  The body must only launch kernels: no allocation, copy,
 // memset or synchronization.  Disabled, run() calls the body directly.
 // Used for matrices of at most kGraphMaxRows rows: Poisson 3D, per iteration,
 // 32^3 rows CG 21.1 -> 17.9 us and BiCGSTAB 34.5 -> 27.4 us; 128^3 and 256^3
@@ -1168,8 +1168,8 @@ krylov_scalars run_intervals(gko_context c, interval_graph &graph, state_reader 
 // preconditioner) of n values, the grid reductions' partials and ticket, the
 // iteration scalars and a norm slot.  The solvers allocate them per call
 // (cg_buffers); gko_cg_solve_noalloc carves them from the library's static
-// scratch array instead (S: kStates states).  graphs = false keeps the iteration kernel by
-// kernel (no graph is instantiated).
+// scratch array instead (S: kStates states).  graphs = false keeps the
+// iteration kernel by kernel (no graph is instantiated).
 struct cg_workspace {
     void *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;
     void *p2 = nullptr;  // p's second buffer, of systems that take the mid-size kernels

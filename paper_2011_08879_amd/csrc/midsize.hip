@@ -33,11 +33,12 @@
 // 29.6 -> 26.9 us).
 // Per iteration, five to nine launches against these (64 iterations, the
 // solve's start and the host's polls included, all workgroups of 1024
-// threads; kHalfT below has what smaller ones gave on top): CG on the 3D Poisson matrix (SELL-P) 16^3 rows 19.4
-// -> 16.9 us, 48^3 22.8 -> 17.8, 64^3 26.5 -> 19.4, 110^3 60.6 -> 51.3;
-// block-Jacobi(8) CG 48^3 24.1 -> 20.1; pipelined CG 48^3 18.2 -> 14.6, 110^3
-// 62 -> 48.5; BiCGSTAB on 250^2 convection-diffusion (ELL) 48.6 -> 33.6, 500^2
-// 57.5 -> 36.4; CGS 250^2 59.6 -> 39.1.
+// threads; kHalfT below has what smaller ones gave on top): CG on the 3D
+// Poisson matrix (SELL-P) 16^3 rows 19.4 -> 16.9 us, 48^3 22.8 -> 17.8, 64^3
+// 26.5 -> 19.4, 110^3 60.6 -> 51.3; block-Jacobi(8) CG 48^3 24.1 -> 20.1;
+// pipelined CG 48^3 18.2 -> 14.6, 110^3 62 -> 48.5; BiCGSTAB on 250^2
+// convection-diffusion (ELL) 48.6 -> 33.6, 500^2 57.5 -> 36.4; CGS 250^2 59.6 ->
+// 39.1.
 #include <cmath>
 
 #include "bj_tile.hpp"

@@ -122,9 +122,11 @@ hipError_t cgs_update(hipStream_t s, int64_t n, void *r, const void *t, const vo
 hipError_t cgs_direction(hipStream_t s, int64_t n, const void *r, const void *q, void *u, void *p,
                          const krylov_scalars *sc);
 
-// Iterations of systems that mid_fits accepts, at most kMidRows rows (midsize.hip).  Each kernel
-// takes its scalars by a scalar_link and leaves its sums as *parts partials
-// each (up to 3 * kMidParts doubles).  lanes of a CSR matrix: 1, 4, 8 or 32.  p / p_old (and v / v_old, w / w_old) are different buffers.
+// Iterations of systems that mid_fits accepts, at most kMidRows rows
+// (midsize.hip).  Each kernel takes its scalars by a scalar_link and leaves its
+// sums as *parts partials each (up to 3 * kMidParts doubles).  lanes of a CSR
+// matrix: 1, 4, 8 or 32.  p / p_old (and v / v_old, w / w_old) are different
+// buffers.
 constexpr int64_t kMidRows = 2000000;
 constexpr int kMidBlocks = 512;          // workgroups of a grid
 constexpr int kMidParts = 4 * kMidBlocks;  // partials of a sum

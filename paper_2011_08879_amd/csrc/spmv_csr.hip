@@ -271,9 +271,9 @@ hipError_t spmv_csr(hipStream_t s, vt t, int64_t n, const int32_t *rp, const int
 // long the rows.  Tiles of 4 items per thread measured best (2048
 // items 301 us, 1024 236 us, 512 275 us on the stencil, one workgroup per
 // tile).  The staged products are padded by one slot per 8, so the threads'
-// walks, which start about IPT entries apart, fall into different LDS banks.  Rows crossing tile boundaries
-// leave a carry per tile, added by a second kernel in ascending tile order,
-// so results are bitwise repeatable.
+// walks, which start about IPT entries apart, fall into different LDS banks.
+// Rows crossing tile boundaries leave a carry per tile, added by a second
+// kernel in ascending tile order, so results are bitwise repeatable.
 constexpr int kMergeBlock = 256;
 constexpr int kMergeIpt = 4;
 constexpr int kMergeTile = kMergeBlock * kMergeIpt;
