@@ -11,9 +11,9 @@
 //               first round shrank w below 1/sqrt(2) of its length (Daniel,
 //               Gragg, Kaufman and Stewart's criterion); otherwise the
 //               launch returns at once
-//   step        (one thread) the column of H, the earlier rotations, the new
-//               Givens rotation, |g_{j+1}| as the residual estimate, the end
-//               of the cycle
+//   step        (one wavefront; the rotations in series on one lane) the
+//               column of H, the earlier rotations, the new Givens rotation,
+//               |g_{j+1}| as the residual estimate, the end of the cycle
 //   normalise   v_{j+1} = w / h_{j+1,j}
 // The basis is column-major with a leading dimension rounded up to 64
 // doubles.  The multi-vector passes keep each thread's rows of w in
@@ -21,7 +21,8 @@
 // per-vector sums are wave DPP reductions accumulated per wave in LDS, then
 // per-block partials summed in block order by a one-block-per-value kernel,
 // so every result repeats bitwise.  A cycle ends with the back substitution
-// (one thread) and x += V_k y in one pass.
+// (one workgroup, by column panels) and x += V_k y in one pass.  Up to
+// kCompactMaxRows rows the compact passes below take their place.
 #include <cmath>
 
 #include "device.hpp"
