@@ -1012,19 +1012,21 @@ hipError_t gmres_cycle_start(hipStream_t s, int64_t n, double *V, gmres_state *s
 }
 
 // us per step, estimated.  One workgroup's time grows with the dots of a step,
-// the basis entries it passes over and the entries of its product (a least
-// squares fit, 5% rms); the compact passes are bound by their launches (31-38, by
-// the process), and pay once per cycle for the start, the update and the host's
-// look at the state.
-// Measured over two cycles, one workgroup / compact passes: 5-point, 400 rows
-// GMRES(50) 29 / 35, (64) 36 / 36; 1,024 rows (40) 29 / 36, (50) 34 / 34, (64)
-// 42 / 38; 2,025 rows (25) 27 / 33, (40) 38 / 35; 4,096 rows (15) 33 / 38, (30)
-// 50 / 33; scattered, 9 entries a row, 500 rows (50) 31 / 38, 1,500 (40) 38 / 36,
-// 4,096 (15) 50 / 40; 40 entries a row, 1,000 rows (10) 36 / 39, (25) 40 / 36.
+// the basis entries it passes over and the entries of its product; the compact
+// passes are bound by their launches, whose number grows little with m, and pay
+// once per cycle for the start, the update and the host's look at the state.
+// Least squares over solves of two and of ten whole cycles, 15 sizes, m = 5 to
+// 64; the side taken was at most 7% slower than the other, but for data on which
+// the second Gram-Schmidt round is rare.  Two cycles, one workgroup / compact:
+// 5-point, 225 rows GMRES(50) 29.5 / 30.0, (64) 36.4 / 32.1; 1,024 rows (30) 24.2
+// / 26.5, (50) 35.1 / 30.6; 2,025 rows (20) 25.4 / 29.2, (25) 28.7 / 28.3; 4,096
+// rows (10) 29.9 / 35.4, (15) 34.4 / 31.0, (30) 51.5 / 28.4; scattered, 1,500
+// rows of 9 (20) 27.4 / 30.3, (30) 32.9 / 29.1, of 21 (15) 34.2 / 31.5; 4,096 of
+// 21 (10) 76 / 36.
 bool gmres_small_fits(int64_t n, int64_t nnz, int m) {
     if (n < 1 || n > (int64_t)kSGT * kSGRows || m < 1 || m > kGmresSmallKrylov) return false;
-    const double one = 14.0 + 0.0044 * m * m + 0.000137 * n * m + 0.00052 * nnz;
-    return one <= 31.0 + 75.0 / m;
+    const double one = 12.0 + 0.005 * m * m + 0.00016 * n * m + 0.0006 * nnz;
+    return one <= 17.0 + 0.24 * m + 125.0 / m;
 }
 
 hipError_t gmres_small(hipStream_t s, int64_t n, int64_t nnz, int m, const int32_t *rp,
